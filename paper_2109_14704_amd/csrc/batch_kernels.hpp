@@ -16,8 +16,8 @@ namespace hentt {
 
 struct BatchUnit {        // one (polynomial, limb) of a job
   uint64_t *data;         // N words, in place
-  const Tw *tw;           // this limb's table for the launch direction
-  const LimbConst *lc;    // this limb's constants
+  const TwM *tw;           // this limb's table for the launch direction
+  const NttConst *lc;    // this limb's constants
   uint32_t logn;          // 12 .. 17
   uint32_t pass1;         // pass-1 tiles of this unit (0: one whole-transform tile)
 };
@@ -33,24 +33,26 @@ enum { BATCH_B = 12, BATCH_E = 4, BATCH_LANES = 256 };
 // of a word made the uneven workload 18% slower.
 
 // Forward block pass (stages logn-12 .. logn-1) on the 2^12 words at p.
-__device__ __forceinline__ void batch_fwd_block(uint64_t *p, uint32_t blockStart, uint32_t logn, const Tw *t,
-                                                const LimbConst &c, uint64_t *lds, uint32_t tid) {
+template <bool FIX>
+__device__ __forceinline__ void batch_fwd_block(uint64_t *p, uint32_t blockStart, uint32_t logn, const TwM *t,
+                                                const NttConst &c, uint64_t *lds, uint32_t tid) {
   using F = FwdFirst<BATCH_B, BATCH_E>;
   uint64_t v[1 << BATCH_E];
   load_global<BATCH_B, BATCH_E, F::LO, F::R>(v, p, RoundMap<BATCH_B, BATCH_E, F::LO, F::R>::lane_part(tid));
-  fwd_block_rounds<BATCH_B, BATCH_E, F::LO, F::R>(v, logn, lds, tid, blockStart, t, c.m);
-  reduce_fwd<BATCH_E>(v, c.m, c.mu, c.k);
+  fwd_block_rounds<BATCH_B, BATCH_E, F::LO, F::R, FIX>(v, logn, lds, tid, blockStart, t, c);
+  reduce_out<BATCH_E, FIX>(v, c);
   store_global_m0<BATCH_B, BATCH_E>(v, p, lds, tid);
 }
 
 // Inverse block pass (stages 0 .. 11); canonical when it is the whole transform.
-__device__ __forceinline__ void batch_inv_block(uint64_t *p, uint32_t blockStart, uint32_t logn, const Tw *it,
-                                                const LimbConst &c, uint64_t *lds, uint32_t tid) {
+template <bool FIX>
+__device__ __forceinline__ void batch_inv_block(uint64_t *p, uint32_t blockStart, uint32_t logn, const TwM *it,
+                                                const NttConst &c, uint64_t *lds, uint32_t tid) {
   using L = InvLast<BATCH_B, BATCH_E>;
   uint64_t v[1 << BATCH_E];
   load_global_m0_fresh<BATCH_B, BATCH_E>(v, p, lds, tid);  // the previous tile ended with a barrier
-  inv_block_rounds<BATCH_B, BATCH_E, 0, BATCH_E>(v, logn, lds, tid, blockStart, it, c);
-  if (logn == BATCH_B) reduce_inv<BATCH_E>(v, c.m);
+  inv_block_rounds<BATCH_B, BATCH_E, 0, BATCH_E, FIX>(v, logn, lds, tid, blockStart, it, c);
+  if (logn == BATCH_B) reduce_out<BATCH_E, FIX>(v, c);
   store_global<BATCH_B, BATCH_E, L::LO, L::R>(v, p, RoundMap<BATCH_B, BATCH_E, L::LO, L::R>::lane_part(tid));
 }
 
@@ -72,9 +74,9 @@ __device__ __forceinline__ const uint64_t *opaque_s(const uint64_t *p) {
 
 // Column pass of 2^EC stages (N = 2^(12+EC)) on a tile of 4096 coefficients:
 // 256 lanes x CPL columns each (CPL = 16 / 2^EC, at least 1).
-template <int EC, bool INV>
-__device__ __forceinline__ void batch_cols(uint64_t *p, uint32_t tile, uint32_t tid, const Tw *t,
-                                           const LimbConst &c) {
+template <int EC, bool INV, bool FIX>
+__device__ __forceinline__ void batch_cols(uint64_t *p, uint32_t tile, uint32_t tid, const TwM *t,
+                                           const NttConst &c) {
   constexpr int LOGN = BATCH_B + EC, LO = BATCH_B;
   constexpr uint32_t CPL = EC >= 4 ? 1u : (16u >> EC);
 #pragma unroll
@@ -85,10 +87,10 @@ __device__ __forceinline__ void batch_cols(uint64_t *p, uint32_t tile, uint32_t 
 #pragma unroll
     for (int s = 0; s < (1 << EC); ++s) v[s] = gload<false>(col_elem<LOGN, EC>(pl, s), col);
     if constexpr (!INV) {
-      fwd_round<LOGN, EC, LO, EC, 0>(v, LOGN, 0, col, t, c.m);
+      fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, t, c);
     } else {
-      inv_round<LOGN, EC, LO, EC>(v, LOGN, 0, col, t, c);
-      reduce_inv<EC>(v, c.m);
+      inv_round<LOGN, EC, LO, EC, 4, 4, FIX>(v, LOGN, 0, col, t, c);
+      reduce_out<EC, FIX>(v, c);
     }
     const uint64_t *ps = opaque_s(p);
 #pragma unroll
@@ -96,15 +98,15 @@ __device__ __forceinline__ void batch_cols(uint64_t *p, uint32_t tile, uint32_t 
   }
 }
 
-template <bool INV>
+template <bool INV, bool FIX>
 __device__ __forceinline__ void batch_cols_any(uint32_t logn, uint64_t *p, uint32_t tile, uint32_t tid,
-                                               const Tw *t, const LimbConst &c) {
+                                               const TwM *t, const NttConst &c) {
   switch (logn) {
-    case 13: batch_cols<1, INV>(p, tile, tid, t, c); break;
-    case 14: batch_cols<2, INV>(p, tile, tid, t, c); break;
-    case 15: batch_cols<3, INV>(p, tile, tid, t, c); break;
-    case 16: batch_cols<4, INV>(p, tile, tid, t, c); break;
-    default: batch_cols<5, INV>(p, tile, tid, t, c); break;
+    case 13: batch_cols<1, INV, FIX>(p, tile, tid, t, c); break;
+    case 14: batch_cols<2, INV, FIX>(p, tile, tid, t, c); break;
+    case 15: batch_cols<3, INV, FIX>(p, tile, tid, t, c); break;
+    case 16: batch_cols<4, INV, FIX>(p, tile, tid, t, c); break;
+    default: batch_cols<5, INV, FIX>(p, tile, tid, t, c); break;
   }
 }
 
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(BATCH_LANES, 4) void k_batch(const BatchUnit *__res
     const BatchTile tile = tiles[q0 + ti];
     const BatchUnit u = units[tile.unit];
     const uint32_t kind = tile.kind_idx >> 16, idx = tile.kind_idx & 0xffffu;
-    const LimbConst c = ld_lc(u.lc);
+    const NttConst c = ld_nc(u.lc);
     if (kind == BT_PASS2) {
       if (tid == 0) {
         uint32_t spins = 0, ok = 1;
@@ -175,15 +177,18 @@ __global__ __launch_bounds__(BATCH_LANES, 4) void k_batch(const BatchUnit *__res
         continue;
       }
     }
-    if constexpr (!INV) {
-      if (kind == BT_WHOLE) batch_fwd_block(u.data, 0, BATCH_B, u.tw, c, lds, tid);
-      else if (kind == BT_PASS1) batch_cols_any<false>(u.logn, u.data, idx, tid, u.tw, c);
-      else batch_fwd_block(u.data + ((uint64_t)idx << BATCH_B), idx << BATCH_B, u.logn, u.tw, c, lds, tid);
-    } else {
-      if (kind == BT_WHOLE) batch_inv_block(u.data, 0, BATCH_B, u.tw, c, lds, tid);
-      else if (kind == BT_PASS1) batch_inv_block(u.data + ((uint64_t)idx << BATCH_B), idx << BATCH_B, u.logn, u.tw, c, lds, tid);
-      else batch_cols_any<true>(u.logn, u.data, idx, tid, u.tw, c);
-    }
+    by_class(c, [&](auto FX) __attribute__((always_inline)) {
+      constexpr bool FIX = decltype(FX)::value;
+      if constexpr (!INV) {
+        if (kind == BT_WHOLE) batch_fwd_block<FIX>(u.data, 0, BATCH_B, u.tw, c, lds, tid);
+        else if (kind == BT_PASS1) batch_cols_any<false, FIX>(u.logn, u.data, idx, tid, u.tw, c);
+        else batch_fwd_block<FIX>(u.data + ((uint64_t)idx << BATCH_B), idx << BATCH_B, u.logn, u.tw, c, lds, tid);
+      } else {
+        if (kind == BT_WHOLE) batch_inv_block<FIX>(u.data, 0, BATCH_B, u.tw, c, lds, tid);
+        else if (kind == BT_PASS1) batch_inv_block<FIX>(u.data + ((uint64_t)idx << BATCH_B), idx << BATCH_B, u.logn, u.tw, c, lds, tid);
+        else batch_cols_any<true, FIX>(u.logn, u.data, idx, tid, u.tw, c);
+      }
+    });
     if (kind == BT_PASS1) {
       __builtin_amdgcn_s_waitcnt(0);  // this lane's stores have reached the XCD's L2
       __syncthreads();

@@ -23,8 +23,8 @@ struct GroupJob {
     ColArgs ca;
     ProdArgs pa;
   };
-  const Tw *tw;           // [limbs][2][N]
-  const LimbConst *lc;    // [limbs] plain or folded constants (host's choice)
+  const TwM *tw;           // [limbs][2][N]
+  const NttConst *lc;     // [limbs] plain or folded constants (host's choice)
   const MontLimb *mont;   // [limbs]
   uint32_t batch, limbs;
   uint32_t ustart;        // sum of batch x limbs over the earlier jobs of the launch

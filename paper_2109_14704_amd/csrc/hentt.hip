@@ -33,7 +33,9 @@ void release(Storage *s) {
     (void)hipSetDevice(s->device);
     if (s->d_tw) (void)hipFree(s->d_tw);
     if (s->d_lc) (void)hipFree(s->d_lc);
-    if (s->d_lcm) (void)hipFree(s->d_lcm);
+    if (s->d_twm) (void)hipFree(s->d_twm);
+    if (s->d_nc) (void)hipFree(s->d_nc);
+    if (s->d_ncm) (void)hipFree(s->d_ncm);
     if (s->d_mont) (void)hipFree(s->d_mont);
     for (auto &kv : s->rs) (void)hipFree(kv.second);
     for (auto &kv : s->ks) (void)hipFree(kv.second);
@@ -180,6 +182,23 @@ void prof_record(const char *name, int log_n, hipEvent_t a, hipEvent_t b) {
 
 }  // namespace hentt_rt
 
+namespace {
+
+// The transforms' tables from the Shoup pairs: W to (W 2^30 mod q, W 2^62 mod q),
+// split at bit 30.  One lane per entry, a workgroup within one limb (2N >= 128
+// entries per limb).
+__global__ __launch_bounds__(64) void k_tables_m(const Tw *__restrict__ tw, TwM *__restrict__ out,
+                                                 const NttConst *__restrict__ nc, uint32_t log_n) {
+  const uint32_t i = blockIdx.x * 64 + threadIdx.x;
+  const NttConst c = nc[(blockIdx.x * 64) >> (log_n + 1)];
+  const uint64_t w = tw[i].w, lo = (1ull << 30) - 1;
+  const uint64_t a = mulmod(w, (1ull << 30) % c.q, c.q, c.mu, c.k);
+  const uint64_t b = mulmod(w, (1ull << 62) % c.q, c.q, c.mu, c.k);
+  out[i] = TwM{(uint32_t)(a & lo), (uint32_t)(a >> 30), (uint32_t)(b & lo), (uint32_t)(b >> 30)};
+}
+
+}  // namespace
+
 // ------------------------------------------------------------ input check
 namespace {
 
@@ -317,7 +336,7 @@ int plan_queues(hentt_batch_plan *p) {
   // pieces placed largest first on the least-loaded queue; each queue then
   // runs its pieces largest N first.
   auto cost = [&](uint32_t i) { return (double)(1u << p->units[i].logn) * p->units[i].logn; };
-  std::map<const Tw *, std::vector<uint32_t>> by_table;
+  std::map<const TwM *, std::vector<uint32_t>> by_table;
   double total = 0;
   for (uint32_t i = 0; i < p->units.size(); ++i) {
     by_table[p->units[i].tw].push_back(i);
@@ -466,8 +485,8 @@ int plan_build(const hentt_job *jobs, uint32_t njobs, int dir, hentt_batch_plan 
       for (uint32_t l = 0; l < jb.limbs; ++l) {
         BatchUnit u;
         u.data = jb.data + ((uint64_t)b * jb.limbs + l) * N;
-        u.tw = jb.t->s->d_tw + ((size_t)l * 2 + (dir < 0 ? 1 : 0)) * N;
-        u.lc = jb.t->s->d_lc + l;
+        u.tw = jb.t->s->d_twm + ((size_t)l * 2 + (dir < 0 ? 1 : 0)) * N;
+        u.lc = jb.t->s->d_nc + l;
         u.logn = ln;
         u.pass1 = pass1_tiles(ln, dir);
         p->units.push_back(u);
@@ -625,13 +644,17 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
     if (!host::modulus_ok(moduli_host[l], (int)log_n)) return HENTT_EMODULUS;
   const uint32_t N = 1u << log_n;
   std::vector<Tw> tw((size_t)limbs * 2 * N);
-  std::vector<LimbConst> lc(limbs), lcm(limbs);
+  std::vector<LimbConst> lc(limbs);
+  std::vector<NttConst> nc(2 * (size_t)limbs);  // plain, then R-scaled N^-1
   std::vector<MontLimb> mont(limbs);
   std::vector<uint64_t> pw(N), ipw(N);
   for (uint32_t l = 0; l < limbs; ++l) {
     Tw *f = &tw[(size_t)l * 2 * N];
-    if (!host::make_limb(moduli_host[l], (int)log_n, f, f + N, lc[l], lcm[l], mont[l], pw.data(), ipw.data()))
+    LimbConst lcm;
+    if (!host::make_limb(moduli_host[l], (int)log_n, f, f + N, lc[l], lcm, mont[l], pw.data(), ipw.data()))
       return HENTT_EMODULUS;
+    nc[l] = host::ntt_const(lc[l]);
+    nc[limbs + l] = host::ntt_const(lcm);
   }
   Storage *s = new (std::nothrow) Storage();
   if (!s) return HENTT_ENOMEM;
@@ -643,14 +666,22 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   hipError_t e = hipMalloc(&s->d_tw, tw.size() * sizeof(Tw));
   if (e == hipSuccess) e = hipMalloc(&s->d_lc, lc.size() * sizeof(LimbConst));
   if (e == hipSuccess) e = hipMemcpyAsync(s->d_tw, tw.data(), tw.size() * sizeof(Tw), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMalloc(&s->d_lcm, lcm.size() * sizeof(LimbConst));
+  if (e == hipSuccess) e = hipMalloc(&s->d_twm, tw.size() * sizeof(TwM));
+  if (e == hipSuccess) e = hipMalloc(&s->d_nc, limbs * sizeof(NttConst));
+  if (e == hipSuccess) e = hipMalloc(&s->d_ncm, limbs * sizeof(NttConst));
   if (e == hipSuccess) e = hipMalloc(&s->d_mont, mont.size() * sizeof(MontLimb));
   if (e == hipSuccess)
     e = hipMemcpyAsync(s->d_lc, lc.data(), lc.size() * sizeof(LimbConst), hipMemcpyHostToDevice, st);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(s->d_lcm, lcm.data(), lcm.size() * sizeof(LimbConst), hipMemcpyHostToDevice, st);
+    e = hipMemcpyAsync(s->d_nc, nc.data(), limbs * sizeof(NttConst), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(s->d_ncm, nc.data() + limbs, limbs * sizeof(NttConst), hipMemcpyHostToDevice, st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(s->d_mont, mont.data(), mont.size() * sizeof(MontLimb), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_tables_m, dim3(limbs * 2 * N / 64), dim3(64), 0, st, s->d_tw, s->d_twm, s->d_nc, log_n);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     release(s);

@@ -145,5 +145,33 @@ inline bool make_limb(uint64_t q, int log_n, Tw *fwd, Tw *inv, LimbConst &c, Lim
   return true;
 }
 
+// W in the transforms' split Montgomery form (see mul_tw in modarith.hpp).
+inline TwM tw_m(uint64_t w, uint64_t q) {
+  const uint64_t a = mul(w, (1ull << 30) % q, q), b = mul(w, (1ull << 62) % q, q), lo = (1ull << 30) - 1;
+  return TwM{(uint32_t)(a & lo), (uint32_t)(a >> 30), (uint32_t)(b & lo), (uint32_t)(b >> 30)};
+}
+
+// The transforms' constants from a limb record of make_limb (plain, or with
+// R-scaled N^-1 values).
+inline NttConst ntt_const(const LimbConst &c) {
+  const uint64_t q = c.m.q;
+  NttConst n{};
+  n.q = q;
+  n.nq = 0 - q;
+  n.mu = c.mu;
+  n.off = 12 * q;
+  n.qlo = (uint32_t)(q & ((1ull << 30) - 1));
+  n.qhi = (uint32_t)(q >> 30);
+  n.qi = (uint32_t)(0 - inv64(n.qlo));
+  n.k = c.k;
+  n.c64 = c.k >= 34 ? (uint32_t)(((u128)1 << 64) / q) : 0;
+  n.ce = (uint32_t)(((u128)1 << (c.k + 31)) / q);
+  n.s0 = c.k >= 34 ? 32 : c.k > 11 ? c.k - 11 : 0;
+  n.s1 = c.k >= 34 ? c.k - 33 : c.k - 1 - n.s0;
+  n.ninv = tw_m(c.ninv, q);
+  n.ninvw = tw_m(c.ninvw, q);
+  return n;
+}
+
 }  // namespace host
 }  // namespace hentt

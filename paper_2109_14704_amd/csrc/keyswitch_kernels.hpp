@@ -42,40 +42,41 @@ struct KsArgs {
 __device__ __forceinline__ uint64_t ks_lift(uint64_t x, uint64_t mu, uint64_t q) { return x - mulhi64(x, mu) * q; }
 
 // acc0 += v . key0 R^-1, acc1 += v . key1 R^-1 (mod q, accumulators kept
-// in [0, 2q)) for the words of v (lazy forward outputs below 16q, so that
-// v . key < 16 q^2 < q R) held in the (0, E) map of a 2^B block; key0 at k,
+// in [0, 2q)) for the words of v (lazy forward outputs, any 64-bit words: the
+// key is canonical, so v . key < q R) held in the (0, E) map of a 2^B block; key0 at k,
 // key1 one prime-row further (`row` blocks of 2^B words).  The two products
 // run one after the other (scheduling barrier) so that only one key array is
 // live.
 template <int B, int E>
 __device__ __forceinline__ void ks_mac(const uint64_t (&v)[1 << E], const uint64_t *k, uint32_t row, uint32_t lp,
-                                       uint64_t (&acc0)[1 << E], uint64_t (&acc1)[1 << E], const ModQ &m,
+                                       uint64_t (&acc0)[1 << E], uint64_t (&acc1)[1 << E], const NttConst &c,
                                        uint64_t qinv) {
+  const uint64_t nq2 = c.nq + c.nq;
   uint64_t kv[1 << E];
   load_global<B, E, 0, E>(kv, k, lp);
 #pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc0[s] = csubn(acc0[s] + mont_mul(v[s], kv[s], m.q, qinv), m.nq2);
+  for (int s = 0; s < (1 << E); ++s) acc0[s] = csubn(acc0[s] + mont_mul(v[s], kv[s], c.q, qinv), nq2);
   __builtin_amdgcn_sched_barrier(0);
   load_global<B, E, 0, E>(kv, k + ((uint64_t)row << B), lp);
 #pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc1[s] = csubn(acc1[s] + mont_mul(v[s], kv[s], m.q, qinv), m.nq2);
+  for (int s = 0; s < (1 << E); ++s) acc1[s] = csubn(acc1[s] + mont_mul(v[s], kv[s], c.q, qinv), nq2);
 }
 
 // Accumulators (sums of Montgomery products, [0, 2q)) to canonical values:
 // times R mod q by a Shoup product, plus P c_s when cs (c_s's words of the
 // block, in the (0, E) map) is given; each Shoup product lies in [0, 4q).
 template <int B, int E>
-__device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb &kc, const ModQ &m,
+__device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb &kc, const NttConst &c,
                                           const uint64_t *cs, uint32_t lp) {
   if (cs) {
     uint64_t cv[1 << E];
     load_global<B, E, 0, E>(cv, cs, lp);
 #pragma unroll
     for (int s = 0; s < (1 << E); ++s)
-      acc[s] = reduce_8q(shoup(kc.r, kc.rs, acc[s], m.nq) + shoup(kc.pm, kc.pms, cv[s], m.nq), m);
+      acc[s] = reduce_word(shoup(kc.r, kc.rs, acc[s], c.nq) + shoup(kc.pm, kc.pms, cv[s], c.nq), c);
   } else {
 #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_4q(shoup(kc.r, kc.rs, acc[s], m.nq), m);
+    for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(shoup(kc.r, kc.rs, acc[s], c.nq), c);
   }
 }
 
@@ -89,44 +90,47 @@ __device__ __forceinline__ const uint64_t *ks_cs(const KsArgs &a, uint32_t b, ui
 // Whole transforms (N <= 2^12, 256 lanes): one workgroup per (batch entry,
 // target prime), looping over the digits.
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw *__restrict__ tw,
-                                                               const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const TwM *__restrict__ tw,
+                                                               const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<LOGN>::value];
   const uint32_t L1 = a.l + 1;
   const uint32_t t = blockIdx.x / a.batch, b = blockIdx.x % a.batch;
-  const LimbConst c = lc[t];
+  const NttConst c = lc[t];
   const KsLimb kc = a.kc[t];
-  const Tw *tt = tw + (size_t)t * 2 * (1u << LOGN);
+  const TwM *tt = tw + (size_t)t * 2 * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<LOGN, E>;
   using M0 = RoundMap<LOGN, E, 0, E>;
-  uint64_t acc0[1 << E], acc1[1 << E];
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc0[s] = acc1[s] = 0;
-#pragma unroll 1
-  for (uint32_t j = 0; j < a.l; ++j) {
-    if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
-    uint64_t v[1 << E];
-    load_global<LOGN, E, F::LO, F::R>(v, a.d + (((uint64_t)b * a.l + j) << LOGN),
-                                       RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
-#pragma unroll
-    for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c.m.q);
-    // an opaque copy of the table pointer per digit: the twiddles (the same
-    // for every digit) are re-read from cache instead of held in VGPRs
-    fwd_block_rounds<LOGN, E, F::LO, F::R>(v, LOGN, lds, tid, 0, opaque(tt), c.m);
-    ks_mac<LOGN, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN), L1, M0::lane_part(tid), acc0, acc1, c.m,
-                    kc.qinv);
-  }
-  ks_finish<LOGN, E>(acc0, kc, c.m, ks_cs(a, b, 0, t, LOGN, 0), M0::lane_part(tid));
-  store_global_m0<LOGN, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN), lds, tid);
-  ks_finish<LOGN, E>(acc1, kc, c.m, ks_cs(a, b, 1, t, LOGN, 0), M0::lane_part(tid));
-  store_global_m0<LOGN, E>(acc1, a.acc + (((uint64_t)(b * 2 + 1) * L1 + t) << LOGN), lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t acc0[1 << E], acc1[1 << E];
+  #pragma unroll
+    for (int s = 0; s < (1 << E); ++s) acc0[s] = acc1[s] = 0;
+  #pragma unroll 1
+    for (uint32_t j = 0; j < a.l; ++j) {
+      if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
+      uint64_t v[1 << E];
+      load_global<LOGN, E, F::LO, F::R>(v, a.d + (((uint64_t)b * a.l + j) << LOGN),
+                                         RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
+  #pragma unroll
+      for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c.q);
+      // an opaque copy of the table pointer per digit: the twiddles (the same
+      // for every digit) are re-read from cache instead of held in VGPRs
+      fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, opaque(tt), c);
+      ks_mac<LOGN, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN), L1, M0::lane_part(tid), acc0, acc1, c,
+                      kc.qinv);
+    }
+    ks_finish<LOGN, E>(acc0, kc, c, ks_cs(a, b, 0, t, LOGN, 0), M0::lane_part(tid));
+    store_global_m0<LOGN, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN), lds, tid);
+    ks_finish<LOGN, E>(acc1, kc, c, ks_cs(a, b, 1, t, LOGN, 0), M0::lane_part(tid));
+    store_global_m0<LOGN, E>(acc1, a.acc + (((uint64_t)(b * 2 + 1) * L1 + t) << LOGN), lds, tid);
+  });
 }
 
 // Two-pass sizes, pass 1: column pass of digit j modulo q_t into e.
 template <int LOGN, int EC>
-__global__ __launch_bounds__(256) void k_ks_cols(KsArgs a, const Tw *__restrict__ tw,
-                                                 const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(256) void k_ks_cols(KsArgs a, const TwM *__restrict__ tw,
+                                                 const NttConst *__restrict__ lc) {
   constexpr uint32_t tiles = (1u << (LOGN - EC)) / 256;
   constexpr int LO = LOGN - EC;
   const uint32_t L1 = a.l + 1;
@@ -135,50 +139,56 @@ __global__ __launch_bounds__(256) void k_ks_cols(KsArgs a, const Tw *__restrict_
   const uint32_t t = r % L1;
   r /= L1;
   const uint32_t j = r % a.l, b = r / a.l;
-  const ModQ m = lc[t].m;
+  const NttConst c = lc[t];
   const uint64_t mu = a.kc[t].mu;
-  uint64_t v[1 << EC];
-  load_global<LOGN, EC, LO, EC, true>(v, a.d + (((uint64_t)b * a.l + j) << LOGN), col);
-#pragma unroll
-  for (int s = 0; s < (1 << EC); ++s) v[s] = ks_lift(v[s], mu, m.q);
-  fwd_round<LOGN, EC, LO, EC, 0>(v, LOGN, 0, col, tw + (size_t)t * 2 * (1u << LOGN), m);
-  store_global<LOGN, EC, LO, EC, true>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN), col);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << EC];
+    load_global<LOGN, EC, LO, EC, true>(v, a.d + (((uint64_t)b * a.l + j) << LOGN), col);
+  #pragma unroll
+    for (int s = 0; s < (1 << EC); ++s) v[s] = ks_lift(v[s], mu, c.q);
+    fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, tw + (size_t)t * 2 * (1u << LOGN), c);
+    store_global<LOGN, EC, LO, EC, true>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN), col);
+  });
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
 // rounds of every digit, accumulated with the key in registers.
 template <int LOGN, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const Tw *__restrict__ tw,
-                                                             const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM *__restrict__ tw,
+                                                             const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
   const uint32_t L1 = a.l + 1;
   const uint32_t blockStart = (blockIdx.x % tiles) << B;
   const uint32_t r = blockIdx.x / tiles;
   const uint32_t t = r / a.batch, b = r % a.batch;
-  const LimbConst c = lc[t];
+  const NttConst c = lc[t];
   const KsLimb kc = a.kc[t];
-  const Tw *tt = tw + (size_t)t * 2 * (1u << LOGN);
+  const TwM *tt = tw + (size_t)t * 2 * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<B, E>;
   using M0 = RoundMap<B, E, 0, E>;
-  uint64_t acc0[1 << E], acc1[1 << E];
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc0[s] = acc1[s] = 0;
-#pragma unroll 1
-  for (uint32_t j = 0; j < a.l; ++j) {
-    if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
-    uint64_t v[1 << E];
-    load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
-                                   RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-    fwd_block_rounds<B, E, F::LO, F::R>(v, LOGN, lds, tid, blockStart, opaque(tt), c.m);
-    ks_mac<B, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B),
-                 M0::lane_part(tid), acc0, acc1, c.m, kc.qinv);
-  }
-  ks_finish<B, E>(acc0, kc, c.m, ks_cs(a, b, 0, t, LOGN, blockStart), M0::lane_part(tid));
-  store_global_m0<B, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN) + blockStart, lds, tid);
-  ks_finish<B, E>(acc1, kc, c.m, ks_cs(a, b, 1, t, LOGN, blockStart), M0::lane_part(tid));
-  store_global_m0<B, E>(acc1, a.acc + (((uint64_t)(b * 2 + 1) * L1 + t) << LOGN) + blockStart, lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t acc0[1 << E], acc1[1 << E];
+  #pragma unroll
+    for (int s = 0; s < (1 << E); ++s) acc0[s] = acc1[s] = 0;
+  #pragma unroll 1
+    for (uint32_t j = 0; j < a.l; ++j) {
+      if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
+      uint64_t v[1 << E];
+      load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
+                                     RoundMap<B, E, F::LO, F::R>::lane_part(tid));
+      fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, opaque(tt), c);
+      ks_mac<B, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B),
+                   M0::lane_part(tid), acc0, acc1, c, kc.qinv);
+    }
+    ks_finish<B, E>(acc0, kc, c, ks_cs(a, b, 0, t, LOGN, blockStart), M0::lane_part(tid));
+    store_global_m0<B, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN) + blockStart, lds, tid);
+    ks_finish<B, E>(acc1, kc, c, ks_cs(a, b, 1, t, LOGN, blockStart), M0::lane_part(tid));
+    store_global_m0<B, E>(acc1, a.acc + (((uint64_t)(b * 2 + 1) * L1 + t) << LOGN) + blockStart, lds, tid);
+  });
 }
 
 }  // namespace hentt

@@ -3,9 +3,8 @@
 //
 // Data: x[poly][N] uint64, poly = batch * limbs + limb (limb fastest among
 // polynomials, coefficient fastest overall).  Twiddles per limb: forward table
-// psi^brv(k) and inverse table psi^-brv(k), k < N, each stored as (W, W')
-// 16-byte pairs with W' = floor(W 2^64 / q) (the root powers and root power
-// quotients of Algorithm 1).
+// psi^brv(k) and inverse table psi^-brv(k), k < N, each a 16-byte TwM word
+// (modarith.hpp).
 //
 // A transform is a sequence of "rounds".  A round applies R consecutive
 // butterfly stages to groups of 2^R elements held in one lane's registers;
@@ -56,98 +55,170 @@ struct RoundMap {
 // Twiddle tables are never written while a kernel runs, so they are read
 // through the constant address space: a wave-uniform index becomes a scalar
 // load even when the table pointer was itself read from memory.
-__device__ __forceinline__ Tw ld_tw(const Tw* t, uint32_t i) {
+__device__ __forceinline__ TwM ld_tw(const TwM* t, uint32_t i) {
   const __attribute__((address_space(4))) uint64_t* p = (const __attribute__((address_space(4))) uint64_t*)(t + i);
-  return Tw{p[0], p[1]};
+  const uint64_t a = p[0], b = p[1];
+  return TwM{lo32(a), hi32(a), lo32(b), hi32(b)};
+}
+
+// Returns p unchanged but hides that from the optimiser (adds an opaque,
+// wave-uniform zero), so loads through it are not merged with earlier ones.
+template <typename T> __device__ __forceinline__ const T *opaque(const T *p) {
+  uint32_t z = 0;
+  asm volatile("" : "+s"(z));
+  return p + z;
 }
 
 // Limb constants through the constant address space as well: with a
 // wave-uniform pointer (also one read from memory) they become scalar loads
 // into SGPRs instead of 24 VGPRs of per-lane copies.
-__device__ __forceinline__ LimbConst ld_lc(const LimbConst *p) {
+__device__ __forceinline__ NttConst ld_nc(const NttConst *p) {
   const __attribute__((address_space(4))) uint64_t *w = (const __attribute__((address_space(4))) uint64_t *)p;
-  LimbConst c;
-  c.m = ModQ{w[0], w[1], w[2], w[3], w[4], w[5]};
-  c.ninv = w[6];
-  c.ninv_s = w[7];
-  c.ninvw = w[8];
-  c.ninvw_s = w[9];
-  c.mu = w[10];
-  c.k = (uint32_t)w[11];
-  c.pad = 0;
+  NttConst c;
+  c.q = w[0];
+  c.nq = w[1];
+  c.mu = w[2];
+  c.off = w[3];
+  c.qlo = lo32(w[4]);
+  c.qhi = hi32(w[4]);
+  c.qi = lo32(w[5]);
+  c.k = hi32(w[5]);
+  c.c64 = lo32(w[6]);
+  c.ce = hi32(w[6]);
+  c.s0 = lo32(w[7]);
+  c.s1 = hi32(w[7]);
+  c.ninv = TwM{lo32(w[8]), hi32(w[8]), lo32(w[9]), hi32(w[9])};
+  c.ninvw = TwM{lo32(w[10]), hi32(w[10]), lo32(w[11]), hi32(w[11])};
   return c;
+}
+
+// Compile-time loop: f(std::integral_constant<int, I>) for I in [I0, I1), so
+// that array indices stay constants (no stack arrays) even for loop bodies too
+// large for the unroller.
+template <int I0, int I1, typename F> __device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (I0 < I1) {
+    f(std::integral_constant<int, I0>{});
+    static_for<I0 + 1, I1>(f);
+  }
+}
+
+// Moduli of 34 to 55 bits run without corrections inside the rounds; the
+// others (FIX) take theirs unconditionally.  A kernel holds both forms of its
+// body and branches once, on its workgroup's limb.  Tests at every stage
+// instead cut the body into blocks that the scheduler could not overlap and
+// roughly doubled its registers (k_cols of five stages 260 VGPRs against 103);
+// the markers keep the compiler from merging the two forms' heads and tails,
+// which did the same.
+template <typename F> __device__ __forceinline__ void by_class(const NttConst &c, F &&f) {
+  if (c.k - 34u <= 21u) {
+    asm volatile("; class 0");
+    f(std::false_type{});
+    asm volatile("; end 0");
+  } else {
+    asm volatile("; class 1");
+    f(std::true_type{});
+    asm volatile("; end 1");
+  }
 }
 
 // ---------------------------------------------------------------- rounds --
 // Forward stages with global index s = LOGN - LO - R + u, u < R.  Stage s
 // pairs j with j + N/2^(s+1) and uses psi_rev[2^s + (j >> (LOGN - s))].
-// P0 >= 0: the library's butterfly (ct_bfly16, values below 16q), P0 being
-// the parity of the round's first stage within its pass (a stage corrects X
-// when its index within the pass is even).  P0 < 0: the classic butterfly
-// (every stage corrects, values below 8q), for the reference designs.
-template <int B, int E, int LO, int R, int P0 = -1>
+// Moduli of up to 56 bits need no corrections: a transform adds at most 12q
+// per stage to inputs of a few q.  Larger ones (FIX) enter with any 64-bit
+// words and bring X below 3q before every stage (3 + 12 < 16).
+template <int B, int E, int LO, int R, bool FIX>
 __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
-                                          uint32_t lanePart, const Tw* __restrict__ tw, const ModQ &m) {
+                                          uint32_t lanePart, const TwM* __restrict__ tw, const NttConst &c) {
   using M = RoundMap<B, E, LO, R>;
+  const uint32_t four = opaque4();
+  static_for<0, R>([&](auto U) __attribute__((always_inline)) {
+    constexpr int u = decltype(U)::value, h = 1 << (R - 1 - u);
+    if constexpr (FIX) {
 #pragma unroll
-  for (int g = 0; g < (1 << (E - R)); ++g) {
-    const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
+      for (int i = 0; i < (1 << E); ++i)
+        if (!(i & h)) x[i] = est3(x[i], c);
+    }
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
+    for (int g = 0; g < (1 << (E - R)); ++g) {
+      const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
       // stage s = logn - LO - R + u: 2^s = 2^(logn - B) * 2^(B - LO - R + u)
       const uint32_t base = ((1u << (logn - B)) << (B - LO - R + u)) + (J0 >> (LO + R - u));
-      const int h = 1 << (R - 1 - u);
 #pragma unroll
       for (int k = 0; k < (1 << R); ++k) {
         if (k & h) continue;
-        const Tw w = ld_tw(tw, base + (k >> (R - u)));
-        if constexpr (P0 < 0) ct_bfly(x[(g << R) + k], x[(g << R) + k + h], w.w, w.ws, m);
-        else if (((P0 + u) & 1) == 0) ct_bfly16<true>(x[(g << R) + k], x[(g << R) + k + h], w.w, w.ws, m);
-        else ct_bfly16<false>(x[(g << R) + k], x[(g << R) + k + h], w.w, w.ws, m);
+        ct_bfly_m(x[(g << R) + k], x[(g << R) + k + h], ld_tw(tw, base + (k >> (R - u))), c, four);
       }
     }
-  }
+  });
 }
-
 // Inverse stages v = LO + u.  Stage v pairs j with j + 2^v and uses
 // psi_rev^-1[N/2^(v+1) + (j >> (v+1))].  The last stage (v = LOGN-1) also
 // multiplies both outputs by N^-1.
-template <int B, int E, int LO, int R>
+//
+// X' = X + Y doubles the bound of the words that stay on the X side, while
+// every product is below 12q.  Corrections (est3, to below 3q) by modulus
+// size, k uniform per workgroup:
+//   34..55 bits  (not FIX) none inside a round of up to five stages: words enter below
+//                2^LBIN q (16q, or 32q for rounds of at most four stages) and
+//                stay below 512q; at its end the words that could exceed
+//                2^LBOUT q are corrected (the few with a long run of X sides
+//                behind them);
+//   56..60 bits  words below 8q on entry: the product corrected after every
+//                stage, X' after every second one and after the round's last
+//                (3 + 3 < 8, 6 + 6 < 16);
+//   33 or fewer  none in the whole transform: at stage v words are below
+//                16q 2^v < 2^54 (est3 leaves them as they are).
+// `off`, the multiple of q that keeps X - Y positive, follows the same bounds.
+template <int R, int LBIN, int LBOUT> constexpr bool inv_over(int k) {
+  int h = -1;
+  for (int b = 0; b < R; ++b)
+    if ((k >> b) & 1) h = b;
+  const int bound = h < 0 ? 1 << (LBIN + R) : 12 << (R - 1 - h);
+  return bound > (1 << LBOUT);
+}
+template <int B, int E, int LO, int R, int LBIN, int LBOUT, bool FIX>
 __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
-                                          uint32_t lanePart, const Tw* __restrict__ itw, const LimbConst& c) {
+                                           uint32_t lanePart, const TwM* __restrict__ itw, const NttConst& c) {
   using M = RoundMap<B, E, LO, R>;
+  static_assert(LBIN + R <= 9, "words stay below 512q inside a round");
+  const uint32_t four = opaque4();
+  static_for<0, R>([&](auto U) __attribute__((always_inline)) {
+    constexpr int u = decltype(U)::value, v = LO + u, d = 1 << u;
+    const uint64_t off = c.q << (!FIX ? (uint32_t)(LBIN + u) : c.k < 34 ? 4u + v : 3u);
+    // only the block's top stage can be the transform's last one
+    if (LO + u == B - 1 && (uint32_t)v == logn - 1) {
+      // last stage: one group, twiddle psi^-brv(1) folded with N^-1
 #pragma unroll
-  for (int g = 0; g < (1 << (E - R)); ++g) {
-    const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
+      for (int i = 0; i < (1 << E); ++i) {
+        if (i & d) continue;
+        const uint64_t s = x[i] + x[i + d], df = (x[i] + off) - x[i + d];
+        x[i] = mul_tw(c.ninv, s, c, four);
+        x[i + d] = mul_tw(c.ninvw, df, c, four);
+      }
+    } else {
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const int v = LO + u;
-      const int d = 1 << u;
-      // only the block's top stage can be the transform's last one
-      if (LO + u == B - 1 && (uint32_t)v == logn - 1) {
-        // last stage: one group, twiddle psi^-brv(1) folded with N^-1
-#pragma unroll
-        for (int k = 0; k < (1 << R); ++k) {
-          if (k & d) continue;
-          uint64_t& X = x[(g << R) + k];
-          uint64_t& Y = x[(g << R) + k + d];
-          const uint64_t s = X + Y, df = (X + c.m.q4) - Y;
-          X = shoup(c.ninv, c.ninv_s, s, c.m.nq);
-          Y = shoup(c.ninvw, c.ninvw_s, df, c.m.nq);
-        }
-      } else {
+      for (int g = 0; g < (1 << (E - R)); ++g) {
+        const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
         const uint32_t base = ((1u << logn) >> (v + 1)) + (J0 >> (v + 1));
 #pragma unroll
         for (int k = 0; k < (1 << R); ++k) {
           if (k & d) continue;
-          const Tw w = ld_tw(itw, base + (k >> (u + 1)));
-          gs_bfly(x[(g << R) + k], x[(g << R) + k + d], w.w, w.ws, c.m);
+          gs_bfly_m(x[(g << R) + k], x[(g << R) + k + d], ld_tw(itw, base + (k >> (u + 1))), off, c, four);
         }
       }
+      if constexpr (FIX) {
+#pragma unroll
+        for (int i = 0; i < (1 << E); ++i)
+          if ((i & d) || (u & 1) || u == R - 1) x[i] = est3(x[i], c);
+      } else if (u == R - 1) {
+#pragma unroll
+        for (int i = 0; i < (1 << E); ++i)
+          if (inv_over<R, LBIN, LBOUT>(i & ((1 << R) - 1))) x[i] = est3(x[i], c);
+      }
     }
-  }
+  });
 }
-
 // ------------------------------------------------------------ data moves --
 // Polynomial words are addressed as a base pointer plus a 32-bit byte offset
 // (every index below lies inside one polynomial or block, < 2^17 words), in
@@ -285,39 +356,26 @@ __device__ __forceinline__ void load_global_m0_fresh(uint64_t (&x)[1 << E], cons
   }
 }
 
-// Canonical reductions of forward outputs ([0, 16q)) and inverse outputs
-// ([0, 4q)).  Forward: moduli above 2^33 (bit length k >= 34; mu is the
-// limb's Barrett constant) take the quotient estimate and one conditional
-// subtraction, smaller ones the chain of four conditional subtractions (k
-// is uniform per workgroup, so the branch is a scalar one).
-template <int E>
-__device__ __forceinline__ void reduce_fwd(uint64_t (&x)[1 << E], const ModQ &m, uint64_t mu, uint32_t k) {
-  if (k >= 34) {
-    const uint32_t c = est_c(mu, k), sh = k - 33;
+// Canonical reduction of a transform's outputs.
+template <int E, bool FIX> __device__ __forceinline__ void reduce_out(uint64_t (&x)[1 << E], const NttConst &c) {
 #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) x[s] = csubn(reduce_est(x[s], m.nq, c, sh), m.nq);
-  } else {
-#pragma unroll
-    for (int s = 0; s < (1 << E); ++s) x[s] = reduce_16q(x[s], m);
+  for (int s = 0; s < (1 << E); ++s) {
+    if constexpr (FIX) x[s] = reduce_word(x[s], c);
+    else x[s] = csubn(reduce_est(x[s], c.nq, c.ce, c.k - 33), c.nq);
   }
-}
-template <int E> __device__ __forceinline__ void reduce_inv(uint64_t (&x)[1 << E], const ModQ &m) {
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) x[s] = reduce_4q(x[s], m);
 }
 
 // --------------------------------------------------- block transforms ----
 // Forward rounds over the block bits [0, LO+R) (the first round covers
 // [LO, LO+R)), starting from registers already loaded with the first round's
 // map.  Ends with the lane holding the last round (LO = 0) map in registers,
-// i.e. 2^E consecutive elements, values in [0, 16q).  P: parity of the
-// round's first stage within the block pass.
-template <int B, int E, int LO, int R, int P = 0>
+// i.e. 2^E consecutive elements, lazy values (see fwd_round).
+template <int B, int E, int LO, int R, bool FIX>
 __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
-                                                 uint32_t blockStart, const Tw* __restrict__ tw, const ModQ &m) {
+                                                 uint32_t blockStart, const TwM* __restrict__ tw, const NttConst &c) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  fwd_round<B, E, LO, R, P>(x, logn, blockStart, lp, tw, m);
+  fwd_round<B, E, LO, R, FIX>(x, logn, blockStart, lp, tw, c);
   if constexpr (LO > 0) {
     constexpr int R2 = E;
     constexpr int LO2 = LO - R2;
@@ -326,20 +384,21 @@ __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t
     __syncthreads();
     using M2 = RoundMap<B, E, LO2, R2>;
     load_lds<B, E, LO2, R2>(x, lds, M2::lane_part(tid));
-    fwd_block_rounds<B, E, LO2, R2, (P + R) & 1>(x, logn, lds, tid, blockStart, tw, m);
+    fwd_block_rounds<B, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, tw, c);
   }
 }
 
 // Inverse rounds over block bits [LO, B), starting from registers loaded with
 // the (LO, R) map.  Ends with the lane holding the last round's map
-// (covering [B - Rlast, B)); values in [0, 2q).
-template <int B, int E, int LO, int R>
+// (covering [B - Rlast, B)); words enter below 16q and leave below 16q, or
+// are the transform's lazy outputs.
+template <int B, int E, int LO, int R, bool FIX>
 __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
-                                                 uint32_t blockStart, const Tw* __restrict__ itw,
-                                                 const LimbConst& c) {
+                                                 uint32_t blockStart, const TwM* __restrict__ itw,
+                                                 const NttConst& c) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  inv_round<B, E, LO, R>(x, logn, blockStart, lp, itw, c);
+  inv_round<B, E, LO, R, 5, (LO + R < B ? 5 : 4), FIX>(x, logn, blockStart, lp, itw, c);
   if constexpr (LO + R < B) {
     constexpr int LO2 = LO + R;
     constexpr int R2 = (B - LO2) < E ? (B - LO2) : E;
@@ -347,7 +406,7 @@ __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t
     __syncthreads();
     using M2 = RoundMap<B, E, LO2, R2>;
     load_lds<B, E, LO2, R2>(x, lds, M2::lane_part(tid));
-    inv_block_rounds<B, E, LO2, R2>(x, logn, lds, tid, blockStart, itw, c);
+    inv_block_rounds<B, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, itw, c);
   }
 }
 
@@ -379,39 +438,45 @@ __device__ __forceinline__ Unit unit_of(uint32_t bid, uint32_t tiles, uint32_t b
 // ------------------------------------------------------------- kernels ----
 // Whole transform of one polynomial per workgroup (N = 2^LOGN fits in LDS).
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_fwd_whole(uint64_t* __restrict__ x, const Tw* __restrict__ tw,
-                                                                const LimbConst* __restrict__ lc, uint32_t batch,
+__global__ __launch_bounds__(1 << (LOGN - E)) void k_fwd_whole(uint64_t* __restrict__ x, const TwM* __restrict__ tw,
+                                                                const NttConst* __restrict__ lc, uint32_t batch,
                                                                 uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<LOGN>::value];
   const Unit un = unit_of(blockIdx.x, 1, batch, limbs);
-  const ModQ m = lc[un.limb].m;
-  const Tw* t = tw + (size_t)un.limb * 2 * (1u << LOGN);
+  const NttConst c = lc[un.limb];
+  const TwM* t = tw + (size_t)un.limb * 2 * (1u << LOGN);
   uint64_t* p = x + (size_t)un.poly * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<LOGN, E>;
-  uint64_t v[1 << E];
-  load_global<LOGN, E, F::LO, F::R>(v, p, RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
-  fwd_block_rounds<LOGN, E, F::LO, F::R>(v, LOGN, lds, tid, 0, t, m);
-  reduce_fwd<E>(v, m, lc[un.limb].mu, lc[un.limb].k);
-  store_global_m0<LOGN, E>(v, p, lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global<LOGN, E, F::LO, F::R>(v, p, RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
+    fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, t, c);
+    reduce_out<E, FIX>(v, c);
+    store_global_m0<LOGN, E>(v, p, lds, tid);
+  });
 }
 
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_inv_whole(uint64_t* __restrict__ x, const Tw* __restrict__ tw,
-                                                                const LimbConst* __restrict__ lc, uint32_t batch,
+__global__ __launch_bounds__(1 << (LOGN - E)) void k_inv_whole(uint64_t* __restrict__ x, const TwM* __restrict__ tw,
+                                                                const NttConst* __restrict__ lc, uint32_t batch,
                                                                 uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<LOGN>::value];
   const Unit un = unit_of(blockIdx.x, 1, batch, limbs);
-  const LimbConst c = lc[un.limb];
-  const Tw* it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
+  const NttConst c = lc[un.limb];
+  const TwM* it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
   uint64_t* p = x + (size_t)un.poly * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using L = InvLast<LOGN, E>;
-  uint64_t v[1 << E];
-  load_global_m0_fresh<LOGN, E>(v, p, lds, tid);
-  inv_block_rounds<LOGN, E, 0, (LOGN < E ? LOGN : E)>(v, LOGN, lds, tid, 0, it, c);
-  reduce_inv<E>(v, c.m);
-  store_global<LOGN, E, L::LO, L::R>(v, p, RoundMap<LOGN, E, L::LO, L::R>::lane_part(tid));
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global_m0_fresh<LOGN, E>(v, p, lds, tid);
+    inv_block_rounds<LOGN, E, 0, (LOGN < E ? LOGN : E), FIX>(v, LOGN, lds, tid, 0, it, c);
+    reduce_out<E, FIX>(v, c);
+    store_global<LOGN, E, L::LO, L::R>(v, p, RoundMap<LOGN, E, L::LO, L::R>::lane_part(tid));
+  });
 }
 
 // Column pass: the first E forward stages (or the last E inverse stages) on
@@ -428,17 +493,17 @@ struct ColArgs {
 // One column of the column pass: 2^E elements at stride N / 2^E starting at
 // word `col`, read from src and written to dst (equal for in place).  `t` is
 // the limb's forward table, or its inverse table when INV.
-template <int LOGN, int E, bool INV>
-__device__ __forceinline__ void col_pass(const uint64_t *src, uint64_t *dst, uint32_t col, const Tw *t,
-                                         const LimbConst &c) {
+template <int LOGN, int E, bool INV, bool FIX>
+__device__ __forceinline__ void col_pass(const uint64_t *src, uint64_t *dst, uint32_t col, const TwM *t,
+                                         const NttConst &c) {
   constexpr int LO = LOGN - E;
   uint64_t v[1 << E];
   load_global<LOGN, E, LO, E, true>(v, src, col);
   if constexpr (!INV) {
-    fwd_round<LOGN, E, LO, E, 0>(v, LOGN, 0, col, t, c.m);
+    fwd_round<LOGN, E, LO, E, FIX>(v, LOGN, 0, col, t, c);
   } else {
-    inv_round<LOGN, E, LO, E>(v, LOGN, 0, col, t, c);
-    reduce_inv<E>(v, c.m);
+    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v, LOGN, 0, col, t, c);
+    reduce_out<E, FIX>(v, c);
   }
   store_global<LOGN, E, LO, E, true>(v, dst, col);
 }
@@ -449,9 +514,9 @@ __device__ __forceinline__ void col_pass(const uint64_t *src, uint64_t *dst, uin
 // transforms 12% faster, of the 2^15 and 2^16 products 6-10% slower).
 template <int E> struct ColCpl { static constexpr int value = E <= 4 ? 2 : 1; };
 // Two neighbouring columns per lane: 16-byte accesses.
-template <int LOGN, int E, bool INV>
-__device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, uint32_t col, const Tw *t,
-                                          const LimbConst &c) {
+template <int LOGN, int E, bool INV, bool FIX>
+__device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, uint32_t col, const TwM *t,
+                                          const NttConst &c) {
   constexpr int LO = LOGN - E;
   uint64_t v0[1 << E], v1[1 << E];
 #pragma unroll
@@ -462,13 +527,13 @@ __device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, ui
     v1[s] = w.y;
   }
   if constexpr (!INV) {
-    fwd_round<LOGN, E, LO, E, 0>(v0, LOGN, 0, col, t, c.m);
-    fwd_round<LOGN, E, LO, E, 0>(v1, LOGN, 0, col, t, c.m);
+    fwd_round<LOGN, E, LO, E, FIX>(v0, LOGN, 0, col, t, c);
+    fwd_round<LOGN, E, LO, E, FIX>(v1, LOGN, 0, col, t, c);
   } else {
-    inv_round<LOGN, E, LO, E>(v0, LOGN, 0, col, t, c);
-    inv_round<LOGN, E, LO, E>(v1, LOGN, 0, col, t, c);
-    reduce_inv<E>(v0, c.m);
-    reduce_inv<E>(v1, c.m);
+    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v0, LOGN, 0, col, t, c);
+    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v1, LOGN, 0, col, t, c);
+    reduce_out<E, FIX>(v0, c);
+    reduce_out<E, FIX>(v1, c);
   }
 #pragma unroll
   for (int s = 0; s < (1 << E); ++s) {
@@ -483,8 +548,8 @@ __device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, ui
 // Workgroup `blk` of a column pass over batch x limbs units of every
 // component of `a` (the body of k_cols and of its grouped form).
 template <int LOGN, int E, bool INV>
-__device__ __forceinline__ void cols_block(const ColArgs &a, const Tw *__restrict__ tw,
-                                           const LimbConst *__restrict__ lc, uint32_t batch, uint32_t limbs,
+__device__ __forceinline__ void cols_block(const ColArgs &a, const TwM *__restrict__ tw,
+                                           const NttConst *__restrict__ lc, uint32_t batch, uint32_t limbs,
                                            uint32_t blk) {
   constexpr uint32_t CPL = ColCpl<E>::value;
   constexpr uint32_t tiles = (1u << (LOGN - E)) / (256 * CPL);
@@ -493,13 +558,16 @@ __device__ __forceinline__ void cols_block(const ColArgs &a, const Tw *__restric
   const uint32_t r = blk / tiles;
   const uint32_t comp = r / units, u = r % units;
   const uint32_t limb = u / batch, b = u % batch;
-  const LimbConst c = lc[limb];
+  const NttConst c = lc[limb];
   const uint64_t off = (uint64_t)limb << LOGN;
   const uint64_t *src = a.src[comp] + (uint64_t)b * a.src_sb + off;
   uint64_t *dst = a.dst[comp] + (uint64_t)b * a.dst_sb + off;
-  const Tw *t = tw + ((size_t)limb * 2 + (INV ? 1 : 0)) * (1u << LOGN);
-  if constexpr (CPL == 2) col_pass2<LOGN, E, INV>(src, dst, tile * 512 + 2 * threadIdx.x, t, c);
-  else col_pass<LOGN, E, INV>(src, dst, tile * 256 + threadIdx.x, t, c);
+  const TwM *t = tw + ((size_t)limb * 2 + (INV ? 1 : 0)) * (1u << LOGN);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    if constexpr (CPL == 2) col_pass2<LOGN, E, INV, FIX>(src, dst, tile * 512 + 2 * threadIdx.x, t, c);
+    else col_pass<LOGN, E, INV, FIX>(src, dst, tile * 256 + threadIdx.x, t, c);
+  });
 }
 
 // Workgroups per component of a column pass over `units` (batch x limbs) units.
@@ -508,7 +576,7 @@ template <int LOGN, int E> constexpr uint32_t cols_blocks_per_unit() {
 }
 
 template <int LOGN, int E, bool INV>
-__global__ __launch_bounds__(256) void k_cols(ColArgs a, const Tw *__restrict__ tw, const LimbConst *__restrict__ lc,
+__global__ __launch_bounds__(256) void k_cols(ColArgs a, const TwM *__restrict__ tw, const NttConst *__restrict__ lc,
                                               uint32_t batch, uint32_t limbs) {
   cols_block<LOGN, E, INV>(a, tw, lc, batch, limbs, blockIdx.x);
 }
@@ -516,64 +584,52 @@ __global__ __launch_bounds__(256) void k_cols(ColArgs a, const Tw *__restrict__ 
 // Block pass of the forward transform: stages LOGN-B .. LOGN-1 on contiguous
 // blocks of 2^B elements; canonical output.
 template <int LOGN, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restrict__ x, const Tw *__restrict__ tw,
-                                                              const LimbConst *__restrict__ lc, uint32_t batch,
+__global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restrict__ x, const TwM *__restrict__ tw,
+                                                              const NttConst *__restrict__ lc, uint32_t batch,
                                                               uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
   const Unit un = unit_of(blockIdx.x, tiles, batch, limbs);
-  const ModQ m = lc[un.limb].m;
-  const Tw *t = tw + (size_t)un.limb * 2 * (1u << LOGN);
+  const NttConst c = lc[un.limb];
+  const TwM *t = tw + (size_t)un.limb * 2 * (1u << LOGN);
   const uint32_t blockStart = un.tile << B;
   uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<B, E>;
-  uint64_t v[1 << E];
-  load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-  fwd_block_rounds<B, E, F::LO, F::R>(v, LOGN, lds, tid, blockStart, t, m);
-  reduce_fwd<E>(v, m, lc[un.limb].mu, lc[un.limb].k);
-  store_global_m0<B, E>(v, p, lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
+    fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, t, c);
+    reduce_out<E, FIX>(v, c);
+    store_global_m0<B, E>(v, p, lds, tid);
+  });
 }
 
 // Block pass of the inverse transform: stages 0 .. B-1; lazy [0, 2q) output.
 template <int LOGN, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restrict__ x, const Tw *__restrict__ tw,
-                                                              const LimbConst *__restrict__ lc, uint32_t batch,
+__global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restrict__ x, const TwM *__restrict__ tw,
+                                                              const NttConst *__restrict__ lc, uint32_t batch,
                                                               uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
   const Unit un = unit_of(blockIdx.x, tiles, batch, limbs);
-  const LimbConst c = lc[un.limb];
-  const Tw *it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
+  const NttConst c = lc[un.limb];
+  const TwM *it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
   const uint32_t blockStart = un.tile << B;
   uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
   using L = InvLast<B, E>;
-  uint64_t v[1 << E];
-  load_global_m0_fresh<B, E>(v, p, lds, tid);
-  inv_block_rounds<B, E, 0, E>(v, LOGN, lds, tid, blockStart, it, c);
-  store_global<B, E, L::LO, L::R>(v, p, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global_m0_fresh<B, E>(v, p, lds, tid);
+    inv_block_rounds<B, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, it, c);
+    store_global<B, E, L::LO, L::R>(v, p, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
+  });
 }
 
 // ------------------------------------------------------ fused products ----
-// Compile-time loop: f(std::integral_constant<int, I>) for I in [I0, I1), so
-// that array indices stay constants (no stack arrays) even for loop bodies too
-// large for the unroller.
-template <int I0, int I1, typename F> __device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (I0 < I1) {
-    f(std::integral_constant<int, I0>{});
-    static_for<I0 + 1, I1>(f);
-  }
-}
-
-// Returns p unchanged but hides that from the optimiser (adds an opaque,
-// wave-uniform zero), so loads through it are not merged with earlier ones.
-template <typename T> __device__ __forceinline__ const T *opaque(const T *p) {
-  uint32_t z = 0;
-  asm volatile("" : "+s"(z));
-  return p + z;
-}
-
 // Products of section II: PROD_MUL is the dyadic product of two polynomials
 // (a (.) b); PROD_TENSOR the ciphertext Mul tensor (c0 d0, c0 d1 + c1 d0,
 // c1 d1) with the middle term reduced once (mad_mod, section III-A-1).
@@ -607,15 +663,15 @@ template <typename T, int N> __device__ __forceinline__ T pick_ptr(T const (&arr
 
 template <int MODE, int E>
 __device__ __forceinline__ void products(uint64_t (&X)[ProdShape<MODE>::NIN][1 << E],
-                                         uint64_t (&Y)[ProdShape<MODE>::NOUT][1 << E], const LimbConst &c) {
+                                         uint64_t (&Y)[ProdShape<MODE>::NOUT][1 << E], const NttConst &c) {
 #pragma unroll
   for (int s = 0; s < (1 << E); ++s) {
     if constexpr (MODE == PROD_MUL) {
-      Y[0][s] = mulmod(X[0][s], X[1][s], c.m.q, c.mu, c.k);
+      Y[0][s] = mulmod(X[0][s], X[1][s], c.q, c.mu, c.k);
     } else {
-      Y[0][s] = mulmod(X[0][s], X[2][s], c.m.q, c.mu, c.k);
-      Y[1][s] = madmod(X[0][s], X[3][s], X[1][s], X[2][s], c.m.q, c.mu, c.k);
-      Y[2][s] = mulmod(X[1][s], X[3][s], c.m.q, c.mu, c.k);
+      Y[0][s] = mulmod(X[0][s], X[2][s], c.q, c.mu, c.k);
+      Y[1][s] = madmod(X[0][s], X[3][s], X[1][s], X[2][s], c.q, c.mu, c.k);
+      Y[2][s] = mulmod(X[1][s], X[3][s], c.q, c.mu, c.k);
     }
   }
 }
@@ -642,25 +698,15 @@ __device__ __forceinline__ void products_mont(uint64_t (&X)[ProdShape<MODE>::NIN
   }
 }
 
-// Forward outputs ([0, 16q)) brought to the factor range of products_mont.
-// Factors below 16q already keep a product below q R for q < 2^56
-// (256 q^2 < q 2^64), and the tensor's sum of two products for q < 2^55:
-// such limbs skip the reduction (k, the bit length, is uniform per
+// Forward outputs (lazy words, below 256q up to 56 bits) brought to the factor
+// range of products_mont, below 2q.  Up to 47 bits the lazy words already keep
+// the tensor's sum of two products below q R (2 (207 q)^2 < q 2^64: 17 stages
+// of 12q on inputs of at most 3q), and the step is skipped (k is uniform per
 // workgroup, so the test is a scalar branch).
-template <int MODE, int E>
-__device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1 << E], const ModQ &m, uint64_t mu, uint32_t k) {
-  if (k <= (MODE == PROD_TENSOR ? 55u : 56u)) return;
-  if (k >= 34) {  // quotient estimate: [0, 2q) for either product
-    const uint32_t c = est_c(mu, k), sh = k - 33;
+template <int E> __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1 << E], const NttConst &c) {
+  if (c.k < 48) return;
 #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) x[s] = reduce_est(x[s], m.nq, c, sh);
-    return;
-  }
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) {
-    x[s] = csubn(csubn(x[s], m.nq4 + m.nq4), m.nq4);
-    if constexpr (MODE == PROD_TENSOR) x[s] = csubn(x[s], m.nq2);
-  }
+  for (int s = 0; s < (1 << E); ++s) x[s] = reduce_est(x[s], c.nq, c.ce, c.k - 33);
 }
 
 // One workgroup per block of 2^B coefficients of one (batch entry, limb):
@@ -675,24 +721,11 @@ __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1 << E], const Mod
 // and lc must hold the folded constants (N^-1 R in place of N^-1), also for
 // the inverse column pass that completes the transform.  Without DO_INV the
 // products are exact (Barrett) and lc the plain constants.
-// Workgroup `blk` of the fused product over batch x limbs units (the body of
-// k_prod and of its grouped form).
-template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
-__device__ __forceinline__ void prod_block(const ProdArgs &a, const Tw *__restrict__ tw,
-                                           const LimbConst *__restrict__ lc, const MontLimb *__restrict__ mont,
-                                           uint32_t batch, uint32_t limbs, uint32_t blk) {
+template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV, bool FIX>
+__device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, uint64_t out_off, uint32_t blockStart,
+                                          const TwM *t, const NttConst &c, const MontLimb *mont, uint64_t *lds) {
   constexpr int NIN = ProdShape<MODE>::NIN, NOUT = ProdShape<MODE>::NOUT;
-  __shared__ __attribute__((aligned(16))) uint64_t lds[(DO_FWD || DO_INV) ? LdsSize<B>::value : 2];
-  constexpr uint32_t tiles = 1u << (LOGN - B);
-  const uint32_t tile = blk % tiles;
-  const uint32_t r = blk / tiles;
-  const uint32_t limb = r / batch, b = r % batch;
-  const LimbConst c = lc[limb];
-  const Tw *t = tw + (size_t)limb * 2 * (1u << LOGN);
-  const Tw *it = t + (1u << LOGN);
-  const uint32_t blockStart = tile << B;
-  const uint64_t in_off = (uint64_t)b * a.in_sb + ((uint64_t)limb << LOGN) + blockStart;
-  const uint64_t out_off = (uint64_t)b * a.out_sb + ((uint64_t)limb << LOGN) + blockStart;
+  const TwM *it = t + (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<B, E>;
   using L = InvLast<B, E>;
@@ -708,11 +741,11 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const Tw *__restri
       if (p > 0) __syncthreads();  // the previous input's last LDS reads are done
       // an opaque copy of the table pointer per input: the twiddles are re-read
       // from cache instead of being hoisted out of the loop into VGPRs
-      const Tw *tp = opaque(t);
+      const TwM *tp = opaque(t);
       load_global<B, E, F::LO, F::R, true>(v, pick_ptr(a.in, p) + in_off, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-      fwd_block_rounds<B, E, F::LO, F::R>(v, LOGN, lds, tid, blockStart, tp, c.m);
-      if constexpr (DO_INV) reduce_for_mont<MODE, E>(v, c.m, c.mu, c.k);
-      else reduce_fwd<E>(v, c.m, c.mu, c.k);
+      fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, tp, c);
+      if constexpr (DO_INV) reduce_for_mont<E>(v, c);
+      else reduce_out<E, FIX>(v, c);
     } else {
       load_global_m0<B, E, true>(v, pick_ptr(a.in, p) + in_off, lds, tid);
     }
@@ -727,7 +760,7 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const Tw *__restri
     });
   }
   uint64_t Y[NOUT][1 << E];
-  if constexpr (DO_INV) products_mont<MODE, E>(X, Y, c.m.q, mont[limb].qinv);
+  if constexpr (DO_INV) products_mont<MODE, E>(X, Y, c.q, mont->qinv);
   else products<MODE, E>(X, Y, c);
 #pragma unroll 1
   for (int o = 0; o < NOUT; ++o) {
@@ -741,8 +774,8 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const Tw *__restri
     });
     if constexpr (DO_INV) {
       __syncthreads();  // earlier LDS reads of this workgroup are done
-      inv_block_rounds<B, E, 0, E>(v, LOGN, lds, tid, blockStart, opaque(it), c);
-      if constexpr (B == LOGN) reduce_inv<E>(v, c.m);
+      inv_block_rounds<B, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, opaque(it), c);
+      if constexpr (B == LOGN) reduce_out<E, FIX>(v, c);
       store_global<B, E, L::LO, L::R>(v, pick_ptr(a.out, o) + out_off, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
     } else {
       store_global_m0<B, E>(v, pick_ptr(a.out, o) + out_off, lds, tid);
@@ -750,9 +783,31 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const Tw *__restri
   }
 }
 
+// Workgroup `blk` of the fused product over batch x limbs units (the body of
+// k_prod and of its grouped form).
 template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
-__global__ __launch_bounds__(1 << (B - E)) void k_prod(ProdArgs a, const Tw *__restrict__ tw,
-                                                        const LimbConst *__restrict__ lc,
+__device__ __forceinline__ void prod_block(const ProdArgs &a, const TwM *__restrict__ tw,
+                                           const NttConst *__restrict__ lc, const MontLimb *__restrict__ mont,
+                                           uint32_t batch, uint32_t limbs, uint32_t blk) {
+  __shared__ __attribute__((aligned(16))) uint64_t lds[(DO_FWD || DO_INV) ? LdsSize<B>::value : 2];
+  constexpr uint32_t tiles = 1u << (LOGN - B);
+  const uint32_t tile = blk % tiles;
+  const uint32_t r = blk / tiles;
+  const uint32_t limb = r / batch, b = r % batch;
+  const NttConst c = lc[limb];
+  const TwM *t = tw + (size_t)limb * 2 * (1u << LOGN);
+  const uint32_t blockStart = tile << B;
+  const uint64_t in_off = (uint64_t)b * a.in_sb + ((uint64_t)limb << LOGN) + blockStart;
+  const uint64_t out_off = (uint64_t)b * a.out_sb + ((uint64_t)limb << LOGN) + blockStart;
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    prod_body<LOGN, B, E, MODE, DO_FWD, DO_INV, decltype(FX)::value>(a, in_off, out_off, blockStart, t, c, mont + limb,
+                                                                     lds);
+  });
+}
+
+template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
+__global__ __launch_bounds__(1 << (B - E)) void k_prod(ProdArgs a, const TwM *__restrict__ tw,
+                                                        const NttConst *__restrict__ lc,
                                                         const MontLimb *__restrict__ mont, uint32_t batch,
                                                         uint32_t limbs) {
   prod_block<LOGN, B, E, MODE, DO_FWD, DO_INV>(a, tw, lc, mont, batch, limbs, blockIdx.x);
@@ -855,13 +910,13 @@ __global__ __launch_bounds__(256) void k_ct_matmul(const uint64_t *__restrict__ 
 // words of one (batch entry, limb), coalesced, limb constants uniform per
 // workgroup.
 template <int MODE>
-__device__ __forceinline__ void elem_block(const ProdArgs &a, const LimbConst *__restrict__ lc, uint32_t batch,
+__device__ __forceinline__ void elem_block(const ProdArgs &a, const NttConst *__restrict__ lc, uint32_t batch,
                                            uint32_t limbs, uint32_t log_n, uint32_t tiles, uint32_t blk) {
   constexpr int NIN = ProdShape<MODE>::NIN, NOUT = ProdShape<MODE>::NOUT;
   const uint32_t tile = blk % tiles;
   const uint32_t r = blk / tiles;
   const uint32_t limb = r / batch, b = r % batch;
-  const LimbConst c = lc[limb];
+  const NttConst c = lc[limb];
   const uint32_t n = 1u << log_n;
   const uint64_t in_off = (uint64_t)b * a.in_sb + ((uint64_t)limb << log_n) + tile * 2048u;
   const uint64_t out_off = (uint64_t)b * a.out_sb + ((uint64_t)limb << log_n) + tile * 2048u;
@@ -884,7 +939,7 @@ __device__ __forceinline__ void elem_block(const ProdArgs &a, const LimbConst *_
 }
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_elem(ProdArgs a, const LimbConst *__restrict__ lc, uint32_t batch,
+__global__ __launch_bounds__(256) void k_elem(ProdArgs a, const NttConst *__restrict__ lc, uint32_t batch,
                                               uint32_t limbs, uint32_t log_n, uint32_t tiles) {
   elem_block<MODE>(a, lc, batch, limbs, log_n, tiles, blockIdx.x);
 }

@@ -18,10 +18,10 @@ namespace hentt_rt {
 template <int LOGN, int MODE, int PEC, int PE, bool ALL_FLAGS>
 void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, bool in_coeff, bool out_coeff,
                      uint64_t *ws, hipStream_t st) {
-  const Tw *tw = t->s->d_tw;
+  const TwM *tw = t->s->d_twm;
   // outputs going back to the coefficient domain take Montgomery products,
   // whose R^-1 the inverse transform's folded N^-1 R scaling cancels
-  const LimbConst *lc = out_coeff ? t->s->d_lcm : t->s->d_lc;
+  const NttConst *lc = out_coeff ? t->s->d_ncm : t->s->d_nc;
   const MontLimb *mont = t->s->d_mont;
   const uint32_t L = t->limbs;
   const uint32_t units = batch * L;

@@ -28,6 +28,26 @@ struct MontLimb {
   uint64_t pad;
 };
 
+// A root power in the form the transforms multiply by (mul_tw in modarith.hpp):
+// A = W 2^30 mod q and B = W 2^62 mod q, each split at bit 30 (A = a1 2^30 + a0,
+// B = b1 2^30 + b0), in one 16-byte word.
+struct alignas(16) TwM { uint32_t a0, a1, b0, b1; };
+
+// Per-limb constants of the transforms.
+struct alignas(16) NttConst {
+  uint64_t q, nq;        // q and -q mod 2^64
+  uint64_t mu;           // floor(2^(2k) / q) (Barrett)
+  uint64_t off;          // 12 q, the bound of a mul_tw product
+  uint32_t qlo, qhi;     // q split at bit 30
+  uint32_t qi;           // -qlo^-1 mod 2^32
+  uint32_t k;            // bit length of q
+  uint32_t c64;          // floor(2^64 / q) (k >= 34, else 0)
+  uint32_t ce;           // floor(2^(k+31) / q)
+  uint32_t s0, s1;       // shifts of the quotient estimate of reduce_word
+  TwM ninv, ninvw;       // N^-1 and N^-1 psi^-brv(1)
+};
+static_assert(sizeof(NttConst) == 96, "read field by field as 12 words (ld_nc)");
+
 // A root power and its Shoup quotient (W, W' = floor(W 2^64 / q)), Algorithm 1.
 struct alignas(16) Tw { uint64_t w, ws; };
 

@@ -28,8 +28,9 @@ __device__ __forceinline__ uint64_t rs_prologue(uint64_t x, uint64_t qL, uint64_
 }
 
 // (c - t) qL^-1 mod q for canonical c, t: canonical.
-__device__ __forceinline__ uint64_t rs_epilogue(uint64_t c, uint64_t t, const RsLimb &r, const ModQ &m) {
-  return reduce_4q(shoup(r.w, r.ws, c + m.q - t, m.nq), m);
+__device__ __forceinline__ uint64_t rs_epilogue(uint64_t c, uint64_t t, const RsLimb &r, const NttConst &n) {
+  const uint64_t x = shoup(r.w, r.ws, c + n.q - t, n.nq);
+  return csubn(csubn(x, n.nq + n.nq), n.nq);
 }
 
 struct RsArgs {
@@ -51,27 +52,30 @@ __device__ __forceinline__ void rs_unit(uint32_t u, uint32_t batch, uint32_t &b,
 // Whole transform per workgroup (N <= 2^14): prologue, forward rounds,
 // canonical reduction, epilogue.
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const Tw *__restrict__ tw,
-                                                               const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const TwM *__restrict__ tw,
+                                                               const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<LOGN>::value];
   uint32_t b, i;
   rs_unit(blockIdx.x, a.batch, b, i);
-  const ModQ m = lc[i].m;
+  const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
-  const Tw *t = tw + (size_t)i * 2 * (1u << LOGN);
+  const TwM *t = tw + (size_t)i * 2 * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<LOGN, E>;
-  uint64_t v[1 << E];
-  load_global<LOGN, E, F::LO, F::R>(v, a.tl + ((uint64_t)b << LOGN), RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, m.q);
-  fwd_block_rounds<LOGN, E, F::LO, F::R>(v, LOGN, lds, tid, 0, t, m);
-  reduce_fwd<E>(v, m, lc[i].mu, lc[i].k);
-  uint64_t cv[1 << E];
-  load_global_m0<LOGN, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN), lds, tid);
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, m);
-  store_global_m0<LOGN, E>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global<LOGN, E, F::LO, F::R>(v, a.tl + ((uint64_t)b << LOGN), RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
+  #pragma unroll
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, c.q);
+    fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, t, c);
+    reduce_out<E, FIX>(v, c);
+    uint64_t cv[1 << E];
+    load_global_m0<LOGN, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN), lds, tid);
+  #pragma unroll
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c);
+    store_global_m0<LOGN, E>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), lds, tid);
+  });
 }
 
 // Column pass (first EC forward stages) of t_i from the last limb, into out.
@@ -81,55 +85,61 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const Tw
 // a multiple of 8); limb-major order re-read the whole batch's last limbs
 // from HBM or the MALL once per limb.
 template <int LOGN, int EC>
-__global__ __launch_bounds__(256) void k_rs_cols(RsArgs a, const Tw *__restrict__ tw,
-                                                 const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(256) void k_rs_cols(RsArgs a, const TwM *__restrict__ tw,
+                                                 const NttConst *__restrict__ lc) {
   constexpr uint32_t tiles = (1u << (LOGN - EC)) / 256;
   constexpr int LO = LOGN - EC;
   const uint32_t u = blockIdx.x / tiles;
   const uint32_t b = u / a.L, i = u % a.L;
   const uint32_t col = (blockIdx.x % tiles) * 256 + threadIdx.x;
-  const ModQ m = lc[i].m;
+  const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
-  uint64_t v[1 << EC];
-  load_global<LOGN, EC, LO, EC, true>(v, a.tl + ((uint64_t)b << LOGN), col);
-#pragma unroll
-  for (int s = 0; s < (1 << EC); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, m.q);
-  fwd_round<LOGN, EC, LO, EC, 0>(v, LOGN, 0, col, tw + (size_t)i * 2 * (1u << LOGN), m);
-  store_global<LOGN, EC, LO, EC, true>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), col);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << EC];
+    load_global<LOGN, EC, LO, EC, true>(v, a.tl + ((uint64_t)b << LOGN), col);
+  #pragma unroll
+    for (int s = 0; s < (1 << EC); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, c.q);
+    fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, tw + (size_t)i * 2 * (1u << LOGN), c);
+    store_global<LOGN, EC, LO, EC, true>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), col);
+  });
 }
 
 // Block pass (remaining stages) in place on out, then the epilogue.
 template <int LOGN, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_rs_blocks(RsArgs a, const Tw *__restrict__ tw,
-                                                             const LimbConst *__restrict__ lc) {
+__global__ __launch_bounds__(1 << (B - E)) void k_rs_blocks(RsArgs a, const TwM *__restrict__ tw,
+                                                             const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
   uint32_t b, i;
   rs_unit(blockIdx.x / tiles, a.batch, b, i);
   const uint32_t blockStart = (blockIdx.x % tiles) << B;
-  const ModQ m = lc[i].m;
+  const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
   uint64_t *p = a.out + (((uint64_t)b * a.L + i) << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<B, E>;
-  uint64_t v[1 << E];
-  load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-  fwd_block_rounds<B, E, F::LO, F::R>(v, LOGN, lds, tid, blockStart, tw + (size_t)i * 2 * (1u << LOGN), m);
-  reduce_fwd<E>(v, m, lc[i].mu, lc[i].k);
-  uint64_t cv[1 << E];
-  load_global_m0<B, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN) + blockStart, lds, tid);
-#pragma unroll
-  for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, m);
-  store_global_m0<B, E>(v, p, lds, tid);
+  by_class(c, [&](auto FX) __attribute__((always_inline)) {
+    constexpr bool FIX = decltype(FX)::value;
+    uint64_t v[1 << E];
+    load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
+    fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, tw + (size_t)i * 2 * (1u << LOGN), c);
+    reduce_out<E, FIX>(v, c);
+    uint64_t cv[1 << E];
+    load_global_m0<B, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN) + blockStart, lds, tid);
+  #pragma unroll
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c);
+    store_global_m0<B, E>(v, p, lds, tid);
+  });
 }
 
 // Coefficient-domain rescale: element-wise, tiles of 2048 words.
-__global__ __launch_bounds__(256) void k_rs_coeff(RsArgs a, const LimbConst *__restrict__ lc, uint32_t log_n,
+__global__ __launch_bounds__(256) void k_rs_coeff(RsArgs a, const NttConst *__restrict__ lc, uint32_t log_n,
                                                   uint32_t tiles) {
   uint32_t b, i;
   rs_unit(blockIdx.x / tiles, a.batch, b, i);
   const uint32_t n = 1u << log_n, base = (blockIdx.x % tiles) * 2048u;
-  const ModQ m = lc[i].m;
+  const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
   const uint64_t *ci = a.c + (((uint64_t)b * (a.L + 1) + i) << log_n);
   const uint64_t *cl = a.c + (((uint64_t)b * (a.L + 1) + a.L) << log_n);
@@ -137,7 +147,7 @@ __global__ __launch_bounds__(256) void k_rs_coeff(RsArgs a, const LimbConst *__r
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     const uint32_t k = base + threadIdx.x + 256u * s;
-    if (k < n) o[k] = rs_epilogue(ci[k], reduce_4q(rs_prologue(cl[k], a.qL, a.h, r, m.q), m), r, m);
+    if (k < n) o[k] = rs_epilogue(ci[k], csubn(csubn(rs_prologue(cl[k], a.qL, a.h, r, c.q), c.nq + c.nq), c.nq), r, c);
   }
 }
 

@@ -41,9 +41,11 @@ inline int hip_fail(hipError_t e) {
 struct Storage {
   std::atomic<int> refs{1};
   uint32_t log_n = 0, limbs = 0;
-  Tw *d_tw = nullptr;          // [limbs][2][N]
+  Tw *d_tw = nullptr;          // [limbs][2][N] Shoup pairs (the ABI's table views, the design ladder)
   LimbConst *d_lc = nullptr;   // [limbs]
-  LimbConst *d_lcm = nullptr;  // [limbs] the same with N^-1 R mod q for N^-1 (after Montgomery products)
+  TwM *d_twm = nullptr;        // [limbs][2][N] the transforms' tables
+  NttConst *d_nc = nullptr;    // [limbs]
+  NttConst *d_ncm = nullptr;   // [limbs] the same with N^-1 R mod q for N^-1 (after Montgomery products)
   MontLimb *d_mont = nullptr;  // [limbs] Montgomery constants
   std::vector<uint64_t> moduli;
   int device = 0;

@@ -56,16 +56,16 @@ template <int LOGN> void launch_rescale_ntt(const RsArgs &a, const Storage *s, h
   using P = RsPlan<LOGN>;
   if constexpr (P::WHOLE) {
     LaunchTimer lt_("k_rs_whole", LOGN, st);
-    hipLaunchKernelGGL((k_rs_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, a, s->d_tw, s->d_lc);
+    hipLaunchKernelGGL((k_rs_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, a, s->d_twm, s->d_nc);
   } else {
     {
       LaunchTimer lt_("k_rs_cols", LOGN, st);
       hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC>), dim3(units * ((1u << (LOGN - P::EC)) / 256)), dim3(256), 0, st, a,
-                         s->d_tw, s->d_lc);
+                         s->d_twm, s->d_nc);
     }
     LaunchTimer lt_("k_rs_blocks", LOGN, st);
     hipLaunchKernelGGL((k_rs_blocks<LOGN, P::B, 4>), dim3(units << (LOGN - P::B)), dim3(1 << (P::B - 4)), 0, st, a,
-                       s->d_tw, s->d_lc);
+                       s->d_twm, s->d_nc);
   }
 }
 typedef void (*rs_fn)(const RsArgs &, const Storage *, hipStream_t);
@@ -119,16 +119,16 @@ template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hip
   using P = KsPlan<LOGN>;
   if constexpr (P::WHOLE) {
     LaunchTimer lt_("k_ks_whole", LOGN, st);
-    hipLaunchKernelGGL((k_ks_whole<LOGN, 4>), dim3(a.batch * L1), dim3(1 << (LOGN - 4)), 0, st, a, s->d_tw, s->d_lc);
+    hipLaunchKernelGGL((k_ks_whole<LOGN, 4>), dim3(a.batch * L1), dim3(1 << (LOGN - 4)), 0, st, a, s->d_twm, s->d_nc);
   } else {
     {
       LaunchTimer lt_("k_ks_cols", LOGN, st);
       hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * L1 * ((1u << (LOGN - P::EC)) / 256)),
-                         dim3(256), 0, st, a, s->d_tw, s->d_lc);
+                         dim3(256), 0, st, a, s->d_twm, s->d_nc);
     }
     LaunchTimer lt_("k_ks_blocks", LOGN, st);
     hipLaunchKernelGGL((k_ks_blocks<LOGN, P::B, P::E>), dim3((a.batch * L1) << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0,
-                       st, a, s->d_tw, s->d_lc);
+                       st, a, s->d_twm, s->d_nc);
   }
 }
 typedef void (*ks_fn)(const KsArgs &, const Storage *, hipStream_t);
@@ -155,7 +155,7 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
   if (!ntt) {
     const uint32_t tiles = (uint32_t)((N + 2047) / 2048);
     LaunchTimer lt_("k_rs_coeff", (int)ln, st);
-    hipLaunchKernelGGL(k_rs_coeff, dim3(batch * L * tiles), dim3(256), 0, st, a, s->d_lc, ln, tiles);
+    hipLaunchKernelGGL(k_rs_coeff, dim3(batch * L * tiles), dim3(256), 0, st, a, s->d_nc, ln, tiles);
     HIPCHK(hipGetLastError());
     return HENTT_OK;
   }
@@ -169,9 +169,8 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
     Storage last;  // limb L's tables alone (a view: owns nothing)
     last.log_n = ln;
     last.limbs = 1;
-    last.d_tw = s->d_tw + (size_t)L * 2 * N;
-    last.d_lc = s->d_lc + L;
-    last.d_lcm = s->d_lcm + L;
+    last.d_twm = s->d_twm + (size_t)L * 2 * N;
+    last.d_nc = s->d_nc + L;
     last.d_mont = s->d_mont + L;
     last.device = s->device;
     const hentt_tables lv{&last, 1};

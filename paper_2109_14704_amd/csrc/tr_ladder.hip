@@ -83,6 +83,25 @@ template <int J> __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, uint
   return ((uint64_t)lane_xor32<J>(hi32(v), lane) << 32) | lane_xor32<J>(lo32(v), lane);
 }
 
+__device__ __forceinline__ Tw ld_pair(const Tw *t, uint32_t i) {
+  const __attribute__((address_space(4))) uint64_t *p = (const __attribute__((address_space(4))) uint64_t *)(t + i);
+  return Tw{p[0], p[1]};
+}
+
+// One stage over block bit LO with the classic butterfly (every stage corrects,
+// values below 8q), radix 2.
+template <int B, int E, int LO>
+__device__ __forceinline__ void classic_stage(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
+                                              uint32_t lanePart, const Tw *__restrict__ tw, const ModQ &m) {
+  using M = RoundMap<B, E, LO, 1>;
+#pragma unroll
+  for (int g = 0; g < (1 << (E - 1)); ++g) {
+    const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
+    const Tw w = ld_pair(tw, ((1u << (logn - B)) << (B - LO - 1)) + (J0 >> (LO + 1)));
+    ct_bfly(x[2 * g], x[2 * g + 1], w.w, w.ws, m);
+  }
+}
+
 // Radix-2 LDS rounds over block bits LO, LO-1, .., STOP (one stage each);
 // the last round's words end in LDS (stored and past a barrier).
 template <int B, int E, int LO, int STOP>
@@ -90,7 +109,7 @@ __device__ __forceinline__ void lds_r2_rounds(uint64_t (&x)[1 << E], uint32_t lo
                                               uint32_t blockStart, const Tw *__restrict__ tw, const ModQ &m) {
   using M = RoundMap<B, E, LO, 1>;
   const uint32_t lp = M::lane_part(tid);
-  fwd_round<B, E, LO, 1>(x, logn, blockStart, lp, tw, m);
+  classic_stage<B, E, LO>(x, logn, blockStart, lp, tw, m);
   if constexpr (LO == B - 1) __syncthreads();  // (the first round's words came from HBM)
   store_lds<B, E, LO, 1>(x, lds, lp);
   __syncthreads();
@@ -126,7 +145,7 @@ __device__ __forceinline__ void simd_stage(uint64_t (&v)[2 * S], uint32_t lane, 
     if (k & (1 << RBIT)) continue;
     const uint32_t rpart = IN_REG ? ((uint32_t)k << 6) : ((uint32_t)(k >> 1) << 7);
     const uint32_t g = chunkStart + lpart + rpart;
-    const Tw w = ld_tw(tw, base + (g >> (P + 1)));
+    const Tw w = ld_pair(tw, base + (g >> (P + 1)));
     ct_bfly(v[k], v[k | (1 << RBIT)], w.w, w.ws, m);
   }
   if constexpr (I + 1 < SP::C) simd_stage<S, I + 1>(v, lane, chunkStart, logn, tw, m);
@@ -193,8 +212,8 @@ void launch_naive_stages(const hentt_tables *t, uint64_t *x, uint64_t units, uin
 template <int E> void launch_staged15(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st) {
   const uint32_t L = t->limbs, units = batch * L;
   const char *name = E == 2 ? "k_fwd_blocks_r4" : E == 3 ? "k_fwd_blocks_r8" : "k_fwd_blocks_r16";
-  { LaunchTimer lt_("k_cols_fwd_r8", 15, st); hipLaunchKernelGGL((k_cols<15, 3, false>), dim3(units * ((1u << 12) / (256 * ColCpl<3>::value))), dim3(256), 0, st, col_args(x, (uint64_t)L << 15), t->s->d_tw, t->s->d_lc, batch, L); }
-  { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_tw, t->s->d_lc, batch, L); }
+  { LaunchTimer lt_("k_cols_fwd_r8", 15, st); hipLaunchKernelGGL((k_cols<15, 3, false>), dim3(units * ((1u << 12) / (256 * ColCpl<3>::value))), dim3(256), 0, st, col_args(x, (uint64_t)L << 15), t->s->d_twm, t->s->d_nc, batch, L); }
+  { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_twm, t->s->d_nc, batch, L); }
 }
 
 template <int S> void launch_simd15(const hentt_tables *t, uint64_t *x, uint64_t units, uint32_t batch,
@@ -230,7 +249,7 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
       {
         LaunchTimer lt_("k_fwd_blocks_r2", 15, st);
         hipLaunchKernelGGL((k_fwd_blocks<15, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x,
-                           t->s->d_tw, t->s->d_lc, batch, L);
+                           t->s->d_twm, t->s->d_nc, batch, L);
       }
       break;
     case HENTT_VARIANT_SIMD1:

@@ -18,11 +18,11 @@ void launch_whole(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, 
   const uint32_t L = t->limbs, units = batch * L;
   if (!inv) {
     LaunchTimer lt_("k_fwd_whole", LOGN, st);
-    hipLaunchKernelGGL((k_fwd_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_tw, t->s->d_lc,
+    hipLaunchKernelGGL((k_fwd_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_twm, t->s->d_nc,
                        batch, L);
   } else {
     LaunchTimer lt_("k_inv_whole", LOGN, st);
-    hipLaunchKernelGGL((k_inv_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_tw, t->s->d_lc,
+    hipLaunchKernelGGL((k_inv_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_twm, t->s->d_nc,
                        batch, L);
   }
 }
@@ -31,8 +31,8 @@ void launch_whole(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, 
 template <int LOGN, int EC, int E>
 void launch_two_pass(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, hipStream_t st) {
   constexpr int B = LOGN - EC;
-  const Tw *tw = t->s->d_tw;
-  const LimbConst *lc = t->s->d_lc;
+  const TwM *tw = t->s->d_twm;
+  const NttConst *lc = t->s->d_nc;
   const uint32_t L = t->limbs, units = batch * L;
   const dim3 gcols(units * ((1u << (LOGN - EC)) / (256 * ColCpl<EC>::value)));
   if (!inv) {

@@ -42,9 +42,9 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
   for (uint32_t i = 0; i < n; ++i) {
     const Storage *s = jobs[i].t->s;
     GroupJob &J = g.j[i];
-    J.tw = s->d_tw;
+    J.tw = s->d_twm;
     // outputs going back to the coefficient domain take Montgomery products
-    J.lc = out_coeff ? s->d_lcm : s->d_lc;
+    J.lc = out_coeff ? s->d_ncm : s->d_nc;
     J.mont = s->d_mont;
     J.batch = jobs[i].batch;
     J.limbs = jobs[i].t->limbs;
