@@ -51,7 +51,7 @@ __device__ __forceinline__ void batch_inv_block(uint64_t *p, uint32_t blockStart
   using L = InvLast<BATCH_B, BATCH_E>;
   uint64_t v[1 << BATCH_E];
   load_global_m0_fresh<BATCH_B, BATCH_E>(v, p, lds, tid);  // the previous tile ended with a barrier
-  inv_block_rounds<BATCH_B, BATCH_E, 0, BATCH_E, FIX>(v, logn, lds, tid, blockStart, it, c);
+  inv_block_rounds<BATCH_B, BATCH_B, BATCH_E, 0, BATCH_E, FIX>(v, logn, lds, tid, blockStart, it, c);
   if (logn == BATCH_B) reduce_out<BATCH_E, FIX>(v, c);
   store_global<BATCH_B, BATCH_E, L::LO, L::R>(v, p, RoundMap<BATCH_B, BATCH_E, L::LO, L::R>::lane_part(tid));
 }

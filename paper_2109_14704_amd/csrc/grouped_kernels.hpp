@@ -53,17 +53,17 @@ __device__ __forceinline__ uint32_t group_job(const GroupTable &g, uint32_t u) {
 // Column pass over `COMPS` components of every job (forward into the
 // workspace, or the inverse in place on the outputs).
 template <int LOGN, int E, bool INV, int COMPS>
-__global__ __launch_bounds__(256) void k_cols_g(GroupTable g) {
+__global__ __launch_bounds__(cols_lanes<E>()) void k_cols_g(GroupTable g) {
   constexpr uint32_t per = COMPS * cols_blocks_per_unit<LOGN, E>();
   const GroupJob &J = g.j[group_job(g, blockIdx.x / per)];
   cols_block<LOGN, E, INV>(J.ca, J.tw, J.lc, J.batch, J.limbs, blockIdx.x - J.ustart * per);
 }
 
-template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
+template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
 __global__ __launch_bounds__(1 << (B - E)) void k_prod_g(GroupTable g) {
   constexpr uint32_t per = 1u << (LOGN - B);
   const GroupJob &J = g.j[group_job(g, blockIdx.x / per)];
-  prod_block<LOGN, B, E, MODE, DO_FWD, DO_INV>(J.pa, J.tw, J.lc, J.mont, J.batch, J.limbs,
+  prod_block<LOGN, ST, B, E, MODE, DO_FWD, DO_INV>(J.pa, J.tw, J.lc, J.mont, J.batch, J.limbs,
                                               blockIdx.x - J.ustart * per);
 }
 

@@ -20,10 +20,9 @@
 namespace hentt {
 
 struct KsLimb {     // per target prime q_t of one level
+  TwM r, pm;        // 2^64 mod q_t, P mod q_t (t < l)
   uint64_t mu;      // floor(2^64 / q_t)
   uint64_t qinv;    // -q_t^-1 mod 2^64
-  uint64_t r, rs;   // 2^64 mod q_t and its Shoup quotient
-  uint64_t pm, pms; // P mod q_t and its Shoup quotient (t < l)
 };
 
 struct KsArgs {
@@ -36,10 +35,14 @@ struct KsArgs {
   uint32_t batch, l;
 };
 
-// A digit word x < q_j < 2^60 reduced modulo q_t into [0, 2 q_t) (the
-// estimate floor(x mu / 2^64) of x / q_t is short by at most one): a valid
-// lazy input of the forward transform.
-__device__ __forceinline__ uint64_t ks_lift(uint64_t x, uint64_t mu, uint64_t q) { return x - mulhi64(x, mu) * q; }
+// A digit word x < q_j < 2^60 as an input of the transform modulo q_t: as it is
+// (the forward transform takes any 60-bit word, see rs_prologue), except that
+// moduli of 33 or fewer bits reduce it into [0, 2 q_t) (the estimate
+// floor(x mu / 2^64) of x / q_t is short by at most one).
+__device__ __forceinline__ uint64_t ks_lift(uint64_t x, uint64_t mu, const NttConst &c) {
+  if (c.k < 34) x -= mulhi64(x, mu) * c.q;
+  return x;
+}
 
 // acc0 += v . key0 R^-1, acc1 += v . key1 R^-1 (mod q, accumulators kept
 // in [0, 2q)) for the words of v (lazy forward outputs, any 64-bit words: the
@@ -63,20 +66,21 @@ __device__ __forceinline__ void ks_mac(const uint64_t (&v)[1 << E], const uint64
 }
 
 // Accumulators (sums of Montgomery products, [0, 2q)) to canonical values:
-// times R mod q by a Shoup product, plus P c_s when cs (c_s's words of the
-// block, in the (0, E) map) is given; each Shoup product lies in [0, 4q).
+// times R mod q, plus P c_s when cs (c_s's words of the block, in the (0, E)
+// map) is given; est3 keeps the sum of the two products (12q each) below 16q.
 template <int B, int E>
 __device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb &kc, const NttConst &c,
                                           const uint64_t *cs, uint32_t lp) {
+  const uint32_t four = opaque4();
   if (cs) {
     uint64_t cv[1 << E];
     load_global<B, E, 0, E>(cv, cs, lp);
 #pragma unroll
     for (int s = 0; s < (1 << E); ++s)
-      acc[s] = reduce_word(shoup(kc.r, kc.rs, acc[s], c.nq) + shoup(kc.pm, kc.pms, cv[s], c.nq), c);
+      acc[s] = reduce_word(mul_tw_add(kc.pm, cv[s], est3(mul_tw(kc.r, acc[s], c, four), c), c, four), c);
   } else {
 #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(shoup(kc.r, kc.rs, acc[s], c.nq), c);
+    for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(mul_tw(kc.r, acc[s], c, four), c);
   }
 }
 
@@ -113,7 +117,7 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw
       load_global<LOGN, E, F::LO, F::R>(v, a.d + (((uint64_t)b * a.l + j) << LOGN),
                                          RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
   #pragma unroll
-      for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c.q);
+      for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c);
       // an opaque copy of the table pointer per digit: the twiddles (the same
       // for every digit) are re-read from cache instead of held in VGPRs
       fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, opaque(tt), c);
@@ -129,32 +133,31 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw
 
 // Two-pass sizes, pass 1: column pass of digit j modulo q_t into e.
 template <int LOGN, int EC>
-__global__ __launch_bounds__(256) void k_ks_cols(KsArgs a, const TwM *__restrict__ tw,
-                                                 const NttConst *__restrict__ lc) {
-  constexpr uint32_t tiles = (1u << (LOGN - EC)) / 256;
-  constexpr int LO = LOGN - EC;
+__global__ __launch_bounds__(cols_lanes<EC>()) void k_ks_cols(KsArgs a, const TwM *__restrict__ tw,
+                                                              const NttConst *__restrict__ lc) {
+  __shared__ uint64_t lds[cols_lds<EC>()];
+  constexpr uint32_t tiles = fcols_blocks_per_unit<LOGN, EC>();
   const uint32_t L1 = a.l + 1;
   uint32_t r = blockIdx.x / tiles;
-  const uint32_t col = (blockIdx.x % tiles) * 256 + threadIdx.x;
+  const uint32_t col = fcol<EC>(blockIdx.x % tiles);
   const uint32_t t = r % L1;
   r /= L1;
   const uint32_t j = r % a.l, b = r / a.l;
   const NttConst c = lc[t];
   const uint64_t mu = a.kc[t].mu;
+  const uint64_t *src = a.d + (((uint64_t)b * a.l + j) << LOGN);
+  uint64_t *dst = a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN);
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
-    constexpr bool FIX = decltype(FX)::value;
-    uint64_t v[1 << EC];
-    load_global<LOGN, EC, LO, EC, true>(v, a.d + (((uint64_t)b * a.l + j) << LOGN), col);
-  #pragma unroll
-    for (int s = 0; s < (1 << EC); ++s) v[s] = ks_lift(v[s], mu, c.q);
-    fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, tw + (size_t)t * 2 * (1u << LOGN), c);
-    store_global<LOGN, EC, LO, EC, true>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN), col);
+    fcol_pass<LOGN, EC, decltype(FX)::value>(
+        [&](uint32_t row) { return ks_lift(gload<true>(src, (row << (LOGN - EC)) + col), mu, c); },
+        [&](uint32_t row, uint64_t v) { gstore<true>(dst, (row << (LOGN - EC)) + col, v); },
+        tw + (size_t)t * 2 * (1u << LOGN), c, lds);
   });
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
 // rounds of every digit, accumulated with the key in registers.
-template <int LOGN, int B, int E>
+template <int LOGN, int ST, int B, int E>
 __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM *__restrict__ tw,
                                                              const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM 
   const KsLimb kc = a.kc[t];
   const TwM *tt = tw + (size_t)t * 2 * (1u << LOGN);
   const uint32_t tid = threadIdx.x;
-  using F = FwdFirst<B, E>;
+  using F = FwdFirst<ST, E>;
   using M0 = RoundMap<B, E, 0, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;

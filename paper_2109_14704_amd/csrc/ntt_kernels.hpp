@@ -388,29 +388,30 @@ __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t
   }
 }
 
-// Inverse rounds over block bits [LO, B), starting from registers loaded with
-// the (LO, R) map.  Ends with the lane holding the last round's map
-// (covering [B - Rlast, B)); words enter below 16q and leave below 16q, or
+// Inverse rounds over block bits [LO, ST), starting from registers loaded with
+// the (LO, R) map; ST < B when the lanes of a workgroup hold several blocks of
+// 2^ST words side by side.  Ends with the lane holding the last round's map
+// (covering [ST - Rlast, ST)); words enter below 16q and leave below 16q, or
 // are the transform's lazy outputs.
-template <int B, int E, int LO, int R, bool FIX>
+template <int B, int ST, int E, int LO, int R, bool FIX>
 __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
                                                  uint32_t blockStart, const TwM* __restrict__ itw,
                                                  const NttConst& c) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  inv_round<B, E, LO, R, 5, (LO + R < B ? 5 : 4), FIX>(x, logn, blockStart, lp, itw, c);
-  if constexpr (LO + R < B) {
+  inv_round<B, E, LO, R, 5, (LO + R < ST ? 5 : 4), FIX>(x, logn, blockStart, lp, itw, c);
+  if constexpr (LO + R < ST) {
     constexpr int LO2 = LO + R;
-    constexpr int R2 = (B - LO2) < E ? (B - LO2) : E;
+    constexpr int R2 = (ST - LO2) < E ? (ST - LO2) : E;
     store_lds<B, E, LO, R>(x, lds, lp);
     __syncthreads();
     using M2 = RoundMap<B, E, LO2, R2>;
     load_lds<B, E, LO2, R2>(x, lds, M2::lane_part(tid));
-    inv_block_rounds<B, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, itw, c);
+    inv_block_rounds<B, ST, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, itw, c);
   }
 }
 
-// Round geometry helpers.
+// Round geometry helpers, for the block pass's stage count.
 template <int B, int E> struct FwdFirst {   // forward: first round is the short one
   static constexpr int R = (B % E) ? (B % E) : E;
   static constexpr int LO = B - R;
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_inv_whole(uint64_t* __restr
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
     load_global_m0_fresh<LOGN, E>(v, p, lds, tid);
-    inv_block_rounds<LOGN, E, 0, (LOGN < E ? LOGN : E), FIX>(v, LOGN, lds, tid, 0, it, c);
+    inv_block_rounds<LOGN, LOGN, E, 0, (LOGN < E ? LOGN : E), FIX>(v, LOGN, lds, tid, 0, it, c);
     reduce_out<E, FIX>(v, c);
     store_global<LOGN, E, L::LO, L::R>(v, p, RoundMap<LOGN, E, L::LO, L::R>::lane_part(tid));
   });
@@ -545,14 +546,91 @@ __device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, ui
   }
 }
 
+// Column pass of EC = 6 .. 8 stages (LCOL) through LDS: a workgroup holds 2^EC
+// rows of LC neighbouring columns, one column and 16 rows per lane.  The four
+// stages of the largest gaps and the EC - 4 others are two register rounds
+// with one LDS exchange between them; words of a row lie side by side in LDS
+// as in memory, so that no access conflicts.  The first round's twiddles are
+// scalar loads, and with 64 columns the second's too (a wave then holds one
+// set of rows).  ld(row) and st(row, word) move this lane's word.
+//
+// Passes of five stages in registers alone run at the rate of a copy with the
+// VALU half idle, while the fused product and key-switch blocks behind them
+// are bound by VALU issue: every stage moved here takes seven (tensor) or
+// three (polymul) transforms' worth of instructions from those.  64 columns
+// for 6 and 7 stages, 16 for 8: at 7 stages 32 columns (half the workgroup)
+// were 2-4% slower on the tensors, at 8 stages 64 columns (1024 lanes, one
+// workgroup per CU) 5%.
+template <int EC> constexpr uint32_t LC = EC == 8 ? 16u : 64u;
+template <int LOGN, int EC, bool INV, bool FIX, typename LD, typename STO>
+__device__ __forceinline__ void lcol_pass(LD ld, STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
+  constexpr int R1 = 4, R2 = EC - R1, G = 16 >> R2;
+  static_assert(R2 >= 2 && R2 <= 4, "two rounds of at most 16 words");
+  uint32_t w = threadIdx.x / LC<EC>;
+  if constexpr (LC<EC> == 64) w = __builtin_amdgcn_readfirstlane(w);
+  uint64_t *l = lds + threadIdx.x % LC<EC>;
+  uint64_t v[1 << R1], a[G][1 << R2];
+  if constexpr (!INV) {
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) v[r] = ld((r << R2) + w);
+    fwd_round<LOGN, R1, LOGN - R1, R1, FIX>(v, LOGN, 0, 0, t, c);
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) l[((r << R2) + w) * LC<EC>] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g) {
+      const uint32_t hi = w * G + g;
+#pragma unroll
+      for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = l[((hi << R2) + k) * LC<EC>];
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g) {
+      const uint32_t hi = w * G + g;
+      fwd_round<LOGN, R2, LOGN - EC, R2, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
+#pragma unroll
+      for (uint32_t k = 0; k < (1u << R2); ++k) st((hi << R2) + k, a[g][k]);
+    }
+  } else {
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g) {
+#pragma unroll
+      for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = ld(((w * G + g) << R2) + k);
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g) {
+      const uint32_t hi = w * G + g;
+      inv_round<LOGN, R2, LOGN - EC, R2, 4, 5, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
+#pragma unroll
+      for (uint32_t k = 0; k < (1u << R2); ++k) l[((hi << R2) + k) * LC<EC>] = a[g][k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) v[r] = l[((r << R2) + w) * LC<EC>];
+    inv_round<LOGN, R1, LOGN - R1, R1, 5, 4, FIX>(v, LOGN, 0, 0, t, c);
+    reduce_out<R1, FIX>(v, c);
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) st((r << R2) + w, v[r]);
+  }
+}
+
+// Geometry of a column pass of EC stages: lanes and LDS words of a workgroup,
+// workgroups per polynomial.
+template <int EC> constexpr bool LCOL = EC >= 6;
+template <int EC> constexpr uint32_t cols_lds() { return LCOL<EC> ? LC<EC> << EC : 2u; }
+template <int EC> constexpr uint32_t cols_lanes() { return LCOL<EC> ? (LC<EC> << EC) / 16 : 256u; }
+template <int LOGN, int EC> constexpr uint32_t cols_blocks_per_unit() {
+  return LCOL<EC> ? (1u << (LOGN - EC)) / LC<EC> : (1u << (LOGN - EC)) / (256 * ColCpl<EC>::value);
+}
+
 // Workgroup `blk` of a column pass over batch x limbs units of every
 // component of `a` (the body of k_cols and of its grouped form).
 template <int LOGN, int E, bool INV>
 __device__ __forceinline__ void cols_block(const ColArgs &a, const TwM *__restrict__ tw,
                                            const NttConst *__restrict__ lc, uint32_t batch, uint32_t limbs,
                                            uint32_t blk) {
+  __shared__ uint64_t lds[cols_lds<E>()];
   constexpr uint32_t CPL = ColCpl<E>::value;
-  constexpr uint32_t tiles = (1u << (LOGN - E)) / (256 * CPL);
+  constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, E>();
   const uint32_t units = batch * limbs;
   const uint32_t tile = blk % tiles;
   const uint32_t r = blk / tiles;
@@ -565,25 +643,62 @@ __device__ __forceinline__ void cols_block(const ColArgs &a, const TwM *__restri
   const TwM *t = tw + ((size_t)limb * 2 + (INV ? 1 : 0)) * (1u << LOGN);
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
-    if constexpr (CPL == 2) col_pass2<LOGN, E, INV, FIX>(src, dst, tile * 512 + 2 * threadIdx.x, t, c);
-    else col_pass<LOGN, E, INV, FIX>(src, dst, tile * 256 + threadIdx.x, t, c);
+    if constexpr (LCOL<E>) {
+      const uint32_t col = tile * LC<E> + threadIdx.x % LC<E>;
+      lcol_pass<LOGN, E, INV, FIX>([&](uint32_t row) { return gload<true>(src, (row << (LOGN - E)) + col); },
+                                   [&](uint32_t row, uint64_t v) { gstore<true>(dst, (row << (LOGN - E)) + col, v); },
+                                   t, c, lds);
+    } else if constexpr (CPL == 2) {
+      col_pass2<LOGN, E, INV, FIX>(src, dst, tile * 512 + 2 * threadIdx.x, t, c);
+    } else {
+      col_pass<LOGN, E, INV, FIX>(src, dst, tile * 256 + threadIdx.x, t, c);
+    }
   });
 }
 
-// Workgroups per component of a column pass over `units` (batch x limbs) units.
-template <int LOGN, int E> constexpr uint32_t cols_blocks_per_unit() {
-  return (1u << (LOGN - E)) / (256 * ColCpl<E>::value);
-}
-
 template <int LOGN, int E, bool INV>
-__global__ __launch_bounds__(256) void k_cols(ColArgs a, const TwM *__restrict__ tw, const NttConst *__restrict__ lc,
-                                              uint32_t batch, uint32_t limbs) {
+__global__ __launch_bounds__(cols_lanes<E>()) void k_cols(ColArgs a, const TwM *__restrict__ tw,
+                                                          const NttConst *__restrict__ lc, uint32_t batch,
+                                                          uint32_t limbs) {
   cols_block<LOGN, E, INV>(a, tw, lc, batch, limbs, blockIdx.x);
 }
 
-// Block pass of the forward transform: stages LOGN-B .. LOGN-1 on contiguous
-// blocks of 2^B elements; canonical output.
-template <int LOGN, int B, int E>
+// Forward column pass of EC stages with its own load (a prologue fused into
+// it), for the rescale and the key switch: one column per lane.
+template <int LOGN, int EC> constexpr uint32_t fcols_blocks_per_unit() {
+  return LCOL<EC> ? cols_blocks_per_unit<LOGN, EC>() : (1u << (LOGN - EC)) / 256;
+}
+template <int EC> __device__ __forceinline__ uint32_t fcol(uint32_t tile) {
+  if constexpr (LCOL<EC>) return tile * LC<EC> + threadIdx.x % LC<EC>;
+  else return tile * 256 + threadIdx.x;
+}
+template <int LOGN, int EC, bool FIX, typename LD, typename STO>
+__device__ __forceinline__ void fcol_pass(LD ld, STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
+  if constexpr (LCOL<EC>) {
+    lcol_pass<LOGN, EC, false, FIX>(ld, st, t, c, lds);
+  } else {
+    uint64_t v[1 << EC];
+#pragma unroll
+    for (uint32_t r = 0; r < (1u << EC); ++r) v[r] = ld(r);
+    fwd_round<LOGN, EC, LOGN - EC, EC, FIX>(v, LOGN, 0, 0, t, c);
+#pragma unroll
+    for (uint32_t r = 0; r < (1u << EC); ++r) st(r, v[r]);
+  }
+}
+
+// Column stages of a two-pass transform or product at N = 2^log_n (measured over
+// 6 to 8 stages and, through registers alone, 1 to 5): the blocks behind it are
+// of 2^7 to 2^9 words, so that one wave holds a block (three radix-8 rounds and
+// no barrier).
+constexpr int two_pass_cols(int log_n) { return log_n <= 15 ? 6 : log_n - 9; }
+
+// Words of a workgroup of a two-pass transform's block pass of ST stages, 2^E
+// words per lane: at least one wave.
+constexpr int block_words(int st, int e) { return st > e + 6 ? st : e + 6; }
+
+// Block pass of the forward transform: the last ST stages, on 2^(B - ST)
+// contiguous blocks of 2^ST elements per workgroup; canonical output.
+template <int LOGN, int ST, int B, int E>
 __global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restrict__ x, const TwM *__restrict__ tw,
                                                               const NttConst *__restrict__ lc, uint32_t batch,
                                                               uint32_t limbs) {
@@ -595,7 +710,7 @@ __global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restric
   const uint32_t blockStart = un.tile << B;
   uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
-  using F = FwdFirst<B, E>;
+  using F = FwdFirst<ST, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
@@ -606,8 +721,8 @@ __global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restric
   });
 }
 
-// Block pass of the inverse transform: stages 0 .. B-1; lazy [0, 2q) output.
-template <int LOGN, int B, int E>
+// Block pass of the inverse transform: stages 0 .. ST-1; lazy output below 16q.
+template <int LOGN, int ST, int B, int E>
 __global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restrict__ x, const TwM *__restrict__ tw,
                                                               const NttConst *__restrict__ lc, uint32_t batch,
                                                               uint32_t limbs) {
@@ -619,12 +734,12 @@ __global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restric
   const uint32_t blockStart = un.tile << B;
   uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
-  using L = InvLast<B, E>;
+  using L = InvLast<ST, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
     load_global_m0_fresh<B, E>(v, p, lds, tid);
-    inv_block_rounds<B, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, it, c);
+    inv_block_rounds<B, ST, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, it, c);
     store_global<B, E, L::LO, L::R>(v, p, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
   });
 }
@@ -721,14 +836,14 @@ template <int E> __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1
 // and lc must hold the folded constants (N^-1 R in place of N^-1), also for
 // the inverse column pass that completes the transform.  Without DO_INV the
 // products are exact (Barrett) and lc the plain constants.
-template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV, bool FIX>
+template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV, bool FIX>
 __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, uint64_t out_off, uint32_t blockStart,
                                           const TwM *t, const NttConst &c, const MontLimb *mont, uint64_t *lds) {
   constexpr int NIN = ProdShape<MODE>::NIN, NOUT = ProdShape<MODE>::NOUT;
   const TwM *it = t + (1u << LOGN);
   const uint32_t tid = threadIdx.x;
-  using F = FwdFirst<B, E>;
-  using L = InvLast<B, E>;
+  using F = FwdFirst<ST, E>;
+  using L = InvLast<ST, E>;
   // The transform code appears once for all inputs and once for all outputs
   // (rolled loops): unrolled per polynomial it would outgrow the instruction
   // cache.  Results move between the loop's working registers and the
@@ -774,8 +889,8 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
     });
     if constexpr (DO_INV) {
       __syncthreads();  // earlier LDS reads of this workgroup are done
-      inv_block_rounds<B, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, opaque(it), c);
-      if constexpr (B == LOGN) reduce_out<E, FIX>(v, c);
+      inv_block_rounds<B, ST, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, opaque(it), c);
+      if constexpr (ST == LOGN) reduce_out<E, FIX>(v, c);
       store_global<B, E, L::LO, L::R>(v, pick_ptr(a.out, o) + out_off, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
     } else {
       store_global_m0<B, E>(v, pick_ptr(a.out, o) + out_off, lds, tid);
@@ -785,7 +900,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
 
 // Workgroup `blk` of the fused product over batch x limbs units (the body of
 // k_prod and of its grouped form).
-template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
+template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
 __device__ __forceinline__ void prod_block(const ProdArgs &a, const TwM *__restrict__ tw,
                                            const NttConst *__restrict__ lc, const MontLimb *__restrict__ mont,
                                            uint32_t batch, uint32_t limbs, uint32_t blk) {
@@ -800,17 +915,17 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const TwM *__restr
   const uint64_t in_off = (uint64_t)b * a.in_sb + ((uint64_t)limb << LOGN) + blockStart;
   const uint64_t out_off = (uint64_t)b * a.out_sb + ((uint64_t)limb << LOGN) + blockStart;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
-    prod_body<LOGN, B, E, MODE, DO_FWD, DO_INV, decltype(FX)::value>(a, in_off, out_off, blockStart, t, c, mont + limb,
+    prod_body<LOGN, ST, B, E, MODE, DO_FWD, DO_INV, decltype(FX)::value>(a, in_off, out_off, blockStart, t, c, mont + limb,
                                                                      lds);
   });
 }
 
-template <int LOGN, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
+template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
 __global__ __launch_bounds__(1 << (B - E)) void k_prod(ProdArgs a, const TwM *__restrict__ tw,
                                                         const NttConst *__restrict__ lc,
                                                         const MontLimb *__restrict__ mont, uint32_t batch,
                                                         uint32_t limbs) {
-  prod_block<LOGN, B, E, MODE, DO_FWD, DO_INV>(a, tw, lc, mont, batch, limbs, blockIdx.x);
+  prod_block<LOGN, ST, B, E, MODE, DO_FWD, DO_INV>(a, tw, lc, mont, batch, limbs, blockIdx.x);
 }
 
 // Encrypted element-wise polynomial matrix product (section IV-E), NTT

@@ -26,7 +26,7 @@ void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, 
   const uint32_t L = t->limbs;
   const uint32_t units = batch * L;
   constexpr int NIN = ProdShape<MODE>::NIN, NOUT = ProdShape<MODE>::NOUT;
-  constexpr int B = PEC ? LOGN - PEC : LOGN;
+  constexpr int ST = LOGN - PEC, B = PEC ? block_words(ST, PE) : LOGN;
   const char *kname = MODE == PROD_MUL ? "k_prod_mul" : "k_prod_tensor";
   if constexpr (ALL_FLAGS) {
     if (!in_coeff && !out_coeff) {
@@ -53,7 +53,7 @@ void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, 
       pb.in_sb = NL;
       LaunchTimer lt_("k_cols_fwd", LOGN, st);
       hipLaunchKernelGGL((k_cols<LOGN, PEC, false>),
-                         dim3(NIN * units * ((1u << (LOGN - PEC)) / (256 * ColCpl<PEC>::value))), dim3(256), 0, st,
+                         dim3(NIN * units * cols_blocks_per_unit<LOGN, PEC>()), dim3(cols_lanes<PEC>()), 0, st,
                          ca, tw, lc, batch, L);
     }
   }
@@ -62,13 +62,13 @@ void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, 
     LaunchTimer lt_(kname, LOGN, st);
     if constexpr (ALL_FLAGS) {
       if (in_coeff && out_coeff)
-        hipLaunchKernelGGL((k_prod<LOGN, B, PE, MODE, true, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
+        hipLaunchKernelGGL((k_prod<LOGN, ST, B, PE, MODE, true, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
       else if (in_coeff)
-        hipLaunchKernelGGL((k_prod<LOGN, B, PE, MODE, true, false>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
+        hipLaunchKernelGGL((k_prod<LOGN, ST, B, PE, MODE, true, false>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
       else
-        hipLaunchKernelGGL((k_prod<LOGN, B, PE, MODE, false, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
+        hipLaunchKernelGGL((k_prod<LOGN, ST, B, PE, MODE, false, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
     } else {
-      hipLaunchKernelGGL((k_prod<LOGN, B, PE, MODE, true, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
+      hipLaunchKernelGGL((k_prod<LOGN, ST, B, PE, MODE, true, true>), g, blk, 0, st, pb, tw, lc, mont, batch, L);
     }
   }
   if constexpr (PEC > 0) {
@@ -78,7 +78,7 @@ void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, 
       ca.src_sb = ca.dst_sb = pa.out_sb;
       LaunchTimer lt_("k_cols_inv", LOGN, st);
       hipLaunchKernelGGL((k_cols<LOGN, PEC, true>),
-                         dim3(NOUT * units * ((1u << (LOGN - PEC)) / (256 * ColCpl<PEC>::value))), dim3(256), 0, st,
+                         dim3(NOUT * units * cols_blocks_per_unit<LOGN, PEC>()), dim3(cols_lanes<PEC>()), 0, st,
                          ca, tw, lc, batch, L);
     }
   }

@@ -13,24 +13,33 @@
 namespace hentt {
 
 struct RsLimb {   // per remaining limb i of a level
+  TwM w;          // qL^-1 mod q_i
   uint64_t mu;    // floor(2^64 / q_i)
   uint64_t nh;    // q_i - (h mod q_i)
-  uint64_t w, ws; // qL^-1 mod q_i and its Shoup quotient
+  uint64_t off;   // a multiple of q_i above any lazy forward output (rs_epilogue)
+  uint64_t pad;
 };
 
-// t_i from the last limb's canonical coefficient x (mod qL), in [0, 3 q_i):
-// s = (x + h) mod qL; s - floor-estimate(s / q_i) q_i is in [0, 2 q_i) (the
-// estimate floor(s mu / 2^64) is short by at most one); adding nh subtracts h.
-__device__ __forceinline__ uint64_t rs_prologue(uint64_t x, uint64_t qL, uint64_t h, const RsLimb &r, uint64_t q) {
+// t_i from the last limb's canonical coefficient x (mod qL): s = (x + h) mod qL,
+// then s + nh subtracts h.  The forward transform takes the 60-bit word as it
+// is: without corrections (34..55 bits) it adds at most 17 12q < 2^62.7, and the
+// corrected form takes any word.  Moduli of 33 or fewer bits, whose final
+// reduction is bounded by 2^(k + 21), reduce s first (the estimate floor(s mu /
+// 2^64) is short by at most one).
+__device__ __forceinline__ uint64_t rs_prologue(uint64_t x, uint64_t qL, uint64_t h, const RsLimb &r,
+                                                const NttConst &n) {
   uint64_t s = x + h;
   s = s >= qL ? s - qL : s;
-  return s - mulhi64(s, r.mu) * q + r.nh;
+  if (n.k < 34) s -= mulhi64(s, r.mu) * n.q;
+  return s + r.nh;
 }
 
-// (c - t) qL^-1 mod q for canonical c, t: canonical.
-__device__ __forceinline__ uint64_t rs_epilogue(uint64_t c, uint64_t t, const RsLimb &r, const NttConst &n) {
-  const uint64_t x = shoup(r.w, r.ws, c + n.q - t, n.nq);
-  return csubn(csubn(x, n.nq + n.nq), n.nq);
+// (c - t) qL^-1 mod q for canonical c and a lazy forward output t: canonical.
+// off - t >= 0 and c + off < 2^64: t stays below 2^60 + 2^62.7 up to 55 bits
+// (off: the multiple of q just below 2^63) and below 15q above (off = 15q).
+__device__ __forceinline__ uint64_t rs_epilogue(uint64_t c, uint64_t t, const RsLimb &r, const NttConst &n,
+                                                uint32_t four) {
+  return reduce_word(mul_tw(r.w, (c + r.off) - t, n, four), n);
 }
 
 struct RsArgs {
@@ -67,13 +76,13 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const Tw
     uint64_t v[1 << E];
     load_global<LOGN, E, F::LO, F::R>(v, a.tl + ((uint64_t)b << LOGN), RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
   #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, c.q);
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, c);
     fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, t, c);
-    reduce_out<E, FIX>(v, c);
+    const uint32_t four = opaque4();
     uint64_t cv[1 << E];
     load_global_m0<LOGN, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN), lds, tid);
   #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c);
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c, four);
     store_global_m0<LOGN, E>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), lds, tid);
   });
 }
@@ -85,28 +94,27 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const Tw
 // a multiple of 8); limb-major order re-read the whole batch's last limbs
 // from HBM or the MALL once per limb.
 template <int LOGN, int EC>
-__global__ __launch_bounds__(256) void k_rs_cols(RsArgs a, const TwM *__restrict__ tw,
-                                                 const NttConst *__restrict__ lc) {
-  constexpr uint32_t tiles = (1u << (LOGN - EC)) / 256;
-  constexpr int LO = LOGN - EC;
+__global__ __launch_bounds__(cols_lanes<EC>()) void k_rs_cols(RsArgs a, const TwM *__restrict__ tw,
+                                                              const NttConst *__restrict__ lc) {
+  __shared__ uint64_t lds[cols_lds<EC>()];
+  constexpr uint32_t tiles = fcols_blocks_per_unit<LOGN, EC>();
   const uint32_t u = blockIdx.x / tiles;
   const uint32_t b = u / a.L, i = u % a.L;
-  const uint32_t col = (blockIdx.x % tiles) * 256 + threadIdx.x;
+  const uint32_t col = fcol<EC>(blockIdx.x % tiles);
   const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
+  const uint64_t *src = a.tl + ((uint64_t)b << LOGN);
+  uint64_t *dst = a.out + (((uint64_t)b * a.L + i) << LOGN);
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
-    constexpr bool FIX = decltype(FX)::value;
-    uint64_t v[1 << EC];
-    load_global<LOGN, EC, LO, EC, true>(v, a.tl + ((uint64_t)b << LOGN), col);
-  #pragma unroll
-    for (int s = 0; s < (1 << EC); ++s) v[s] = rs_prologue(v[s], a.qL, a.h, r, c.q);
-    fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, tw + (size_t)i * 2 * (1u << LOGN), c);
-    store_global<LOGN, EC, LO, EC, true>(v, a.out + (((uint64_t)b * a.L + i) << LOGN), col);
+    fcol_pass<LOGN, EC, decltype(FX)::value>(
+        [&](uint32_t row) { return rs_prologue(gload<true>(src, (row << (LOGN - EC)) + col), a.qL, a.h, r, c); },
+        [&](uint32_t row, uint64_t v) { gstore<true>(dst, (row << (LOGN - EC)) + col, v); },
+        tw + (size_t)i * 2 * (1u << LOGN), c, lds);
   });
 }
 
 // Block pass (remaining stages) in place on out, then the epilogue.
-template <int LOGN, int B, int E>
+template <int LOGN, int ST, int B, int E>
 __global__ __launch_bounds__(1 << (B - E)) void k_rs_blocks(RsArgs a, const TwM *__restrict__ tw,
                                                              const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
@@ -118,17 +126,17 @@ __global__ __launch_bounds__(1 << (B - E)) void k_rs_blocks(RsArgs a, const TwM 
   const RsLimb r = a.rs[i];
   uint64_t *p = a.out + (((uint64_t)b * a.L + i) << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
-  using F = FwdFirst<B, E>;
+  using F = FwdFirst<ST, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
     load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
     fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, tw + (size_t)i * 2 * (1u << LOGN), c);
-    reduce_out<E, FIX>(v, c);
+    const uint32_t four = opaque4();
     uint64_t cv[1 << E];
     load_global_m0<B, E>(cv, a.c + (((uint64_t)b * (a.L + 1) + i) << LOGN) + blockStart, lds, tid);
   #pragma unroll
-    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c);
+    for (int s = 0; s < (1 << E); ++s) v[s] = rs_epilogue(cv[s], v[s], r, c, four);
     store_global_m0<B, E>(v, p, lds, tid);
   });
 }
@@ -144,10 +152,11 @@ __global__ __launch_bounds__(256) void k_rs_coeff(RsArgs a, const NttConst *__re
   const uint64_t *ci = a.c + (((uint64_t)b * (a.L + 1) + i) << log_n);
   const uint64_t *cl = a.c + (((uint64_t)b * (a.L + 1) + a.L) << log_n);
   uint64_t *o = a.out + (((uint64_t)b * a.L + i) << log_n);
+  const uint32_t four = opaque4();
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     const uint32_t k = base + threadIdx.x + 256u * s;
-    if (k < n) o[k] = rs_epilogue(ci[k], csubn(csubn(rs_prologue(cl[k], a.qL, a.h, r, c.q), c.nq + c.nq), c.nq), r, c);
+    if (k < n) o[k] = rs_epilogue(ci[k], est3(rs_prologue(cl[k], a.qL, a.h, r, c), c), r, c, four);
   }
 }
 

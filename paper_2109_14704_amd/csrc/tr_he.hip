@@ -28,8 +28,8 @@ int rs_constants(Storage *s, uint32_t level, const RsLimb **out) {
     const uint64_t q = s->moduli[i];
     host[i].mu = (uint64_t)(((host::u128)1 << 64) / q);
     host[i].nh = q - h % q;
-    host[i].w = host::pow(qL % q, q - 2, q);
-    host[i].ws = host::shoup_quot(host[i].w, q);
+    host[i].w = host::tw_m(host::pow(qL % q, q - 2, q), q);
+    host[i].off = q >> 55 ? 15 * q : (1ull << 63) / q * q;
   }
   RsLimb *d = nullptr;
   hipError_t e = hipMalloc(&d, L * sizeof(RsLimb));
@@ -43,12 +43,12 @@ int rs_constants(Storage *s, uint32_t level, const RsLimb **out) {
   return HENTT_OK;
 }
 
-// Stage split of the rescale's forward transforms: the plain transform's
-// default (whole up to 2^14; 5 column stages at 2^15 and 2^16, 4 at 2^17).
+// Stage split of the rescale's forward transforms: whole up to 2^13, the two-pass
+// split above (2^16, 64 polynomials of 24 limbs: 753 us with seven column stages,
+// 771 with six, 762 with five in registers).
 template <int LOGN> struct RsPlan {
-  static constexpr bool WHOLE = LOGN <= 14;
-  static constexpr int EC = LOGN == 15 ? 5 : LOGN == 16 ? 5 : LOGN == 17 ? 4 : (LOGN > 12 ? LOGN - 12 : 1);
-  static constexpr int B = LOGN - EC;
+  static constexpr bool WHOLE = LOGN <= 13;
+  static constexpr int EC = two_pass_cols(LOGN), E = 3, ST = LOGN - EC, B = block_words(ST, E);
 };
 
 template <int LOGN> void launch_rescale_ntt(const RsArgs &a, const Storage *s, hipStream_t st) {
@@ -60,11 +60,11 @@ template <int LOGN> void launch_rescale_ntt(const RsArgs &a, const Storage *s, h
   } else {
     {
       LaunchTimer lt_("k_rs_cols", LOGN, st);
-      hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC>), dim3(units * ((1u << (LOGN - P::EC)) / 256)), dim3(256), 0, st, a,
-                         s->d_twm, s->d_nc);
+      hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC>), dim3(units * fcols_blocks_per_unit<LOGN, P::EC>()),
+                         dim3(cols_lanes<P::EC>()), 0, st, a, s->d_twm, s->d_nc);
     }
     LaunchTimer lt_("k_rs_blocks", LOGN, st);
-    hipLaunchKernelGGL((k_rs_blocks<LOGN, P::B, 4>), dim3(units << (LOGN - P::B)), dim3(1 << (P::B - 4)), 0, st, a,
+    hipLaunchKernelGGL((k_rs_blocks<LOGN, P::ST, P::B, P::E>), dim3(units << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0, st, a,
                        s->d_twm, s->d_nc);
   }
 }
@@ -87,10 +87,8 @@ int ks_consts(Storage *s, uint32_t L1, const KsLimb **out) {
     const uint64_t q = s->moduli[t];
     kc[t].mu = (uint64_t)(((host::u128)1 << 64) / q);
     kc[t].qinv = 0 - host::inv64(q);
-    kc[t].r = (uint64_t)(((host::u128)1 << 64) % q);
-    kc[t].rs = host::shoup_quot(kc[t].r, q);
-    kc[t].pm = P % q;
-    kc[t].pms = host::shoup_quot(kc[t].pm, q);
+    kc[t].r = host::tw_m((uint64_t)(((host::u128)1 << 64) % q), q);
+    kc[t].pm = host::tw_m(P % q, q);
   }
   KsLimb *d = nullptr;
   hipError_t e = hipMalloc(&d, L1 * sizeof(KsLimb));
@@ -105,13 +103,13 @@ int ks_consts(Storage *s, uint32_t L1, const KsLimb **out) {
 }
 
 // Key-switch split: the digit loop holds two accumulator arrays, so whole
-// transforms only up to 2^12 (256 lanes); above, a column pass of EC stages
-// and blocks of at most 2^12.
+// transforms only up to 2^12 (256 lanes); above, the two-pass split (2^15, 32
+// ciphertexts, 8 primes: 546 us with six column stages, 549 with seven, 595 with
+// five in registers).
 template <int LOGN> struct KsPlan {
   static constexpr bool WHOLE = LOGN <= 12;
-  static constexpr int EC = LOGN <= 12 ? 0 : (LOGN == 15 || LOGN == 16 || LOGN == 17) ? 5 : LOGN - 12;
-  static constexpr int B = LOGN - EC;
-  static constexpr int E = 3;  // words per lane in the block kernel (3: occupancy over radix)
+  static constexpr int EC = two_pass_cols(LOGN);
+  static constexpr int E = 3, ST = LOGN - EC, B = block_words(ST, E);  // words per lane in the block kernel (3: occupancy over radix)
 };
 
 template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hipStream_t st) {
@@ -123,11 +121,11 @@ template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hip
   } else {
     {
       LaunchTimer lt_("k_ks_cols", LOGN, st);
-      hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * L1 * ((1u << (LOGN - P::EC)) / 256)),
-                         dim3(256), 0, st, a, s->d_twm, s->d_nc);
+      hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * L1 * fcols_blocks_per_unit<LOGN, P::EC>()),
+                         dim3(cols_lanes<P::EC>()), 0, st, a, s->d_twm, s->d_nc);
     }
     LaunchTimer lt_("k_ks_blocks", LOGN, st);
-    hipLaunchKernelGGL((k_ks_blocks<LOGN, P::B, P::E>), dim3((a.batch * L1) << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0,
+    hipLaunchKernelGGL((k_ks_blocks<LOGN, P::ST, P::B, P::E>), dim3((a.batch * L1) << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0,
                        st, a, s->d_twm, s->d_nc);
   }
 }

@@ -213,7 +213,7 @@ template <int E> void launch_staged15(const hentt_tables *t, uint64_t *x, uint32
   const uint32_t L = t->limbs, units = batch * L;
   const char *name = E == 2 ? "k_fwd_blocks_r4" : E == 3 ? "k_fwd_blocks_r8" : "k_fwd_blocks_r16";
   { LaunchTimer lt_("k_cols_fwd_r8", 15, st); hipLaunchKernelGGL((k_cols<15, 3, false>), dim3(units * ((1u << 12) / (256 * ColCpl<3>::value))), dim3(256), 0, st, col_args(x, (uint64_t)L << 15), t->s->d_twm, t->s->d_nc, batch, L); }
-  { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_twm, t->s->d_nc, batch, L); }
+  { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_twm, t->s->d_nc, batch, L); }
 }
 
 template <int S> void launch_simd15(const hentt_tables *t, uint64_t *x, uint64_t units, uint32_t batch,
@@ -248,7 +248,7 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
       launch_naive_stages(t, x, units, 0, 4, st);
       {
         LaunchTimer lt_("k_fwd_blocks_r2", 15, st);
-        hipLaunchKernelGGL((k_fwd_blocks<15, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x,
+        hipLaunchKernelGGL((k_fwd_blocks<15, 11, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x,
                            t->s->d_twm, t->s->d_nc, batch, L);
       }
       break;

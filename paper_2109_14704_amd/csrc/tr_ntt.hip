@@ -30,28 +30,28 @@ void launch_whole(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, 
 // Column pass of EC stages and block pass on 2^(LOGN - EC) words, 2^E per lane.
 template <int LOGN, int EC, int E>
 void launch_two_pass(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, hipStream_t st) {
-  constexpr int B = LOGN - EC;
+  constexpr int ST = LOGN - EC, B = block_words(ST, E);
   const TwM *tw = t->s->d_twm;
   const NttConst *lc = t->s->d_nc;
   const uint32_t L = t->limbs, units = batch * L;
-  const dim3 gcols(units * ((1u << (LOGN - EC)) / (256 * ColCpl<EC>::value)));
+  const dim3 gcols(units * cols_blocks_per_unit<LOGN, EC>());
   if (!inv) {
     {
       LaunchTimer lt_("k_cols_fwd", LOGN, st);
-      hipLaunchKernelGGL((k_cols<LOGN, EC, false>), gcols, dim3(256), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
+      hipLaunchKernelGGL((k_cols<LOGN, EC, false>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
                          batch, L);
     }
     LaunchTimer lt_("k_fwd_blocks", LOGN, st);
-    hipLaunchKernelGGL((k_fwd_blocks<LOGN, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
+    hipLaunchKernelGGL((k_fwd_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
                        batch, L);
   } else {
     {
       LaunchTimer lt_("k_inv_blocks", LOGN, st);
-      hipLaunchKernelGGL((k_inv_blocks<LOGN, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
+      hipLaunchKernelGGL((k_inv_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
                          batch, L);
     }
     LaunchTimer lt_("k_cols_inv", LOGN, st);
-    hipLaunchKernelGGL((k_cols<LOGN, EC, true>), gcols, dim3(256), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
+    hipLaunchKernelGGL((k_cols<LOGN, EC, true>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
                        batch, L);
   }
 }
@@ -63,19 +63,22 @@ struct TrCand {
   const char *desc;
 };
 
-// Candidate lists per log_n (candidate 0 = default).  Defaults (measured): a
-// whole transform up to 2^14; five column stages at 2^15 and 2^16, so that the
-// HBM-bound column pass takes stages off the ALU-bound block pass (10-19%
-// faster products than three or four stages); four at 2^17.
+// Candidate lists per log_n (candidate 0 = default).  Defaults, from a sweep of
+// whole transforms and of one to eight column stages at 1, 8 and 64 batch entries
+// of 16 limbs: whole up to 2^13 (55 us against 65 with a column pass, 64
+// entries); at 2^14 six column stages take 24 us against 28 whole at 8 entries
+// and the same 102 us at 64; above, six to eight stages through LDS and
+// one-wave blocks are 3-13% faster than five in registers (2^15: 205 against
+// 217 us, 2^17 at 8 entries: 117 against 130 us).
 #define W(n) {launch_whole<n>, 0, "one kernel per (batch entry, limb), block words per lane 2^4"}
 #define T(n, ec, e) {launch_two_pass<n, ec, e>, ec, "column stages " #ec ", block words per lane 2^" #e}
 const TrCand c6[] = {W(6)}, c7[] = {W(7)}, c8[] = {W(8)}, c9[] = {W(9)}, c10[] = {W(10)}, c11[] = {W(11)},
              c12[] = {W(12)};
-const TrCand c13[] = {W(13), T(13, 1, 4)};
-const TrCand c14[] = {T(14, 2, 3), W(14), T(14, 2, 4)};
-const TrCand c15[] = {T(15, 5, 4), T(15, 4, 4), T(15, 3, 4), T(15, 5, 3), T(15, 4, 3)};
-const TrCand c16[] = {T(16, 5, 3), T(16, 5, 4), T(16, 4, 4), T(16, 4, 3)};
-const TrCand c17[] = {T(17, 5, 3), T(17, 5, 4), T(17, 4, 4)};
+const TrCand c13[] = {W(13), T(13, 6, 3)};
+const TrCand c14[] = {T(14, 6, 3), W(14), T(14, 2, 3)};
+const TrCand c15[] = {T(15, 6, 3), T(15, 7, 3), T(15, 5, 3)};
+const TrCand c16[] = {T(16, 7, 3), T(16, 8, 3), T(16, 6, 4)};
+const TrCand c17[] = {T(17, 8, 3), T(17, 7, 3), T(17, 5, 3)};
 #undef W
 #undef T
 struct TrList {

@@ -17,8 +17,10 @@ namespace {
 // Column stages and log2 words per lane of the grouped product at N = 2^log_n
 // (the single-job tensor's default instance; 0 column stages = one kernel per
 // block of N).
-constexpr int grouped_pec(int log_n) { return log_n >= 14 ? (log_n == 14 ? 3 : 5) : log_n == 13 ? 1 : 0; }
-constexpr int grouped_pe(int log_n) { return log_n == 15 ? 2 : 3; }
+constexpr int grouped_pec(int log_n) {
+  return log_n <= 12 ? 0 : log_n == 13 ? 7 : log_n <= 15 ? 6 : log_n == 16 ? 7 : 8;
+}
+constexpr int grouped_pe(int log_n) { return log_n == 13 ? 2 : 3; }
 
 struct HostJob {
   const uint64_t *c, *d;
@@ -35,7 +37,7 @@ uint64_t ws_words(const HostJob &h) { return 4ull * h.batch * ((uint64_t)h.t->li
 template <int LOGN>
 int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff, uint64_t *ws, hipStream_t st) {
   constexpr int PEC = grouped_pec(LOGN), PE = grouped_pe(LOGN);
-  constexpr int B = PEC ? LOGN - PEC : LOGN;
+  constexpr int ST = LOGN - PEC, B = PEC ? block_words(ST, PE) : LOGN;
   GroupTable g{};
   g.n = n;
   uint64_t units = 0;
@@ -90,7 +92,7 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
         off += 4 * jobs[i].batch * nl(i);
       }
       LaunchTimer lt_("k_cols_fwd_g", LOGN, st);
-      hipLaunchKernelGGL((k_cols_g<LOGN, PEC, false, 4>), dim3(4 * u * cols_blocks_per_unit<LOGN, PEC>()), dim3(256),
+      hipLaunchKernelGGL((k_cols_g<LOGN, PEC, false, 4>), dim3(4 * u * cols_blocks_per_unit<LOGN, PEC>()), dim3(cols_lanes<PEC>()),
                          0, st, g);
     }
   }
@@ -116,11 +118,11 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
     const dim3 grid(u << (LOGN - B)), blk(1 << (B - PE));
     LaunchTimer lt_("k_prod_tensor_g", LOGN, st);
     if (in_coeff && out_coeff)
-      hipLaunchKernelGGL((k_prod_g<LOGN, B, PE, PROD_TENSOR, true, true>), grid, blk, 0, st, g);
+      hipLaunchKernelGGL((k_prod_g<LOGN, ST, B, PE, PROD_TENSOR, true, true>), grid, blk, 0, st, g);
     else if (in_coeff)
-      hipLaunchKernelGGL((k_prod_g<LOGN, B, PE, PROD_TENSOR, true, false>), grid, blk, 0, st, g);
+      hipLaunchKernelGGL((k_prod_g<LOGN, ST, B, PE, PROD_TENSOR, true, false>), grid, blk, 0, st, g);
     else
-      hipLaunchKernelGGL((k_prod_g<LOGN, B, PE, PROD_TENSOR, false, true>), grid, blk, 0, st, g);
+      hipLaunchKernelGGL((k_prod_g<LOGN, ST, B, PE, PROD_TENSOR, false, true>), grid, blk, 0, st, g);
   }
   if constexpr (PEC > 0) {
     if (out_coeff) {
@@ -131,7 +133,7 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
         a.src_sb = a.dst_sb = 3 * nl(i);
       }
       LaunchTimer lt_("k_cols_inv_g", LOGN, st);
-      hipLaunchKernelGGL((k_cols_g<LOGN, PEC, true, 3>), dim3(3 * u * cols_blocks_per_unit<LOGN, PEC>()), dim3(256),
+      hipLaunchKernelGGL((k_cols_g<LOGN, PEC, true, 3>), dim3(3 * u * cols_blocks_per_unit<LOGN, PEC>()), dim3(cols_lanes<PEC>()),
                          0, st, g);
     }
   }
