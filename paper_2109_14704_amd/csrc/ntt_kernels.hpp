@@ -424,17 +424,25 @@ template <int B, int E> struct InvLast {    // inverse: last round is the short 
 // Map blockIdx -> (polynomial, tile): limb-major, batch next, tile fastest, so
 // that concurrently running workgroups share one limb's twiddle table in L2.
 struct Unit {
-  uint32_t poly, limb, tile;
+  uint32_t poly, b, limb, tile;
 };
 __device__ __forceinline__ Unit unit_of(uint32_t bid, uint32_t tiles, uint32_t batch, uint32_t limbs) {
   Unit u;
   u.tile = bid % tiles;
   uint32_t r = bid / tiles;
   u.limb = r / batch;
-  uint32_t b = r % batch;
-  u.poly = b * limbs + u.limb;
+  u.b = r % batch;
+  u.poly = u.b * limbs + u.limb;
   return u;
 }
+
+// Words per lane (log2) of the kernels that hold a whole transform, product, or
+// rescale in one workgroup.  Measured over 2, 3 and 4 at 1 to 4096 units: more
+// lanes with fewer words win at every batch size, by latency at few units (the
+// product of one pair of 2^12: 13.0 us with 8 words, 16.2 with 16) and by
+// occupancy at many (2^12 forward, 4096 units: 68.6 against 72.9 us; 2^10
+// product, 512 units: 9.8 us with 4 words, 12.4 with 8, 14.9 with 16).
+constexpr int whole_e(int log_n) { return log_n <= 10 ? 2 : log_n <= 13 ? 3 : 4; }
 
 // ------------------------------------------------------------- kernels ----
 // Whole transform of one polynomial per workgroup (N = 2^LOGN fits in LDS).
@@ -459,24 +467,33 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_fwd_whole(uint64_t* __restr
   });
 }
 
+// Batch of an inverse transform: limb l of entry b is read at src + b src_sb +
+// l N and its first pass written to dst + b dst_sb + l N (equal for in place).
+struct InvIO {
+  const uint64_t* src;
+  uint64_t* dst;
+  uint64_t src_sb, dst_sb;  // words between consecutive batch entries
+};
+
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_inv_whole(uint64_t* __restrict__ x, const TwM* __restrict__ tw,
+__global__ __launch_bounds__(1 << (LOGN - E)) void k_inv_whole(InvIO io, const TwM* __restrict__ tw,
                                                                 const NttConst* __restrict__ lc, uint32_t batch,
                                                                 uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<LOGN>::value];
   const Unit un = unit_of(blockIdx.x, 1, batch, limbs);
   const NttConst c = lc[un.limb];
   const TwM* it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
-  uint64_t* p = x + (size_t)un.poly * (1u << LOGN);
+  const uint64_t* src = io.src + un.b * io.src_sb + ((uint64_t)un.limb << LOGN);
+  uint64_t* dst = io.dst + un.b * io.dst_sb + ((uint64_t)un.limb << LOGN);
   const uint32_t tid = threadIdx.x;
   using L = InvLast<LOGN, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
-    load_global_m0_fresh<LOGN, E>(v, p, lds, tid);
+    load_global_m0_fresh<LOGN, E>(v, src, lds, tid);
     inv_block_rounds<LOGN, LOGN, E, 0, (LOGN < E ? LOGN : E), FIX>(v, LOGN, lds, tid, 0, it, c);
     reduce_out<E, FIX>(v, c);
-    store_global<LOGN, E, L::LO, L::R>(v, p, RoundMap<LOGN, E, L::LO, L::R>::lane_part(tid));
+    store_global<LOGN, E, L::LO, L::R>(v, dst, RoundMap<LOGN, E, L::LO, L::R>::lane_part(tid));
   });
 }
 
@@ -723,7 +740,7 @@ __global__ __launch_bounds__(1 << (B - E)) void k_fwd_blocks(uint64_t *__restric
 
 // Block pass of the inverse transform: stages 0 .. ST-1; lazy output below 16q.
 template <int LOGN, int ST, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restrict__ x, const TwM *__restrict__ tw,
+__global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(InvIO io, const TwM *__restrict__ tw,
                                                               const NttConst *__restrict__ lc, uint32_t batch,
                                                               uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<B>::value];
@@ -732,15 +749,16 @@ __global__ __launch_bounds__(1 << (B - E)) void k_inv_blocks(uint64_t *__restric
   const NttConst c = lc[un.limb];
   const TwM *it = tw + ((size_t)un.limb * 2 + 1) * (1u << LOGN);
   const uint32_t blockStart = un.tile << B;
-  uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
+  const uint64_t *src = io.src + un.b * io.src_sb + ((uint64_t)un.limb << LOGN) + blockStart;
+  uint64_t *dst = io.dst + un.b * io.dst_sb + ((uint64_t)un.limb << LOGN) + blockStart;
   const uint32_t tid = threadIdx.x;
   using L = InvLast<ST, E>;
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t v[1 << E];
-    load_global_m0_fresh<B, E>(v, p, lds, tid);
+    load_global_m0_fresh<B, E>(v, src, lds, tid);
     inv_block_rounds<B, ST, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, it, c);
-    store_global<B, E, L::LO, L::R>(v, p, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
+    store_global<B, E, L::LO, L::R>(v, dst, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
   });
 }
 

@@ -145,6 +145,10 @@ inline ColArgs col_args(uint64_t *x, uint64_t sb) {
 // ------------------------------------------------------------ dispatch
 // tr_ntt.hip
 int run_transform(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st, bool inv);
+// inverse transform of `batch` entries read src_sb words apart, into the compact
+// [batch][limbs][N] dst (no overlap with src)
+int run_inverse_from(const hentt_tables *t, const uint64_t *src, uint64_t src_sb, uint64_t *dst, uint32_t batch,
+                     hipStream_t st);
 void stage_split(uint32_t log_n, uint32_t *transform_cols, uint32_t *product_cols);
 // tr_prod_mul.hip / tr_prod_tensor.hip: products, fused with the transforms
 // when in_coeff / out_coeff; the workspace comes from the pool.

@@ -56,7 +56,7 @@ template <int LOGN> void launch_rescale_ntt(const RsArgs &a, const Storage *s, h
   using P = RsPlan<LOGN>;
   if constexpr (P::WHOLE) {
     LaunchTimer lt_("k_rs_whole", LOGN, st);
-    hipLaunchKernelGGL((k_rs_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, a, s->d_twm, s->d_nc);
+    hipLaunchKernelGGL((k_rs_whole<LOGN, whole_e(LOGN)>), dim3(units), dim3(1 << (LOGN - whole_e(LOGN))), 0, st, a, s->d_twm, s->d_nc);
   } else {
     {
       LaunchTimer lt_("k_rs_cols", LOGN, st);
@@ -117,7 +117,7 @@ template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hip
   using P = KsPlan<LOGN>;
   if constexpr (P::WHOLE) {
     LaunchTimer lt_("k_ks_whole", LOGN, st);
-    hipLaunchKernelGGL((k_ks_whole<LOGN, 4>), dim3(a.batch * L1), dim3(1 << (LOGN - 4)), 0, st, a, s->d_twm, s->d_nc);
+    hipLaunchKernelGGL((k_ks_whole<LOGN, whole_e(LOGN)>), dim3(a.batch * L1), dim3(1 << (LOGN - whole_e(LOGN))), 0, st, a, s->d_twm, s->d_nc);
   } else {
     {
       LaunchTimer lt_("k_ks_cols", LOGN, st);
@@ -157,27 +157,25 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
     HIPCHK(hipGetLastError());
     return HENTT_OK;
   }
-  // the last limb of every batch entry, inverse-transformed modulo qL
+  // the last limb of every batch entry, inverse-transformed modulo qL, read
+  // where it lies (no copy first)
   void *tl = nullptr;
   rc = pool_get((size_t)batch * N * 8, st, &tl);
   if (rc) return rc;
-  hipError_t e = hipMemcpy2DAsync(tl, N * 8, c + (size_t)L * N, (size_t)level * N * 8, N * 8, batch,
-                                  hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess) {
-    Storage last;  // limb L's tables alone (a view: owns nothing)
-    last.log_n = ln;
-    last.limbs = 1;
-    last.d_twm = s->d_twm + (size_t)L * 2 * N;
-    last.d_nc = s->d_nc + L;
-    last.d_mont = s->d_mont + L;
-    last.device = s->device;
-    const hentt_tables lv{&last, 1};
-    rc = run_transform(&lv, (uint64_t *)tl, batch, st, true);
-    if (!rc) {
-      a.tl = (const uint64_t *)tl;
-      k_rs_table[ln - HENTT_LOG_N_MIN](a, s, st);
-      e = hipGetLastError();
-    }
+  Storage last;  // limb L's tables alone (a view: owns nothing)
+  last.log_n = ln;
+  last.limbs = 1;
+  last.d_twm = s->d_twm + (size_t)L * 2 * N;
+  last.d_nc = s->d_nc + L;
+  last.d_mont = s->d_mont + L;
+  last.device = s->device;
+  const hentt_tables lv{&last, 1};
+  rc = run_inverse_from(&lv, c + (size_t)L * N, (uint64_t)level * N, (uint64_t *)tl, batch, st);
+  hipError_t e = hipSuccess;
+  if (!rc) {
+    a.tl = (const uint64_t *)tl;
+    k_rs_table[ln - HENTT_LOG_N_MIN](a, s, st);
+    e = hipGetLastError();
   }
   pool_put(tl);
   if (rc) return rc;
@@ -201,10 +199,10 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
   if (rc) return rc;
   uint64_t *d = (uint64_t *)buf, *acc = d + batch * P, *e = acc + (size_t)batch * 2 * L1 * N;
   // digits: c2 in the coefficient domain, modulo its own primes
-  hipError_t he = hipMemcpy2DAsync(d, P * 8, c + 2 * P, 3 * P * 8, P * 8, batch, hipMemcpyDeviceToDevice, st);
   const hentt_tables lv{s, l};
-  if (he == hipSuccess) rc = run_transform(&lv, d, batch, st, true);
-  if (he == hipSuccess && !rc) {
+  rc = run_inverse_from(&lv, c + 2 * P, 3 * P, d, batch, st);
+  hipError_t he = hipSuccess;
+  if (!rc) {
     KsArgs a{};
     a.d = d;
     a.ksk = ksk;

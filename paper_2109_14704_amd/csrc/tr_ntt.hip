@@ -12,24 +12,25 @@
 namespace hentt_rt {
 namespace {
 
-// Whole transform of one (batch entry, limb) per workgroup, 16 words per lane.
+// Whole transform of one (batch entry, limb) per workgroup.
 template <int LOGN>
-void launch_whole(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, hipStream_t st) {
+void launch_whole(const hentt_tables *t, const InvIO &io, uint32_t batch, bool inv, hipStream_t st) {
+  constexpr int E = whole_e(LOGN);
   const uint32_t L = t->limbs, units = batch * L;
   if (!inv) {
     LaunchTimer lt_("k_fwd_whole", LOGN, st);
-    hipLaunchKernelGGL((k_fwd_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_twm, t->s->d_nc,
+    hipLaunchKernelGGL((k_fwd_whole<LOGN, E>), dim3(units), dim3(1 << (LOGN - E)), 0, st, io.dst, t->s->d_twm, t->s->d_nc,
                        batch, L);
   } else {
     LaunchTimer lt_("k_inv_whole", LOGN, st);
-    hipLaunchKernelGGL((k_inv_whole<LOGN, 4>), dim3(units), dim3(1 << (LOGN - 4)), 0, st, x, t->s->d_twm, t->s->d_nc,
+    hipLaunchKernelGGL((k_inv_whole<LOGN, E>), dim3(units), dim3(1 << (LOGN - E)), 0, st, io, t->s->d_twm, t->s->d_nc,
                        batch, L);
   }
 }
 
 // Column pass of EC stages and block pass on 2^(LOGN - EC) words, 2^E per lane.
 template <int LOGN, int EC, int E>
-void launch_two_pass(const hentt_tables *t, uint64_t *x, uint32_t batch, bool inv, hipStream_t st) {
+void launch_two_pass(const hentt_tables *t, const InvIO &io, uint32_t batch, bool inv, hipStream_t st) {
   constexpr int ST = LOGN - EC, B = block_words(ST, E);
   const TwM *tw = t->s->d_twm;
   const NttConst *lc = t->s->d_nc;
@@ -38,25 +39,25 @@ void launch_two_pass(const hentt_tables *t, uint64_t *x, uint32_t batch, bool in
   if (!inv) {
     {
       LaunchTimer lt_("k_cols_fwd", LOGN, st);
-      hipLaunchKernelGGL((k_cols<LOGN, EC, false>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
+      hipLaunchKernelGGL((k_cols<LOGN, EC, false>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(io.dst, io.dst_sb), tw, lc,
                          batch, L);
     }
     LaunchTimer lt_("k_fwd_blocks", LOGN, st);
-    hipLaunchKernelGGL((k_fwd_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
+    hipLaunchKernelGGL((k_fwd_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, io.dst, tw, lc,
                        batch, L);
   } else {
     {
       LaunchTimer lt_("k_inv_blocks", LOGN, st);
-      hipLaunchKernelGGL((k_inv_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, x, tw, lc,
+      hipLaunchKernelGGL((k_inv_blocks<LOGN, ST, B, E>), dim3(units << (LOGN - B)), dim3(1 << (B - E)), 0, st, io, tw, lc,
                          batch, L);
     }
     LaunchTimer lt_("k_cols_inv", LOGN, st);
-    hipLaunchKernelGGL((k_cols<LOGN, EC, true>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(x, (uint64_t)L << LOGN), tw, lc,
+    hipLaunchKernelGGL((k_cols<LOGN, EC, true>), gcols, dim3(cols_lanes<EC>()), 0, st, col_args(io.dst, io.dst_sb), tw, lc,
                        batch, L);
   }
 }
 
-typedef void (*tr_fn)(const hentt_tables *, uint64_t *, uint32_t, bool, hipStream_t);
+typedef void (*tr_fn)(const hentt_tables *, const InvIO &, uint32_t, bool, hipStream_t);
 struct TrCand {
   tr_fn fn;
   uint32_t ec;        // column stages (0: whole)
@@ -70,7 +71,7 @@ struct TrCand {
 // and the same 102 us at 64; above, six to eight stages through LDS and
 // one-wave blocks are 3-13% faster than five in registers (2^15: 205 against
 // 217 us, 2^17 at 8 entries: 117 against 130 us).
-#define W(n) {launch_whole<n>, 0, "one kernel per (batch entry, limb), block words per lane 2^4"}
+#define W(n) {launch_whole<n>, 0, "one kernel per (batch entry, limb)"}
 #define T(n, ec, e) {launch_two_pass<n, ec, e>, ec, "column stages " #ec ", block words per lane 2^" #e}
 const TrCand c6[] = {W(6)}, c7[] = {W(7)}, c8[] = {W(8)}, c9[] = {W(9)}, c10[] = {W(10)}, c11[] = {W(11)},
              c12[] = {W(12)};
@@ -106,14 +107,31 @@ const char *transform_describe(uint32_t log_n, uint32_t choice) { return k_tr[lo
 
 uint32_t transform_cols(uint32_t log_n, uint32_t choice) { return k_tr[log_n - HENTT_LOG_N_MIN].c[choice].ec; }
 
-int run_transform(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st, bool inv) {
+static int run(const hentt_tables *t, const InvIO &io, uint32_t batch, hipStream_t st, bool inv) {
   const uint32_t ln = t->s->log_n;
   const TrList &l = k_tr[ln - HENTT_LOG_N_MIN];
   uint32_t c = tune_choice(inv ? HENTT_OP_INV : HENTT_OP_FWD, ln, (uint64_t)batch * t->limbs);
   if (c >= l.n) c = 0;
-  l.c[c].fn(t, x, batch, inv, st);
+  l.c[c].fn(t, io, batch, inv, st);
   HIPCHK(hipGetLastError());
   return HENTT_OK;
+}
+
+int run_transform(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st, bool inv) {
+  const uint64_t sb = (uint64_t)t->limbs << t->s->log_n;
+  return run(t, InvIO{x, x, sb, sb}, batch, st, inv);
+}
+
+int run_inverse_from(const hentt_tables *t, const uint64_t *src, uint64_t src_sb, uint64_t *dst, uint32_t batch,
+                     hipStream_t st) {
+  const uint64_t sb = (uint64_t)t->limbs << t->s->log_n;
+  // the inverse kernels load 16 bytes per lane: words of a source that is only
+  // 8-byte aligned are copied first (dst is the library's own buffer)
+  if ((uintptr_t)src & 15) {
+    HIPCHK(hipMemcpy2DAsync(dst, sb * 8, src, src_sb * 8, sb * 8, batch, hipMemcpyDeviceToDevice, st));
+    return run(t, InvIO{dst, dst, sb, sb}, batch, st, true);
+  }
+  return run(t, InvIO{src, dst, src_sb, sb}, batch, st, true);
 }
 
 void stage_split(uint32_t log_n, uint32_t *transform_cols, uint32_t *product_cols) {

@@ -20,7 +20,7 @@ namespace {
 constexpr int grouped_pec(int log_n) {
   return log_n <= 12 ? 0 : log_n == 13 ? 7 : log_n <= 15 ? 6 : log_n == 16 ? 7 : 8;
 }
-constexpr int grouped_pe(int log_n) { return log_n == 13 ? 2 : 3; }
+constexpr int grouped_pe(int log_n) { return log_n <= 10 || log_n == 13 ? 2 : 3; }
 
 struct HostJob {
   const uint64_t *c, *d;

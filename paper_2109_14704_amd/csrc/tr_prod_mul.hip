@@ -7,9 +7,9 @@ namespace hentt_rt {
 namespace {
 #define D(n, pec, e) {launch_prod_cfg<n, PROD_MUL, pec, e, true>, pec, "column stages " #pec ", block words per lane 2^" #e}
 #define C(n, pec, e) {launch_prod_cfg<n, PROD_MUL, pec, e, false>, pec, "column stages " #pec ", block words per lane 2^" #e}
-const ProdCand m6[] = {D(6, 0, 4)}, m7[] = {D(7, 0, 4)}, m8[] = {D(8, 0, 4)}, m9[] = {D(9, 0, 4)},
-               m10[] = {D(10, 0, 4)}, m11[] = {D(11, 0, 4)}, m12[] = {D(12, 0, 4)};
-const ProdCand m13[] = {D(13, 6, 3), C(13, 0, 4)};
+const ProdCand m6[] = {D(6, 0, 2)}, m7[] = {D(7, 0, 2)}, m8[] = {D(8, 0, 2)}, m9[] = {D(9, 0, 2)},
+               m10[] = {D(10, 0, 2)}, m11[] = {D(11, 0, 3)}, m12[] = {D(12, 0, 3)};
+const ProdCand m13[] = {D(13, 6, 3), C(13, 0, 3)};
 const ProdCand m14[] = {D(14, 6, 3), C(14, 7, 2)};
 const ProdCand m15[] = {D(15, 6, 3), C(15, 7, 3)};
 const ProdCand m16[] = {D(16, 7, 3), C(16, 8, 3)};
