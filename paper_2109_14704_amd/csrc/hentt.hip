@@ -37,6 +37,7 @@ void release(Storage *s) {
     if (s->d_nc) (void)hipFree(s->d_nc);
     if (s->d_ncm) (void)hipFree(s->d_ncm);
     if (s->d_mont) (void)hipFree(s->d_mont);
+    if (s->d_mat) (void)hipFree(s->d_mat);
     for (auto &kv : s->rs) (void)hipFree(kv.second);
     for (auto &kv : s->ks) (void)hipFree(kv.second);
     (void)hipSetDevice(cur);
@@ -647,6 +648,7 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   std::vector<LimbConst> lc(limbs);
   std::vector<NttConst> nc(2 * (size_t)limbs);  // plain, then R-scaled N^-1
   std::vector<MontLimb> mont(limbs);
+  std::vector<MatLimb> mat(limbs);
   std::vector<uint64_t> pw(N), ipw(N);
   for (uint32_t l = 0; l < limbs; ++l) {
     Tw *f = &tw[(size_t)l * 2 * N];
@@ -655,6 +657,8 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
       return HENTT_EMODULUS;
     nc[l] = host::ntt_const(lc[l]);
     nc[limbs + l] = host::ntt_const(lcm);
+    const uint64_t q = moduli_host[l];
+    mat[l] = MatLimb{host::tw_m((1ull << 30) % q, q), host::tw_m((1ull << 62) % q, q)};
   }
   Storage *s = new (std::nothrow) Storage();
   if (!s) return HENTT_ENOMEM;
@@ -670,6 +674,9 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   if (e == hipSuccess) e = hipMalloc(&s->d_nc, limbs * sizeof(NttConst));
   if (e == hipSuccess) e = hipMalloc(&s->d_ncm, limbs * sizeof(NttConst));
   if (e == hipSuccess) e = hipMalloc(&s->d_mont, mont.size() * sizeof(MontLimb));
+  if (e == hipSuccess) e = hipMalloc(&s->d_mat, mat.size() * sizeof(MatLimb));
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(s->d_mat, mat.data(), mat.size() * sizeof(MatLimb), hipMemcpyHostToDevice, st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(s->d_lc, lc.data(), lc.size() * sizeof(LimbConst), hipMemcpyHostToDevice, st);
   if (e == hipSuccess)

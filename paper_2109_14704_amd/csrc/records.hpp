@@ -48,6 +48,10 @@ struct alignas(16) NttConst {
 };
 static_assert(sizeof(NttConst) == 96, "read field by field as 12 words (ld_nc)");
 
+// 2^30 mod q and 2^62 mod q as root powers: they bring a plain word into TwM form
+// (the matrix product).
+struct MatLimb { TwM w30, w62; };
+
 // A root power and its Shoup quotient (W, W' = floor(W 2^64 / q)), Algorithm 1.
 struct alignas(16) Tw { uint64_t w, ws; };
 

@@ -47,6 +47,7 @@ struct Storage {
   NttConst *d_nc = nullptr;    // [limbs]
   NttConst *d_ncm = nullptr;   // [limbs] the same with N^-1 R mod q for N^-1 (after Montgomery products)
   MontLimb *d_mont = nullptr;  // [limbs] Montgomery constants
+  MatLimb *d_mat = nullptr;    // [limbs] constants of the matrix product
   std::vector<uint64_t> moduli;
   int device = 0;
   std::mutex rs_mu;                  // rescale and key-switch constants per level, made on first use

@@ -3,6 +3,7 @@
 // element-wise polynomial matrix product.
 #include "host_tables.hpp"
 #include "keyswitch_kernels.hpp"
+#include "matmul_kernels.hpp"
 #include "rescale_kernels.hpp"
 #include "runtime.hpp"
 
@@ -228,16 +229,13 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
 // ------------------------------------------------------------ matMul
 int run_matmul(const hentt_tables *t, const uint64_t *A, const uint64_t *B, uint64_t *C, uint32_t m, uint32_t n,
                uint32_t k, hipStream_t st) {
-  const uint64_t N = 1ull << t->s->log_n;
-  const uint32_t tiles = (uint32_t)((N + 2047) / 2048);
-  const uint64_t grid = (uint64_t)m * n * t->limbs * tiles;
-  if (grid > 0x7fffffffu) return HENTT_EINVAL;
-  LaunchTimer lt_("k_ct_matmul", (int)t->s->log_n, st);
-  const bool full = N >= 2048, mont = k >= 3;  // Montgomery accumulation pays from k = 3 on
-  auto kern = full ? (mont ? k_ct_matmul<true, true> : k_ct_matmul<true, false>)
-                   : (mont ? k_ct_matmul<false, true> : k_ct_matmul<false, false>);
-  hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(256), 0, st, A, B, C, t->s->d_lc, t->s->d_mont, m, n, k,
-                     t->limbs, t->s->log_n, tiles);
+  const uint32_t ln = t->s->log_n, L = t->limbs;
+  const uint32_t tiles = ln > 8 ? 1u << (ln - 8) : 1u, runs = (n + CT_J - 1) / CT_J;
+  const uint64_t groups = (uint64_t)L * runs * tiles, grid = (groups + 7) / 8 * 8 * m;
+  if ((uint64_t)m * n * L * ((1ull << ln) + 2047 >> 11) > 0x7fffffffu || grid > 0x7fffffffu) return HENTT_EINVAL;
+  const MatmulArgs p{A, B, C, m, n, k, L, ln, tiles, runs, (uint32_t)groups};
+  LaunchTimer lt_("k_ct_matmul", (int)ln, st);
+  hipLaunchKernelGGL(k_ct_matmul, dim3((uint32_t)grid), dim3(256), 0, st, p, t->s->d_nc, t->s->d_mat);
   HIPCHK(hipGetLastError());
   return HENTT_OK;
 }
