@@ -32,7 +32,9 @@ struct KsArgs {
   uint64_t *acc;        // [batch][2][l + 1][N]
   const uint64_t *c;    // [batch][3][l][N] NTT domain: (c0, c1) enter as P c_s
   const KsLimb *kc;     // [l + 1]
+  uint64_t *part;       // [splits][batch][2][l + 1][N] partial sums when splits > 1
   uint32_t batch, l;
+  uint32_t splits;      // workgroups a block's digits are spread over
 };
 
 // A digit word x < q_j < 2^60 as an input of the transform modulo q_t: as it is
@@ -72,16 +74,16 @@ template <int B, int E>
 __device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb &kc, const NttConst &c,
                                           const uint64_t *cs, uint32_t lp) {
   const uint32_t four = opaque4();
+#pragma unroll
+  for (int s = 0; s < (1 << E); ++s) acc[s] = mul_tw(kc.r, acc[s], c, four);
   if (cs) {
     uint64_t cv[1 << E];
     load_global<B, E, 0, E>(cv, cs, lp);
 #pragma unroll
-    for (int s = 0; s < (1 << E); ++s)
-      acc[s] = reduce_word(mul_tw_add(kc.pm, cv[s], est3(mul_tw(kc.r, acc[s], c, four), c), c, four), c);
-  } else {
-#pragma unroll
-    for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(mul_tw(kc.r, acc[s], c, four), c);
+    for (int s = 0; s < (1 << E); ++s) acc[s] = mul_tw_add(kc.pm, cv[s], est3(acc[s], c), c, four);
   }
+#pragma unroll
+  for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(acc[s], c);
 }
 
 // c_s's words (s = 0, 1) at block offset `off` of target prime t for batch
@@ -156,16 +158,25 @@ __global__ __launch_bounds__(cols_lanes<EC>()) void k_ks_cols(KsArgs a, const Tw
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
-// rounds of every digit, accumulated with the key in registers.
+// rounds of every digit, accumulated with the key in registers (138 VGPRs, three
+// waves per SIMD; held to 128 or 96 the spills cost more than the wave gains:
+// 375, 400 and 418 us at 2^15, 8 primes, 32 entries; the key in root-power form,
+// a third fewer instructions for twice its bytes, 370 us with its conversion).
+// A small batch
+// has fewer blocks than the chip has places for waves; their digits are then
+// spread over `splits` workgroups, whose partial sums k_ks_sum adds up.
 template <int LOGN, int ST, int B, int E>
 __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM *__restrict__ tw,
                                                              const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
   const uint32_t L1 = a.l + 1;
-  const uint32_t blockStart = (blockIdx.x % tiles) << B;
-  const uint32_t r = blockIdx.x / tiles;
-  const uint32_t t = r / a.batch, b = r % a.batch;
+  const uint32_t tile = blockIdx.x % tiles, blockStart = tile << B;
+  uint32_t r = blockIdx.x / tiles;
+  const uint32_t b = r % a.batch;
+  r /= a.batch;
+  const uint32_t t = r % L1, part = r / L1;
+  const uint32_t j0 = part * a.l / a.splits, j1 = (part + 1) * a.l / a.splits;
   const NttConst c = lc[t];
   const KsLimb kc = a.kc[t];
   const TwM *tt = tw + (size_t)t * 2 * (1u << LOGN);
@@ -175,23 +186,49 @@ __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM 
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
     constexpr bool FIX = decltype(FX)::value;
     uint64_t acc0[1 << E], acc1[1 << E];
-  #pragma unroll
+#pragma unroll
     for (int s = 0; s < (1 << E); ++s) acc0[s] = acc1[s] = 0;
-  #pragma unroll 1
-    for (uint32_t j = 0; j < a.l; ++j) {
-      if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
+#pragma unroll 1
+    for (uint32_t j = j0; j < j1; ++j) {
+      if (j > j0) __syncthreads();  // the previous digit's last LDS reads are done
       uint64_t v[1 << E];
       load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
                                      RoundMap<B, E, F::LO, F::R>::lane_part(tid));
       fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, opaque(tt), c);
-      ks_mac<B, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B),
-                   M0::lane_part(tid), acc0, acc1, c, kc.qinv);
+      ks_mac<B, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B), M0::lane_part(tid),
+                   acc0, acc1, c, kc.qinv);
     }
-    ks_finish<B, E>(acc0, kc, c, ks_cs(a, b, 0, t, LOGN, blockStart), M0::lane_part(tid));
-    store_global_m0<B, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN) + blockStart, lds, tid);
-    ks_finish<B, E>(acc1, kc, c, ks_cs(a, b, 1, t, LOGN, blockStart), M0::lane_part(tid));
-    store_global_m0<B, E>(acc1, a.acc + (((uint64_t)(b * 2 + 1) * L1 + t) << LOGN) + blockStart, lds, tid);
+    const uint64_t o0 = (((uint64_t)b * 2 * L1 + t) << LOGN) + blockStart, o1 = o0 + ((uint64_t)L1 << LOGN);
+    uint64_t *out = a.acc;
+    if (a.splits > 1) {
+      out = a.part + ((uint64_t)part * a.batch * 2 * L1 << LOGN);
+    } else {
+      ks_finish<B, E>(acc0, kc, c, ks_cs(a, b, 0, t, LOGN, blockStart), M0::lane_part(tid));
+      ks_finish<B, E>(acc1, kc, c, ks_cs(a, b, 1, t, LOGN, blockStart), M0::lane_part(tid));
+    }
+    store_global_m0<B, E>(acc0, out + o0, lds, tid);
+    store_global_m0<B, E>(acc1, out + o1, lds, tid);
   });
+}
+
+// Adds up the partial sums (Montgomery, below 2q each) of k_ks_blocks and
+// finishes them as it does.  One lane per word of [batch][2][l + 1][N].
+template <int LOGN> __global__ __launch_bounds__(256) void k_ks_sum(KsArgs a, const NttConst *__restrict__ lc) {
+  constexpr uint32_t tiles = 1u << (LOGN - 8);
+  const uint32_t L1 = a.l + 1, row = blockIdx.x / tiles;  // (b, s, t), t fastest
+  const uint32_t t = row % L1, s = (row / L1) & 1, b = row / (2 * L1);
+  const uint32_t i = (blockIdx.x % tiles) * 256 + threadIdx.x;
+  const uint64_t words = (uint64_t)a.batch * 2 * L1 << LOGN, at = ((uint64_t)row << LOGN) + i;
+  const NttConst c = lc[t];
+  const KsLimb kc = a.kc[t];
+  const uint64_t nq2 = c.nq + c.nq;
+  const uint32_t four = opaque4();
+  uint64_t x = a.part[at];
+  for (uint32_t k = 1; k < a.splits; ++k) x = csubn(x + a.part[k * words + at], nq2);
+  x = mul_tw(kc.r, x, c, four);
+  const uint64_t *cs = ks_cs(a, b, s, t, LOGN, i);
+  if (cs) x = mul_tw_add(kc.pm, *cs, est3(x, c), c, four);
+  a.acc[at] = reduce_word(x, c);
 }
 
 }  // namespace hentt

@@ -1,6 +1,8 @@
 // Dispatch of the homomorphic routines built on the transforms: rescale (RS),
 // relinearization with the RNS digit key switch (Relin) and the encrypted
 // element-wise polynomial matrix product.
+#include <algorithm>
+
 #include "host_tables.hpp"
 #include "keyswitch_kernels.hpp"
 #include "matmul_kernels.hpp"
@@ -113,6 +115,11 @@ template <int LOGN> struct KsPlan {
   static constexpr int E = 3, ST = LOGN - EC, B = block_words(ST, E);  // words per lane in the block kernel (3: occupancy over radix)
 };
 
+// Blocks of a small batch spread their digits over workgroups up to this many
+// waves in all (N = 2^15: 77 -> 69 us at 8 primes and one entry, 95 -> 90 at two
+// entries, no difference at three; 86 -> 68 us at 2^14, 12 primes, one entry).
+constexpr uint32_t kKsWaves = 2304;
+
 template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hipStream_t st) {
   const uint32_t L1 = a.l + 1;
   using P = KsPlan<LOGN>;
@@ -125,9 +132,15 @@ template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hip
       hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * L1 * fcols_blocks_per_unit<LOGN, P::EC>()),
                          dim3(cols_lanes<P::EC>()), 0, st, a, s->d_twm, s->d_nc);
     }
-    LaunchTimer lt_("k_ks_blocks", LOGN, st);
-    hipLaunchKernelGGL((k_ks_blocks<LOGN, P::ST, P::B, P::E>), dim3((a.batch * L1) << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0,
-                       st, a, s->d_twm, s->d_nc);
+    {
+      LaunchTimer lt_("k_ks_blocks", LOGN, st);
+      hipLaunchKernelGGL((k_ks_blocks<LOGN, P::ST, P::B, P::E>), dim3((a.splits * a.batch * L1) << (LOGN - P::B)),
+                         dim3(1 << (P::B - P::E)), 0, st, a, s->d_twm, s->d_nc);
+    }
+    if (a.splits > 1) {
+      LaunchTimer lt_("k_ks_sum", LOGN, st);
+      hipLaunchKernelGGL((k_ks_sum<LOGN>), dim3(a.batch * 2 * L1 << (LOGN - 8)), dim3(256), 0, st, a, s->d_nc);
+    }
   }
 }
 typedef void (*ks_fn)(const KsArgs &, const Storage *, hipStream_t);
@@ -195,10 +208,16 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
   const bool two_pass = ln > 12;  // KsPlan<>::WHOLE
   const size_t d_bytes = (size_t)batch * P * 8, acc_bytes = (size_t)batch * 2 * L1 * N * 8;
   const size_t e_bytes = two_pass ? (size_t)batch * l * L1 * N * 8 : 0;
+  const uint64_t waves = (uint64_t)batch * L1 * N >> 9;
+  uint32_t splits = two_pass ? (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(l / 2, kKsWaves / waves)) : 1;
   void *buf = nullptr;
-  rc = pool_get(d_bytes + acc_bytes + e_bytes, st, &buf);
+  rc = pool_get(d_bytes + acc_bytes + e_bytes + (splits > 1 ? splits * acc_bytes : 0), st, &buf);
+  if (rc == HENTT_ENOMEM && splits > 1) {  // only faster: do without the partial sums
+    splits = 1;
+    rc = pool_get(d_bytes + acc_bytes + e_bytes, st, &buf);
+  }
   if (rc) return rc;
-  uint64_t *d = (uint64_t *)buf, *acc = d + batch * P, *e = acc + (size_t)batch * 2 * L1 * N;
+  uint64_t *d = (uint64_t *)buf, *acc = d + batch * P, *e = acc + (size_t)batch * 2 * L1 * N, *part = e + e_bytes / 8;
   // digits: c2 in the coefficient domain, modulo its own primes
   const hentt_tables lv{s, l};
   rc = run_inverse_from(&lv, c + 2 * P, 3 * P, d, batch, st);
@@ -211,6 +230,8 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
     a.acc = acc;
     a.c = c;
     a.kc = kc;
+    a.part = splits > 1 ? part : nullptr;
+    a.splits = splits;
     a.batch = batch;
     a.l = l;
     k_ks_table[ln - HENTT_LOG_N_MIN](a, s, st);

@@ -93,3 +93,19 @@ def test_relin(gpu, log_n, bits, offset):
     ksk = words(rng, (l, 2, l + 1, n), mods)
     got = H.relin(H.Tables(log_n, mods), dev(c, gpu, offset), dev(ksk, gpu, offset))
     assert np.array_equal(host(got), oracle.relin(c, ksk, mods))
+
+
+@pytest.mark.parametrize("l,batch,log_n", [(4, 1, 13), (5, 2, 13), (9, 1, 13), (8, 1, 14)])
+def test_relin_digits_spread_over_workgroups(gpu, l, batch, log_n):
+    """Small batches of four and more digits: partial sums of 2 to 4 workgroups
+    per block, even and uneven digit runs, moduli of 33 to 60 bits."""
+    import paper_2109_14704_amd as H
+    print("case relin digit splits l=%d batch=%d log_n=%d" % (l, batch, log_n), flush=True)
+    bits = [60, 55, 56, 33, 34, 50, 58, 47, 54, 59][:l + 1]
+    mods = [primes(b, log_n)[0] for b in bits]
+    rng = np.random.default_rng(77 * l + batch)
+    n = 1 << log_n
+    c = words(rng, (batch, 3, l, n), mods[:l])
+    ksk = words(rng, (l, 2, l + 1, n), mods)
+    got = H.relin(H.Tables(log_n, mods), dev(c, gpu), dev(ksk, gpu))
+    assert np.array_equal(host(got), oracle.relin(c, ksk, mods))
