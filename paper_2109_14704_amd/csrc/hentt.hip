@@ -646,17 +646,17 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   const uint32_t N = 1u << log_n;
   std::vector<Tw> tw((size_t)limbs * 2 * N);
   std::vector<LimbConst> lc(limbs);
-  std::vector<NttConst> nc(2 * (size_t)limbs);  // plain, then R-scaled N^-1
+  std::vector<NttConst> nc(2 * (size_t)limbs);  // plain, then for the inverse after products
   std::vector<MontLimb> mont(limbs);
   std::vector<MatLimb> mat(limbs);
   std::vector<uint64_t> pw(N), ipw(N);
   for (uint32_t l = 0; l < limbs; ++l) {
     Tw *f = &tw[(size_t)l * 2 * N];
-    LimbConst lcm;
+    LimbConst lcm;  // N^-1 R forms that no kernel reads
     if (!host::make_limb(moduli_host[l], (int)log_n, f, f + N, lc[l], lcm, mont[l], pw.data(), ipw.data()))
       return HENTT_EMODULUS;
     nc[l] = host::ntt_const(lc[l]);
-    nc[limbs + l] = host::ntt_const(lcm);
+    nc[limbs + l] = host::ntt_const_after_products(lc[l]);
     const uint64_t q = moduli_host[l];
     mat[l] = MatLimb{host::tw_m((1ull << 30) % q, q), host::tw_m((1ull << 62) % q, q)};
   }

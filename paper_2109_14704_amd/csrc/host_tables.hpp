@@ -173,5 +173,16 @@ inline NttConst ntt_const(const LimbConst &c) {
   return n;
 }
 
+// The constants of an inverse transform that follows products of variables: N^-1
+// scaled by the factor they are short of, 2^60 for the moduli of 34 to 55 bits
+// (mont30_mul), R = 2^64 for the others (mont_mul).
+inline NttConst ntt_const_after_products(const LimbConst &c) {
+  const uint64_t q = c.m.q, f = (uint64_t)(((u128)1 << (c.k >= 34 && c.k <= 55 ? 60 : 64)) % q);
+  NttConst n = ntt_const(c);
+  n.ninv = tw_m(mul(c.ninv, f, q), q);
+  n.ninvw = tw_m(mul(c.ninvw, f, q), q);
+  return n;
+}
+
 }  // namespace host
 }  // namespace hentt

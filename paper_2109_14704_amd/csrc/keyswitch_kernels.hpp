@@ -7,9 +7,9 @@
 // with the key-switching key are accumulated in registers over the digits
 // (fused into the transform's last stage):
 //   acc_s[t] = sum_j NTT_t(d_j mod q_t) . ksk[j][s][t]   (s = 0, 1).
-// The products are Montgomery products (R = 2^64) on the lazy transform
-// outputs, summed lazily below 2 q_t; one Shoup product by R mod q_t per
-// output word removes the common factor R^-1 before the store.  The same
+// The products are Montgomery products (off by 2^-60, see ks_mac) on the
+// lazy transform outputs, summed lazily; one product by the inverse factor per
+// output word removes it before the store.  The same
 // epilogue adds P c_s (s = 0, 1) for t < l: round((x + P c_s) / P) =
 // c_s + round(x / P) exactly (x and x + P c_s agree mod P), so the rescale
 // of rescale_kernels.hpp that divides by P with rounding also completes
@@ -20,9 +20,8 @@
 namespace hentt {
 
 struct KsLimb {     // per target prime q_t of one level
-  TwM r, pm;        // 2^64 mod q_t, P mod q_t (t < l)
+  TwM r, pm;        // 2^60 mod q_t, P mod q_t (t < l)
   uint64_t mu;      // floor(2^64 / q_t)
-  uint64_t qinv;    // -q_t^-1 mod 2^64
 };
 
 struct KsArgs {
@@ -46,29 +45,47 @@ __device__ __forceinline__ uint64_t ks_lift(uint64_t x, uint64_t mu, const NttCo
   return x;
 }
 
-// acc0 += v . key0 R^-1, acc1 += v . key1 R^-1 (mod q, accumulators kept
-// in [0, 2q)) for the words of v (lazy forward outputs, any 64-bit words: the
-// key is canonical, so v . key < q R) held in the (0, E) map of a 2^B block; key0 at k,
-// key1 one prime-row further (`row` blocks of 2^B words).  The two products
-// run one after the other (scheduling barrier) so that only one key array is
-// live.
-template <int B, int E>
-__device__ __forceinline__ void ks_mac(const uint64_t (&v)[1 << E], const uint64_t *k, uint32_t row, uint32_t lp,
+// acc0 += v . key0 2^-60, acc1 += v . key1 2^-60 (mod q, mont30_mul_add) for the
+// words of v (lazy forward outputs) held in the (0, E) map of a 2^B block; key0 at
+// k, key1 one prime-row further (`row` blocks of 2^B words); j counts the digits.
+// The accumulators by modulus size:
+//   34..55 bits  less than 5q a digit, cut back (est3) every 32 digits: below
+//                3q + 160q < 2^63;
+//   56..60 bits  cut back ahead of every digit: below 3q + 7q (the key, canonical,
+//                is the factor below q);
+//   33 or fewer  never cut back: below 5q 2^12, for the most limbs there can be.
+// The two products run one after the other (scheduling barrier) so that only one
+// key array is live.
+template <int B, int E, bool FIX>
+__device__ __forceinline__ void ks_mac(uint64_t (&v)[1 << E], const uint64_t *k, uint32_t row, uint32_t lp,
                                        uint64_t (&acc0)[1 << E], uint64_t (&acc1)[1 << E], const NttConst &c,
-                                       uint64_t qinv) {
-  const uint64_t nq2 = c.nq + c.nq;
+                                       uint32_t j) {
   uint64_t kv[1 << E];
   load_global<B, E, 0, E>(kv, k, lp);
+  const uint32_t four = opaque4();
+  if (FIX || (j & 31) == 31) {
 #pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc0[s] = csubn(acc0[s] + mont_mul(v[s], kv[s], c.q, qinv), nq2);
+    for (int s = 0; s < (1 << E); ++s) {
+      acc0[s] = est3(acc0[s], c);
+      acc1[s] = est3(acc1[s], c);
+    }
+  }
+  reduce_for_mont<E, FIX>(v, c);
+#pragma unroll
+  for (int s = 0; s < (1 << E); ++s) {
+    if constexpr (FIX) acc0[s] = mont30_mul_add(split30(kv[s]), v[s], acc0[s], c, four);
+    else acc0[s] = mont30_mul_add(split30(v[s]), kv[s], acc0[s], c, four);
+  }
   __builtin_amdgcn_sched_barrier(0);
   load_global<B, E, 0, E>(kv, k + ((uint64_t)row << B), lp);
 #pragma unroll
-  for (int s = 0; s < (1 << E); ++s) acc1[s] = csubn(acc1[s] + mont_mul(v[s], kv[s], c.q, qinv), nq2);
+  for (int s = 0; s < (1 << E); ++s) {
+    if constexpr (FIX) acc1[s] = mont30_mul_add(split30(kv[s]), v[s], acc1[s], c, four);
+    else acc1[s] = mont30_mul_add(split30(v[s]), kv[s], acc1[s], c, four);
+  }
 }
 
-// Accumulators (sums of Montgomery products, [0, 2q)) to canonical values:
-// times R mod q, plus P c_s when cs (c_s's words of the block, in the (0, E)
+// Accumulators (sums of Montgomery products) to canonical values: times 2^60, plus P c_s when cs (c_s's words of the block, in the (0, E)
 // map) is given; est3 keeps the sum of the two products (12q each) below 16q.
 template <int B, int E>
 __device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb &kc, const NttConst &c,
@@ -123,8 +140,8 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw
       // an opaque copy of the table pointer per digit: the twiddles (the same
       // for every digit) are re-read from cache instead of held in VGPRs
       fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, opaque(tt), c);
-      ks_mac<LOGN, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN), L1, M0::lane_part(tid), acc0, acc1, c,
-                      kc.qinv);
+      ks_mac<LOGN, E, FIX>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN), L1, M0::lane_part(tid), acc0, acc1, c,
+                           j);
     }
     ks_finish<LOGN, E>(acc0, kc, c, ks_cs(a, b, 0, t, LOGN, 0), M0::lane_part(tid));
     store_global_m0<LOGN, E>(acc0, a.acc + (((uint64_t)b * 2 * L1 + t) << LOGN), lds, tid);
@@ -158,15 +175,16 @@ __global__ __launch_bounds__(cols_lanes<EC>()) void k_ks_cols(KsArgs a, const Tw
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
-// rounds of every digit, accumulated with the key in registers (138 VGPRs, three
-// waves per SIMD; held to 128 or 96 the spills cost more than the wave gains:
-// 375, 400 and 418 us at 2^15, 8 primes, 32 entries; the key in root-power form,
-// a third fewer instructions for twice its bytes, 370 us with its conversion).
-// A small batch
+// rounds of every digit, accumulated with the key in registers.  VALU-bound (a
+// fifth of its HBM time at the copy rate).  N = 2^15, 8 primes, 32 entries, the
+// whole relinearization: 720 us with Montgomery products of 64-bit words, 690 with
+// mont30_mul at the 134 VGPRs it takes (three waves per SIMD), 678 held to 128
+// (four waves, six words spilled).  The key in root-power form, a third fewer
+// instructions than the 64-bit products for twice its bytes, gave 716.  A small batch
 // has fewer blocks than the chip has places for waves; their digits are then
 // spread over `splits` workgroups, whose partial sums k_ks_sum adds up.
 template <int LOGN, int ST, int B, int E>
-__global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM *__restrict__ tw,
+__global__ __launch_bounds__(1 << (B - E), 4) void k_ks_blocks(KsArgs a, const TwM *__restrict__ tw,
                                                              const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[LdsSize<B>::value];
   constexpr uint32_t tiles = 1u << (LOGN - B);
@@ -195,8 +213,8 @@ __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM 
       load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
                                      RoundMap<B, E, F::LO, F::R>::lane_part(tid));
       fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, opaque(tt), c);
-      ks_mac<B, E>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B), M0::lane_part(tid),
-                   acc0, acc1, c, kc.qinv);
+      ks_mac<B, E, FIX>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B), M0::lane_part(tid),
+                   acc0, acc1, c, j - j0);
     }
     const uint64_t o0 = (((uint64_t)b * 2 * L1 + t) << LOGN) + blockStart, o1 = o0 + ((uint64_t)L1 << LOGN);
     uint64_t *out = a.acc;
@@ -211,7 +229,7 @@ __global__ __launch_bounds__(1 << (B - E)) void k_ks_blocks(KsArgs a, const TwM 
   });
 }
 
-// Adds up the partial sums (Montgomery, below 2q each) of k_ks_blocks and
+// Adds up the partial sums (ks_mac's accumulators) of k_ks_blocks and
 // finishes them as it does.  One lane per word of [batch][2][l + 1][N].
 template <int LOGN> __global__ __launch_bounds__(256) void k_ks_sum(KsArgs a, const NttConst *__restrict__ lc) {
   constexpr uint32_t tiles = 1u << (LOGN - 8);
@@ -221,10 +239,9 @@ template <int LOGN> __global__ __launch_bounds__(256) void k_ks_sum(KsArgs a, co
   const uint64_t words = (uint64_t)a.batch * 2 * L1 << LOGN, at = ((uint64_t)row << LOGN) + i;
   const NttConst c = lc[t];
   const KsLimb kc = a.kc[t];
-  const uint64_t nq2 = c.nq + c.nq;
   const uint32_t four = opaque4();
-  uint64_t x = a.part[at];
-  for (uint32_t k = 1; k < a.splits; ++k) x = csubn(x + a.part[k * words + at], nq2);
+  uint64_t x = est3(a.part[at], c);
+  for (uint32_t k = 1; k < a.splits; ++k) x = est3(x + a.part[k * words + at], c);
   x = mul_tw(kc.r, x, c, four);
   const uint64_t *cs = ks_cs(a, b, s, t, LOGN, i);
   if (cs) x = mul_tw_add(kc.pm, *cs, est3(x, c), c, four);

@@ -297,4 +297,49 @@ __device__ __forceinline__ uint64_t mont_mad(uint64_t a, uint64_t b, uint64_t c,
   return redc(h1 + h2 + (l < l1 ? 1 : 0), l, q, qinv);
 }
 
+// Products of two variables, two of mul_tw's Montgomery steps, so that they come
+// out off by 2^-60 (cancelled elsewhere: folded into the N^-1 scaling of the
+// inverse transform that follows, or into the key switch's last product).  With a
+// split at bit 30 (a below 2^62) and b1 four times the high word of b (below 2^62
+// too), a b = a b0 + 2^30 a b1: the first step divides a b0 by 2^30, the second
+// its result U plus a b1.  U enters the second step's p0 whole, so
+// U + a0 b1 + m qlo has to stay below 2^64, with U < a b0 / 2^30 + 4q, m qlo < 2^62
+// and results below a b1 / 2^30 + 4.1q:
+//   34..55 bits  a, b < 3q: U < 16q < 2^59 (the sum of two products 28q), results
+//                below 5q (the sum 6q);
+//   56..60 bits  a < q, b < 2q: U < 8q < 2^63, a0 b1 < 2^61, results below 7q;
+//   33 or fewer  lazy words (below 207q < 2^41): results below 5q.
+//
+// 12 instructions a product and 16 the sum of two, with the splits shared between
+// the products of a ciphertext tensor 46 in all; Montgomery products of whole
+// 64-bit words (R = 2^64) took 117 as compiled, 51 of them moves that zero-extend
+// 32-bit halves.
+struct Split30 { uint32_t lo, hi; };
+__device__ __forceinline__ Split30 split30(uint64_t a) {
+  return Split30{lo32(a) & ((1u << 30) - 1), (uint32_t)(a >> 30)};
+}
+__device__ __forceinline__ uint64_t redc30(uint64_t p0, uint64_t p1, const NttConst &c, uint32_t four) {
+  const uint32_t m = lo32(p0) * c.qi;
+  p0 = mad32(m, c.qlo, p0);
+  p1 = mad32(m, c.qhi, p1);
+  return mad32(hi32(p0), four, p1);
+}
+// x + a b 2^-60 mod q
+__device__ __forceinline__ uint64_t mont30_mul_add(Split30 a, uint64_t b, uint64_t x, const NttConst &c,
+                                                   uint32_t four) {
+  const uint32_t b0 = lo32(b), b1 = hi32(b) << 2;
+  const uint64_t u = redc30(mad32(a.lo, b0, 0), mad32(a.hi, b0, 0), c, four);
+  return redc30(mad32(a.lo, b1, u), mad32(a.hi, b1, x), c, four);
+}
+__device__ __forceinline__ uint64_t mont30_mul(Split30 a, uint64_t b, const NttConst &c, uint32_t four) {
+  return mont30_mul_add(a, b, 0, c, four);
+}
+// (a b + d e) 2^-60 mod q
+__device__ __forceinline__ uint64_t mont30_mad(Split30 a, uint64_t b, Split30 d, uint64_t e, const NttConst &c,
+                                               uint32_t four) {
+  const uint32_t b0 = lo32(b), b1 = hi32(b) << 2, e0 = lo32(e), e1 = hi32(e) << 2;
+  const uint64_t u = redc30(mad32(d.lo, e0, mad32(a.lo, b0, 0)), mad32(d.hi, e0, mad32(a.hi, b0, 0)), c, four);
+  return redc30(mad32(d.lo, e1, mad32(a.lo, b1, u)), mad32(d.hi, e1, mad32(a.hi, b1, 0)), c, four);
+}
+
 }  // namespace hentt

@@ -164,9 +164,9 @@ __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, 
 //                stay below 512q; at its end the words that could exceed
 //                2^LBOUT q are corrected (the few with a long run of X sides
 //                behind them);
-//   56..60 bits  words below 8q on entry: the product corrected after every
+//   56..60 bits  words below 4q on entry: the product corrected after every
 //                stage, X' after every second one and after the round's last
-//                (3 + 3 < 8, 6 + 6 < 16);
+//                (4 + 4 <= 8, 8 + 8 <= 16);
 //   33 or fewer  none in the whole transform: at stage v words are below
 //                16q 2^v < 2^54 (est3 leaves them as they are).
 // `off`, the multiple of q that keeps X - Y positive, follows the same bounds.
@@ -809,37 +809,53 @@ __device__ __forceinline__ void products(uint64_t (&X)[ProdShape<MODE>::NIN][1 <
   }
 }
 
-// The products ahead of an inverse transform, in Montgomery form: every
-// output is off by R^-1 (R = 2^64), a constant factor the inverse transform
-// removes with its N^-1 scaling, taken from the folded constants N^-1 R.
-// Inputs: MUL factors below 4q (a b < 16 q^2 < q R as q < 2^60); TENSOR
-// factors below 2q (c0 d1 + c1 d0 < 8 q^2 < q R).  Outputs in [0, 2q), a valid
-// inverse-transform input.
-template <int MODE, int E>
+// The products ahead of an inverse transform: every output is off by a constant
+// factor, which the inverse transform removes with its N^-1 scaling, taken from
+// the folded constants.
+//   34..55 bits (not FIX)  mont30_mul, off by 2^-60; factors below 3q, outputs
+//                below 6q.  N = 2^16, 24 primes, 32 ciphertext pairs: 960 us of
+//                product kernel, 1000 with the form below.
+//   others       Montgomery products with R = 2^64; MUL factors below 4q
+//                (a b < 16 q^2 < q R as q < 2^60), TENSOR factors below 2q
+//                (c0 d1 + c1 d0 < 8 q^2 < q R), outputs in [0, 2q).  By
+//                mont30_mul, with one factor cut below q and the result below
+//                3q, the registers grow: 600 us for 594 (2^15, 16 primes of 50 to
+//                60 bits, 128 products) and, the tensor at three waves for four
+//                or spilling, 1005 us for 960 even where no such modulus occurs.
+template <int MODE, int E, bool FIX>
 __device__ __forceinline__ void products_mont(uint64_t (&X)[ProdShape<MODE>::NIN][1 << E],
-                                              uint64_t (&Y)[ProdShape<MODE>::NOUT][1 << E], uint64_t q,
+                                              uint64_t (&Y)[ProdShape<MODE>::NOUT][1 << E], const NttConst &c,
                                               uint64_t qinv) {
+  const uint32_t four = opaque4();
 #pragma unroll
   for (int s = 0; s < (1 << E); ++s) {
-    if constexpr (MODE == PROD_MUL) {
-      Y[0][s] = mont_mul(X[0][s], X[1][s], q, qinv);
+    if constexpr (FIX && MODE == PROD_MUL) {
+      Y[0][s] = mont_mul(X[0][s], X[1][s], c.q, qinv);
+    } else if constexpr (FIX) {
+      Y[0][s] = mont_mul(X[0][s], X[2][s], c.q, qinv);
+      Y[1][s] = mont_mad(X[0][s], X[3][s], X[1][s], X[2][s], c.q, qinv);
+      Y[2][s] = mont_mul(X[1][s], X[3][s], c.q, qinv);
+    } else if constexpr (MODE == PROD_MUL) {
+      Y[0][s] = mont30_mul(split30(X[0][s]), X[1][s], c, four);
     } else {
-      Y[0][s] = mont_mul(X[0][s], X[2][s], q, qinv);
-      Y[1][s] = mont_mad(X[0][s], X[3][s], X[1][s], X[2][s], q, qinv);
-      Y[2][s] = mont_mul(X[1][s], X[3][s], q, qinv);
+      const Split30 a0 = split30(X[0][s]), a1 = split30(X[1][s]);
+      Y[0][s] = mont30_mul(a0, X[2][s], c, four);
+      Y[1][s] = mont30_mad(a0, X[3][s], a1, X[2][s], c, four);
+      Y[2][s] = mont30_mul(a1, X[3][s], c, four);
     }
   }
 }
 
-// Forward outputs (lazy words, below 256q up to 56 bits) brought to the factor
-// range of products_mont, below 2q.  Up to 47 bits the lazy words already keep
-// the tensor's sum of two products below q R (2 (207 q)^2 < q 2^64: 17 stages
-// of 12q on inputs of at most 3q), and the step is skipped (k is uniform per
-// workgroup, so the test is a scalar branch).
-template <int E> __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1 << E], const NttConst &c) {
-  if (c.k < 48) return;
+// Forward outputs brought to the factor ranges of the products: lazy words of 34
+// to 55 bits (below 256q) below 3q, of 56 bits and more below 2q, of 33 bits and
+// fewer (below 207q: 17 stages of 12q on inputs below 3q) as they are, which keeps
+// the tensor's sum of two products below q R (2 (207 q)^2 < q 2^64).
+template <int E, bool FIX> __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1 << E], const NttConst &c) {
 #pragma unroll
-  for (int s = 0; s < (1 << E); ++s) x[s] = reduce_est(x[s], c.nq, c.ce, c.k - 33);
+  for (int s = 0; s < (1 << E); ++s) {
+    if constexpr (!FIX) x[s] = est3(x[s], c);
+    else if (c.k >= 34) x[s] = reduce_est(x[s], c.nq, c.ce, c.k - 33);
+  }
 }
 
 // One workgroup per block of 2^B coefficients of one (batch entry, limb):
@@ -851,7 +867,7 @@ template <int E> __device__ __forceinline__ void reduce_for_mont(uint64_t (&x)[1
 // never leave the chip.  With B == LOGN the whole product is one kernel;
 // with B < LOGN the forward column pass runs before it and the inverse
 // column pass after it.  With DO_INV the products are Montgomery products
-// and lc must hold the folded constants (N^-1 R in place of N^-1), also for
+// and lc must hold the folded constants (N^-1 scaled), also for
 // the inverse column pass that completes the transform.  Without DO_INV the
 // products are exact (Barrett) and lc the plain constants.
 template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV, bool FIX>
@@ -877,7 +893,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
       const TwM *tp = opaque(t);
       load_global<B, E, F::LO, F::R, true>(v, pick_ptr(a.in, p) + in_off, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
       fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, tp, c);
-      if constexpr (DO_INV) reduce_for_mont<E>(v, c);
+      if constexpr (DO_INV) reduce_for_mont<E, FIX>(v, c);
       else reduce_out<E, FIX>(v, c);
     } else {
       load_global_m0<B, E, true>(v, pick_ptr(a.in, p) + in_off, lds, tid);
@@ -893,7 +909,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
     });
   }
   uint64_t Y[NOUT][1 << E];
-  if constexpr (DO_INV) products_mont<MODE, E>(X, Y, c.q, mont->qinv);
+  if constexpr (DO_INV) products_mont<MODE, E, FIX>(X, Y, c, mont->qinv);
   else products<MODE, E>(X, Y, c);
 #pragma unroll 1
   for (int o = 0; o < NOUT; ++o) {

@@ -20,7 +20,7 @@ void launch_prod_cfg(const hentt_tables *t, const ProdArgs &pa, uint32_t batch, 
                      uint64_t *ws, hipStream_t st) {
   const TwM *tw = t->s->d_twm;
   // outputs going back to the coefficient domain take Montgomery products,
-  // whose R^-1 the inverse transform's folded N^-1 R scaling cancels
+  // whose stray factor the inverse transform's scaled N^-1 cancels
   const NttConst *lc = out_coeff ? t->s->d_ncm : t->s->d_nc;
   const MontLimb *mont = t->s->d_mont;
   const uint32_t L = t->limbs;

@@ -45,7 +45,7 @@ struct Storage {
   LimbConst *d_lc = nullptr;   // [limbs]
   TwM *d_twm = nullptr;        // [limbs][2][N] the transforms' tables
   NttConst *d_nc = nullptr;    // [limbs]
-  NttConst *d_ncm = nullptr;   // [limbs] the same with N^-1 R mod q for N^-1 (after Montgomery products)
+  NttConst *d_ncm = nullptr;   // [limbs] the same with N^-1 scaled for the inverse after Montgomery products
   MontLimb *d_mont = nullptr;  // [limbs] Montgomery constants
   MatLimb *d_mat = nullptr;    // [limbs] constants of the matrix product
   std::vector<uint64_t> moduli;

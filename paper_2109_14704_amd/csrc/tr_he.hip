@@ -89,8 +89,7 @@ int ks_consts(Storage *s, uint32_t L1, const KsLimb **out) {
   for (uint32_t t = 0; t < L1; ++t) {
     const uint64_t q = s->moduli[t];
     kc[t].mu = (uint64_t)(((host::u128)1 << 64) / q);
-    kc[t].qinv = 0 - host::inv64(q);
-    kc[t].r = host::tw_m((uint64_t)(((host::u128)1 << 64) % q), q);
+    kc[t].r = host::tw_m((1ull << 60) % q, q);
     kc[t].pm = host::tw_m(P % q, q);
   }
   KsLimb *d = nullptr;
@@ -181,7 +180,6 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
   last.limbs = 1;
   last.d_twm = s->d_twm + (size_t)L * 2 * N;
   last.d_nc = s->d_nc + L;
-  last.d_mont = s->d_mont + L;
   last.device = s->device;
   const hentt_tables lv{&last, 1};
   rc = run_inverse_from(&lv, c + (size_t)L * N, (uint64_t)level * N, (uint64_t *)tl, batch, st);

@@ -59,6 +59,21 @@ int main(int argc, char **argv) {
       uint64_t A = a, D = d;
       gs_bfly_m(A, D, w, b, c, 4);
       EXPECT(A == a + d && (u128)D < (u128)12 * q && D % q == mm(W, (a % q + q - d % q) % q, q), "gs_bfly_m\n");
+      {  // products of two variables, at the bounds of each size's factors
+        const uint64_t qa = k < 34 ? 207 * q : k <= 55 ? 3 * q : q, qb = k < 34 ? 207 * q : k <= 55 ? 3 * q : 2 * q;
+        const uint64_t a0 = it % 4 ? g() % qa : qa - 1, a1 = it % 6 ? g() % qa : qa - 1;
+        const uint64_t b0 = it % 3 ? g() % qb : qb - 1, b1 = it % 2 ? g() % qb : qb - 1;
+        const uint64_t r60 = (1ull << 60) % q, b = (k <= 55 ? 5 : 7) * q;
+        const uint64_t p = mont30_mul(split30(a0), b0, c, 4), s2 = mont30_mul_add(split30(a1), b1, 3 * q, c, 4);
+        EXPECT(p < b && s2 < b + 3 * q, "mont30 ranges q=%llx\n", (unsigned long long)q);
+        EXPECT(mm(p % q, r60, q) == mm(a0 % q, b0 % q, q), "mont30_mul q=%llx\n", (unsigned long long)q);
+        EXPECT(mm(s2 % q, r60, q) == mm(a1 % q, b1 % q, q), "mont30_mul_add q=%llx\n", (unsigned long long)q);
+        if (k <= 55) {
+          const uint64_t ps = mont30_mad(split30(a0), b0, split30(a1), b1, c, 4);
+          EXPECT(ps < 6 * q, "mont30_mad range q=%llx\n", (unsigned long long)q);
+          EXPECT(mm(ps % q, r60, q) == (mm(a0 % q, b0 % q, q) + mm(a1 % q, b1 % q, q)) % q, "mont30_mad\n");
+        }
+      }
       if (k >= 34) {
         const uint64_t e = est3(y, c);
         EXPECT((u128)e < (u128)3 * q && e % q == y % q, "est3 q=%llx\n", (unsigned long long)q);
