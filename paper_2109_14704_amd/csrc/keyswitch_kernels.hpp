@@ -103,6 +103,14 @@ __device__ __forceinline__ void ks_finish(uint64_t (&acc)[1 << E], const KsLimb 
   for (int s = 0; s < (1 << E); ++s) acc[s] = reduce_word(acc[s], c);
 }
 
+// Digit t modulo its own prime, back in the NTT domain, is c2's limb t itself: at
+// j = t the kernels read that (canonical words, in the (0, E) map) and transform
+// nothing, one transform in l + 1 (2^15, 8 primes, 32 entries, the whole
+// relinearization: 686 us without, 671 with).
+__device__ __forceinline__ const uint64_t *ks_own(const KsArgs &a, uint32_t b, uint32_t t, int logn, uint32_t off) {
+  return a.c + ((((uint64_t)b * 3 + 2) * a.l + t) << logn) + off;
+}
+
 // c_s's words (s = 0, 1) at block offset `off` of target prime t for batch
 // entry b, or null for the special prime (t = l).
 __device__ __forceinline__ const uint64_t *ks_cs(const KsArgs &a, uint32_t b, uint32_t s, uint32_t t, int logn,
@@ -133,13 +141,17 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw
     for (uint32_t j = 0; j < a.l; ++j) {
       if (j > 0) __syncthreads();  // the previous digit's last LDS reads are done
       uint64_t v[1 << E];
-      load_global<LOGN, E, F::LO, F::R>(v, a.d + (((uint64_t)b * a.l + j) << LOGN),
-                                         RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
-  #pragma unroll
-      for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c);
-      // an opaque copy of the table pointer per digit: the twiddles (the same
-      // for every digit) are re-read from cache instead of held in VGPRs
-      fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, opaque(tt), c);
+      if (j == t) {
+        load_global<LOGN, E, 0, E>(v, ks_own(a, b, t, LOGN, 0), M0::lane_part(tid));
+      } else {
+        load_global<LOGN, E, F::LO, F::R>(v, a.d + (((uint64_t)b * a.l + j) << LOGN),
+                                           RoundMap<LOGN, E, F::LO, F::R>::lane_part(tid));
+#pragma unroll
+        for (int s = 0; s < (1 << E); ++s) v[s] = ks_lift(v[s], kc.mu, c);
+        // an opaque copy of the table pointer per digit: the twiddles (the same
+        // for every digit) are re-read from cache instead of held in VGPRs
+        fwd_block_rounds<LOGN, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, 0, opaque(tt), c);
+      }
       ks_mac<LOGN, E, FIX>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN), L1, M0::lane_part(tid), acc0, acc1, c,
                            j);
     }
@@ -162,6 +174,7 @@ __global__ __launch_bounds__(cols_lanes<EC>()) void k_ks_cols(KsArgs a, const Tw
   const uint32_t t = r % L1;
   r /= L1;
   const uint32_t j = r % a.l, b = r / a.l;
+  if (j == t) return;  // ks_own
   const NttConst c = lc[t];
   const uint64_t mu = a.kc[t].mu;
   const uint64_t *src = a.d + (((uint64_t)b * a.l + j) << LOGN);
@@ -210,9 +223,13 @@ __global__ __launch_bounds__(1 << (B - E), 4) void k_ks_blocks(KsArgs a, const T
     for (uint32_t j = j0; j < j1; ++j) {
       if (j > j0) __syncthreads();  // the previous digit's last LDS reads are done
       uint64_t v[1 << E];
-      load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
-                                     RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-      fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, opaque(tt), c);
+      if (j == t) {
+        load_global<B, E, 0, E>(v, ks_own(a, b, t, LOGN, blockStart), M0::lane_part(tid));
+      } else {
+        load_global<B, E, F::LO, F::R>(v, a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN) + blockStart,
+                                       RoundMap<B, E, F::LO, F::R>::lane_part(tid));
+        fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, opaque(tt), c);
+      }
       ks_mac<B, E, FIX>(v, a.ksk + (((uint64_t)j * 2 * L1 + t) << LOGN) + blockStart, L1 << (LOGN - B), M0::lane_part(tid),
                    acc0, acc1, c, j - j0);
     }
