@@ -25,7 +25,8 @@ struct KsLimb {     // per target prime q_t of one level
 };
 
 struct KsArgs {
-  const uint64_t *d;    // [batch][l][N] digits, coefficient domain, canonical mod q_j
+  const uint64_t *d;    // [batch][l][N] digits, coefficient domain, canonical mod q_j, or,
+                        // two-pass sizes, behind the inverse transform's block pass
   const uint64_t *ksk;  // [l][2][l + 1][N] NTT domain
   uint64_t *e;          // [batch][l][l + 1][N] column-pass scratch (two-pass sizes)
   uint64_t *acc;        // [batch][2][l + 1][N]
@@ -34,6 +35,7 @@ struct KsArgs {
   uint64_t *part;       // [splits][batch][2][l + 1][N] partial sums when splits > 1
   uint32_t batch, l;
   uint32_t splits;      // workgroups a block's digits are spread over
+  uint32_t col_splits;  // workgroups a digit's column tile spreads its target primes over
 };
 
 // A digit word x < q_j < 2^60 as an input of the transform modulo q_t: as it is
@@ -162,29 +164,53 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const Tw
   });
 }
 
-// Two-pass sizes, pass 1: column pass of digit j modulo q_t into e.
+// Two-pass sizes, pass 1: for a tile of columns of digit j, the last EC inverse
+// stages of the digit (the words behind the block pass), which end in the lane map
+// the forward pass begins with, so that the coefficients stay in registers; then,
+// per target prime of this workgroup's run, the first EC forward stages modulo q_t
+// into e.  It writes l words per word read, so a forward pass of its own per
+// prime, reading the digit back each time, was bound by those reads: N = 2^15, 8
+// primes, 32 entries, 180 us with streaming loads, 147 with ordinary ones, and 40 of
+// the inverse column pass; 130 together.  Four waves per SIMD (128 registers).
 template <int LOGN, int EC>
-__global__ __launch_bounds__(cols_lanes<EC>()) void k_ks_cols(KsArgs a, const TwM *__restrict__ tw,
+__global__ __launch_bounds__(cols_lanes<EC>(), EC < 8 ? 4 : 1) void k_ks_cols(KsArgs a, const TwM *__restrict__ tw,
                                                               const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[cols_lds<EC>()];
-  constexpr uint32_t tiles = fcols_blocks_per_unit<LOGN, EC>();
+  constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, EC>();
   const uint32_t L1 = a.l + 1;
   uint32_t r = blockIdx.x / tiles;
-  const uint32_t col = fcol<EC>(blockIdx.x % tiles);
-  const uint32_t t = r % L1;
-  r /= L1;
+  const uint32_t col = (blockIdx.x % tiles) * LC<EC> + threadIdx.x % LC<EC>;
+  const uint32_t part = r % a.col_splits;
+  r /= a.col_splits;
   const uint32_t j = r % a.l, b = r / a.l;
-  if (j == t) return;  // ks_own
-  const NttConst c = lc[t];
-  const uint64_t mu = a.kc[t].mu;
   const uint64_t *src = a.d + (((uint64_t)b * a.l + j) << LOGN);
-  uint64_t *dst = a.e + ((((uint64_t)b * a.l + j) * L1 + t) << LOGN);
-  by_class(c, [&](auto FX) __attribute__((always_inline)) {
-    fcol_pass<LOGN, EC, decltype(FX)::value>(
-        [&](uint32_t row) { return ks_lift(gload<true>(src, (row << (LOGN - EC)) + col), mu, c); },
-        [&](uint32_t row, uint64_t v) { gstore<true>(dst, (row << (LOGN - EC)) + col, v); },
-        tw + (size_t)t * 2 * (1u << LOGN), c, lds);
-  });
+  uint64_t *dst = a.e + (((uint64_t)b * a.l + j) * L1 << LOGN);
+  uint64_t x[16];
+  {
+    const NttConst c = lc[j];
+    by_class(c, [&](auto FX) __attribute__((always_inline)) {
+      lcol_inv<LOGN, EC, decltype(FX)::value>(
+          x, [&](uint32_t row) { return gload<false>(src, (row << (LOGN - EC)) + col); },
+          tw + ((size_t)j * 2 + 1) * (1u << LOGN), c, lds);
+    });
+  }
+  const uint32_t t1 = (part + 1) * L1 / a.col_splits;
+#pragma unroll 1
+  for (uint32_t t = part * L1 / a.col_splits; t < t1; ++t) {
+    if (t == j) continue;  // ks_own
+    __syncthreads();       // the last LDS reads before this prime's writes
+    const NttConst c = lc[t];
+    const uint64_t mu = a.kc[t].mu;
+    uint64_t *o = dst + ((uint64_t)t << LOGN);
+    by_class(c, [&](auto FX) __attribute__((always_inline)) {
+      uint64_t v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = ks_lift(x[k], mu, c);
+      lcol_fwd<LOGN, EC, decltype(FX)::value>(
+          v, [&](uint32_t row, uint64_t y) { gstore<true>(o, (row << (LOGN - EC)) + col, y); },
+          tw + (size_t)t * 2 * (1u << LOGN), c, lds);
+    });
+  }
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block

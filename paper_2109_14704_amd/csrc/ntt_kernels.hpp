@@ -579,54 +579,77 @@ __device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, ui
 // were 2-4% slower on the tensors, at 8 stages 64 columns (1024 lanes, one
 // workgroup per CU) 5%.
 template <int EC> constexpr uint32_t LC = EC == 8 ? 16u : 64u;
-template <int LOGN, int EC, bool INV, bool FIX, typename LD, typename STO>
-__device__ __forceinline__ void lcol_pass(LD ld, STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
+// This lane's first row group: rows (r << (EC - 4)) + w, r < 16, in the round of
+// the large gaps, rows (w G + g << (EC - 4)) + k in the other.
+template <int EC> __device__ __forceinline__ uint32_t lcol_w() {
+  const uint32_t w = threadIdx.x / LC<EC>;
+  if constexpr (LC<EC> == 64) return __builtin_amdgcn_readfirstlane(w);
+  else return w;
+}
+// Forward stages of the words v (row map of the large gaps).
+template <int LOGN, int EC, bool FIX, typename STO>
+__device__ __forceinline__ void lcol_fwd(uint64_t (&v)[16], STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
   constexpr int R1 = 4, R2 = EC - R1, G = 16 >> R2;
   static_assert(R2 >= 2 && R2 <= 4, "two rounds of at most 16 words");
-  uint32_t w = threadIdx.x / LC<EC>;
-  if constexpr (LC<EC> == 64) w = __builtin_amdgcn_readfirstlane(w);
+  const uint32_t w = lcol_w<EC>();
   uint64_t *l = lds + threadIdx.x % LC<EC>;
-  uint64_t v[1 << R1], a[G][1 << R2];
+  uint64_t a[G][1 << R2];
+  fwd_round<LOGN, R1, LOGN - R1, R1, FIX>(v, LOGN, 0, 0, t, c);
+#pragma unroll
+  for (uint32_t r = 0; r < 16; ++r) l[((r << R2) + w) * LC<EC>] = v[r];
+  __syncthreads();
+#pragma unroll
+  for (uint32_t g = 0; g < G; ++g) {
+    const uint32_t hi = w * G + g;
+#pragma unroll
+    for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = l[((hi << R2) + k) * LC<EC>];
+  }
+#pragma unroll
+  for (uint32_t g = 0; g < G; ++g) {
+    const uint32_t hi = w * G + g;
+    fwd_round<LOGN, R2, LOGN - EC, R2, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
+#pragma unroll
+    for (uint32_t k = 0; k < (1u << R2); ++k) st((hi << R2) + k, a[g][k]);
+  }
+}
+// Inverse stages into v (row map of the large gaps), canonical words.
+template <int LOGN, int EC, bool FIX, typename LD>
+__device__ __forceinline__ void lcol_inv(uint64_t (&v)[16], LD ld, const TwM *t, const NttConst &c, uint64_t *lds) {
+  constexpr int R1 = 4, R2 = EC - R1, G = 16 >> R2;
+  static_assert(R2 >= 2 && R2 <= 4, "two rounds of at most 16 words");
+  const uint32_t w = lcol_w<EC>();
+  uint64_t *l = lds + threadIdx.x % LC<EC>;
+  uint64_t a[G][1 << R2];
+#pragma unroll
+  for (uint32_t g = 0; g < G; ++g) {
+#pragma unroll
+    for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = ld(((w * G + g) << R2) + k);
+  }
+#pragma unroll
+  for (uint32_t g = 0; g < G; ++g) {
+    const uint32_t hi = w * G + g;
+    inv_round<LOGN, R2, LOGN - EC, R2, 4, 5, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
+#pragma unroll
+    for (uint32_t k = 0; k < (1u << R2); ++k) l[((hi << R2) + k) * LC<EC>] = a[g][k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < 16; ++r) v[r] = l[((r << R2) + w) * LC<EC>];
+  inv_round<LOGN, R1, LOGN - R1, R1, 5, 4, FIX>(v, LOGN, 0, 0, t, c);
+  reduce_out<R1, FIX>(v, c);
+}
+template <int LOGN, int EC, bool INV, bool FIX, typename LD, typename STO>
+__device__ __forceinline__ void lcol_pass(LD ld, STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
+  uint64_t v[16];
+  const uint32_t w = lcol_w<EC>();
   if constexpr (!INV) {
 #pragma unroll
-    for (uint32_t r = 0; r < 16; ++r) v[r] = ld((r << R2) + w);
-    fwd_round<LOGN, R1, LOGN - R1, R1, FIX>(v, LOGN, 0, 0, t, c);
-#pragma unroll
-    for (uint32_t r = 0; r < 16; ++r) l[((r << R2) + w) * LC<EC>] = v[r];
-    __syncthreads();
-#pragma unroll
-    for (uint32_t g = 0; g < G; ++g) {
-      const uint32_t hi = w * G + g;
-#pragma unroll
-      for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = l[((hi << R2) + k) * LC<EC>];
-    }
-#pragma unroll
-    for (uint32_t g = 0; g < G; ++g) {
-      const uint32_t hi = w * G + g;
-      fwd_round<LOGN, R2, LOGN - EC, R2, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
-#pragma unroll
-      for (uint32_t k = 0; k < (1u << R2); ++k) st((hi << R2) + k, a[g][k]);
-    }
+    for (uint32_t r = 0; r < 16; ++r) v[r] = ld((r << (EC - 4)) + w);
+    lcol_fwd<LOGN, EC, FIX>(v, st, t, c, lds);
   } else {
+    lcol_inv<LOGN, EC, FIX>(v, ld, t, c, lds);
 #pragma unroll
-    for (uint32_t g = 0; g < G; ++g) {
-#pragma unroll
-      for (uint32_t k = 0; k < (1u << R2); ++k) a[g][k] = ld(((w * G + g) << R2) + k);
-    }
-#pragma unroll
-    for (uint32_t g = 0; g < G; ++g) {
-      const uint32_t hi = w * G + g;
-      inv_round<LOGN, R2, LOGN - EC, R2, 4, 5, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
-#pragma unroll
-      for (uint32_t k = 0; k < (1u << R2); ++k) l[((hi << R2) + k) * LC<EC>] = a[g][k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t r = 0; r < 16; ++r) v[r] = l[((r << R2) + w) * LC<EC>];
-    inv_round<LOGN, R1, LOGN - R1, R1, 5, 4, FIX>(v, LOGN, 0, 0, t, c);
-    reduce_out<R1, FIX>(v, c);
-#pragma unroll
-    for (uint32_t r = 0; r < 16; ++r) st((r << R2) + w, v[r]);
+    for (uint32_t r = 0; r < 16; ++r) st((r << (EC - 4)) + w, v[r]);
   }
 }
 
@@ -678,29 +701,6 @@ __global__ __launch_bounds__(cols_lanes<E>()) void k_cols(ColArgs a, const TwM *
                                                           const NttConst *__restrict__ lc, uint32_t batch,
                                                           uint32_t limbs) {
   cols_block<LOGN, E, INV>(a, tw, lc, batch, limbs, blockIdx.x);
-}
-
-// Forward column pass of EC stages with its own load (a prologue fused into
-// it), for the rescale and the key switch: one column per lane.
-template <int LOGN, int EC> constexpr uint32_t fcols_blocks_per_unit() {
-  return LCOL<EC> ? cols_blocks_per_unit<LOGN, EC>() : (1u << (LOGN - EC)) / 256;
-}
-template <int EC> __device__ __forceinline__ uint32_t fcol(uint32_t tile) {
-  if constexpr (LCOL<EC>) return tile * LC<EC> + threadIdx.x % LC<EC>;
-  else return tile * 256 + threadIdx.x;
-}
-template <int LOGN, int EC, bool FIX, typename LD, typename STO>
-__device__ __forceinline__ void fcol_pass(LD ld, STO st, const TwM *t, const NttConst &c, uint64_t *lds) {
-  if constexpr (LCOL<EC>) {
-    lcol_pass<LOGN, EC, false, FIX>(ld, st, t, c, lds);
-  } else {
-    uint64_t v[1 << EC];
-#pragma unroll
-    for (uint32_t r = 0; r < (1u << EC); ++r) v[r] = ld(r);
-    fwd_round<LOGN, EC, LOGN - EC, EC, FIX>(v, LOGN, 0, 0, t, c);
-#pragma unroll
-    for (uint32_t r = 0; r < (1u << EC); ++r) st(r, v[r]);
-  }
 }
 
 // Column stages of a two-pass transform or product at N = 2^log_n (measured over

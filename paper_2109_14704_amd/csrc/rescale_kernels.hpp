@@ -28,8 +28,7 @@ struct RsLimb {   // per remaining limb i of a level
 // 2^64) is short by at most one).
 __device__ __forceinline__ uint64_t rs_prologue(uint64_t x, uint64_t qL, uint64_t h, const RsLimb &r,
                                                 const NttConst &n) {
-  uint64_t s = x + h;
-  s = s >= qL ? s - qL : s;
+  uint64_t s = csub(x + h, qL);
   if (n.k < 34) s -= mulhi64(s, r.mu) * n.q;
   return s + r.nh;
 }
@@ -44,7 +43,7 @@ __device__ __forceinline__ uint64_t rs_epilogue(uint64_t c, uint64_t t, const Rs
 
 struct RsArgs {
   const uint64_t *c;    // [batch][L + 1][N] input (NTT or coefficient domain)
-  const uint64_t *tl;   // [batch][N] last limb in the coefficient domain (NTT path)
+  const uint64_t *tl;   // [batch][N] last limb in the coefficient domain (NTT path; or see k_rs_cols)
   uint64_t *out;        // [batch][L][N]
   const RsLimb *rs;     // [L]
   uint64_t qL, h;
@@ -91,24 +90,42 @@ __global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const Tw
 // Batch-entry-major order: the L units of one batch entry read the same
 // last-limb columns one after another, so all but the first read hit the
 // XCD's L2 (tile t of every unit lands on the same XCD when the tile count is
-// a multiple of 8); limb-major order re-read the whole batch's last limbs
-// from HBM or the MALL once per limb.
-template <int LOGN, int EC>
-__global__ __launch_bounds__(cols_lanes<EC>()) void k_rs_cols(RsArgs a, const TwM *__restrict__ tw,
+// a multiple of 8), with ordinary loads: streaming ones were mostly read again
+// from beyond it (N = 2^16, 24 limbs, 64 polynomials: 255 us, 227 with ordinary).
+// INV: the last limb comes as the inverse transform's block pass leaves it, and
+// every workgroup takes its last EC stages as well (they end in the lane map the
+// forward pass begins with).  That is L times the work for one launch less.
+template <int LOGN, int EC, bool INV>
+__global__ __launch_bounds__(cols_lanes<EC>(), EC < 8 ? 4 : 1) void k_rs_cols(RsArgs a, const TwM *__restrict__ tw,
                                                               const NttConst *__restrict__ lc) {
   __shared__ uint64_t lds[cols_lds<EC>()];
-  constexpr uint32_t tiles = fcols_blocks_per_unit<LOGN, EC>();
+  constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, EC>();
   const uint32_t u = blockIdx.x / tiles;
   const uint32_t b = u / a.L, i = u % a.L;
-  const uint32_t col = fcol<EC>(blockIdx.x % tiles);
+  const uint32_t col = (blockIdx.x % tiles) * LC<EC> + threadIdx.x % LC<EC>;
+  const uint64_t *src = a.tl + ((uint64_t)b << LOGN);
+  const auto ld = [&](uint32_t row) { return gload<false>(src, (row << (LOGN - EC)) + col); };
+  uint64_t x[16];
+  if constexpr (INV) {
+    const NttConst c = lc[a.L];
+    by_class(c, [&](auto FX) __attribute__((always_inline)) {
+      lcol_inv<LOGN, EC, decltype(FX)::value>(x, ld, tw + ((size_t)a.L * 2 + 1) * (1u << LOGN), c, lds);
+    });
+    __syncthreads();  // the LDS reads before the forward pass's writes
+  } else {
+    const uint32_t w = lcol_w<EC>();
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) x[r] = ld((r << (EC - 4)) + w);
+  }
   const NttConst c = lc[i];
   const RsLimb r = a.rs[i];
-  const uint64_t *src = a.tl + ((uint64_t)b << LOGN);
   uint64_t *dst = a.out + (((uint64_t)b * a.L + i) << LOGN);
   by_class(c, [&](auto FX) __attribute__((always_inline)) {
-    fcol_pass<LOGN, EC, decltype(FX)::value>(
-        [&](uint32_t row) { return rs_prologue(gload<true>(src, (row << (LOGN - EC)) + col), a.qL, a.h, r, c); },
-        [&](uint32_t row, uint64_t v) { gstore<true>(dst, (row << (LOGN - EC)) + col, v); },
+    uint64_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = rs_prologue(x[k], a.qL, a.h, r, c);
+    lcol_fwd<LOGN, EC, decltype(FX)::value>(
+        v, [&](uint32_t row, uint64_t y) { gstore<true>(dst, (row << (LOGN - EC)) + col, y); },
         tw + (size_t)i * 2 * (1u << LOGN), c, lds);
   });
 }

@@ -54,24 +54,73 @@ template <int LOGN> struct RsPlan {
   static constexpr int EC = two_pass_cols(LOGN), E = 3, ST = LOGN - EC, B = block_words(ST, E);
 };
 
-template <int LOGN> void launch_rescale_ntt(const RsArgs &a, const Storage *s, hipStream_t st) {
+// Block pass of the inverse transform of `limbs` limbs from limb `first` on, read
+// where they lie (limb l of entry b at src + b src_sb + l N) into dst; the column
+// passes of the rescale and the key switch take the rest.  16-byte loads: words of
+// a source that is only 8-byte aligned are copied first (dst is the library's own
+// buffer).
+template <int LOGN>
+int inv_blocks_from(const Storage *s, uint32_t first, uint32_t limbs, const uint64_t *src, uint64_t src_sb,
+                    uint64_t *dst, uint32_t batch, hipStream_t st) {
+  constexpr int E = 3, ST = LOGN - two_pass_cols(LOGN), B = block_words(ST, E);
+  const uint64_t sb = (uint64_t)limbs << LOGN;
+  InvIO io{src, dst, src_sb, sb};
+  if ((uintptr_t)src & 15) {
+    HIPCHK(hipMemcpy2DAsync(dst, sb * 8, src, src_sb * 8, sb * 8, batch, hipMemcpyDeviceToDevice, st));
+    io = InvIO{dst, dst, sb, sb};
+  }
+  LaunchTimer lt_("k_inv_blocks", LOGN, st);
+  hipLaunchKernelGGL((k_inv_blocks<LOGN, ST, B, E>), dim3((batch * limbs) << (LOGN - B)), dim3(1 << (B - E)), 0, st, io,
+                     s->d_twm + (size_t)first * 2 * (1u << LOGN), s->d_nc + first, batch, limbs);
+  return HENTT_OK;
+}
+
+// The last limb of every batch entry goes through `last`, [batch][N] words of the
+// library's own: inverse-transformed modulo qL, read where it lies.  Two-pass
+// sizes leave its column pass to k_rs_cols while that launch fits the chip at once
+// (kRsWaves, four waves per SIMD): N = 2^15, 8 limbs, 2 polynomials, 16.5 us for
+// the two column passes, 12 for the one; at 64 polynomials 40 to 47 and 57.
+constexpr uint64_t kRsWaves = 4096;
+template <int LOGN> int launch_rescale_ntt(RsArgs a, Storage *s, uint64_t *last, hipStream_t st) {
   const uint32_t units = a.batch * a.L;
+  const uint64_t *cl = a.c + ((uint64_t)a.L << LOGN), sb = (uint64_t)(a.L + 1) << LOGN;
   using P = RsPlan<LOGN>;
+  a.tl = last;
+  Storage one;  // limb L's tables alone (a view: owns nothing)
+  one.log_n = LOGN;
+  one.limbs = 1;
+  one.d_twm = s->d_twm + ((size_t)a.L * 2 << LOGN);
+  one.d_nc = s->d_nc + a.L;
+  one.d_mont = s->d_mont + a.L;
+  one.device = s->device;
+  const hentt_tables lv{&one, 1};
   if constexpr (P::WHOLE) {
+    const int rc = run_inverse_from(&lv, cl, sb, last, a.batch, st);
+    if (rc) return rc;
     LaunchTimer lt_("k_rs_whole", LOGN, st);
     hipLaunchKernelGGL((k_rs_whole<LOGN, whole_e(LOGN)>), dim3(units), dim3(1 << (LOGN - whole_e(LOGN))), 0, st, a, s->d_twm, s->d_nc);
   } else {
-    {
+    constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, P::EC>(), lanes = cols_lanes<P::EC>();
+    const dim3 g(units * tiles), blk(lanes);
+    if ((uint64_t)units * tiles * (lanes / 64) <= kRsWaves) {
+      const int rc = inv_blocks_from<LOGN>(s, a.L, 1, cl, sb, last, a.batch, st);
+      if (rc) return rc;
       LaunchTimer lt_("k_rs_cols", LOGN, st);
-      hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC>), dim3(units * fcols_blocks_per_unit<LOGN, P::EC>()),
-                         dim3(cols_lanes<P::EC>()), 0, st, a, s->d_twm, s->d_nc);
+      hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC, true>), g, blk, 0, st, a, s->d_twm, s->d_nc);
+    } else {
+      const int rc = run_inverse_from(&lv, cl, sb, last, a.batch, st);
+      if (rc) return rc;
+      LaunchTimer lt_("k_rs_cols", LOGN, st);
+      hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC, false>), g, blk, 0, st, a, s->d_twm, s->d_nc);
     }
     LaunchTimer lt_("k_rs_blocks", LOGN, st);
     hipLaunchKernelGGL((k_rs_blocks<LOGN, P::ST, P::B, P::E>), dim3(units << (LOGN - P::B)), dim3(1 << (P::B - P::E)), 0, st, a,
                        s->d_twm, s->d_nc);
   }
+  HIPCHK(hipGetLastError());
+  return HENTT_OK;
 }
-typedef void (*rs_fn)(const RsArgs &, const Storage *, hipStream_t);
+typedef int (*rs_fn)(RsArgs, Storage *, uint64_t *, hipStream_t);
 #define RS_ENTRY(n) launch_rescale_ntt<n>,
 const rs_fn k_rs_table[] = {HENTT_SIZES(RS_ENTRY)};
 
@@ -119,16 +168,37 @@ template <int LOGN> struct KsPlan {
 // entries, no difference at three; 86 -> 68 us at 2^14, 12 primes, one entry).
 constexpr uint32_t kKsWaves = 2304;
 
-template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hipStream_t st) {
+// Workgroups a digit's column tile spreads its target primes over: each repeats
+// the tile's inverse stages, so no more than fill kColWaves waves (2^15, 8 primes,
+// 32 and 4 entries: 600 and 117 us with 4096, 612 and 123 with 8192, 620 and 122
+// with 16384; 2048 differs by the run).
+constexpr uint32_t kColWaves = 4096;
+template <int EC> uint32_t col_splits(uint64_t groups, uint32_t primes) {
+  const uint64_t waves = groups * (cols_lanes<EC>() / 64);
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(primes, kColWaves / waves));
+}
+
+// d: [batch][l][N] words of the library's own for the digits, c2 in the
+// coefficient domain modulo its own primes (two-pass sizes: up to the column pass).
+template <int LOGN> int launch_keyswitch(KsArgs a, Storage *s, uint64_t *d, hipStream_t st) {
   const uint32_t L1 = a.l + 1;
+  const uint64_t P2 = (uint64_t)a.l << LOGN;
   using P = KsPlan<LOGN>;
+  a.d = d;
   if constexpr (P::WHOLE) {
+    const hentt_tables lv{s, a.l};
+    const int rc = run_inverse_from(&lv, a.c + 2 * P2, 3 * P2, d, a.batch, st);
+    if (rc) return rc;
     LaunchTimer lt_("k_ks_whole", LOGN, st);
     hipLaunchKernelGGL((k_ks_whole<LOGN, whole_e(LOGN)>), dim3(a.batch * L1), dim3(1 << (LOGN - whole_e(LOGN))), 0, st, a, s->d_twm, s->d_nc);
   } else {
+    const int rc = inv_blocks_from<LOGN>(s, 0, a.l, a.c + 2 * P2, 3 * P2, d, a.batch, st);
+    if (rc) return rc;
+    constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, P::EC>();
+    a.col_splits = col_splits<P::EC>((uint64_t)a.batch * a.l * tiles, L1);
     {
       LaunchTimer lt_("k_ks_cols", LOGN, st);
-      hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * L1 * fcols_blocks_per_unit<LOGN, P::EC>()),
+      hipLaunchKernelGGL((k_ks_cols<LOGN, P::EC>), dim3(a.batch * a.l * a.col_splits * tiles),
                          dim3(cols_lanes<P::EC>()), 0, st, a, s->d_twm, s->d_nc);
     }
     {
@@ -141,8 +211,10 @@ template <int LOGN> void launch_keyswitch(const KsArgs &a, const Storage *s, hip
       hipLaunchKernelGGL((k_ks_sum<LOGN>), dim3(a.batch * 2 * L1 << (LOGN - 8)), dim3(256), 0, st, a, s->d_nc);
     }
   }
+  HIPCHK(hipGetLastError());
+  return HENTT_OK;
 }
-typedef void (*ks_fn)(const KsArgs &, const Storage *, hipStream_t);
+typedef int (*ks_fn)(KsArgs, Storage *, uint64_t *, hipStream_t);
 #define KS_ENTRY(n) launch_keyswitch<n>,
 const ks_fn k_ks_table[] = {HENTT_SIZES(KS_ENTRY)};
 
@@ -170,29 +242,12 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
     HIPCHK(hipGetLastError());
     return HENTT_OK;
   }
-  // the last limb of every batch entry, inverse-transformed modulo qL, read
-  // where it lies (no copy first)
   void *tl = nullptr;
   rc = pool_get((size_t)batch * N * 8, st, &tl);
   if (rc) return rc;
-  Storage last;  // limb L's tables alone (a view: owns nothing)
-  last.log_n = ln;
-  last.limbs = 1;
-  last.d_twm = s->d_twm + (size_t)L * 2 * N;
-  last.d_nc = s->d_nc + L;
-  last.device = s->device;
-  const hentt_tables lv{&last, 1};
-  rc = run_inverse_from(&lv, c + (size_t)L * N, (uint64_t)level * N, (uint64_t *)tl, batch, st);
-  hipError_t e = hipSuccess;
-  if (!rc) {
-    a.tl = (const uint64_t *)tl;
-    k_rs_table[ln - HENTT_LOG_N_MIN](a, s, st);
-    e = hipGetLastError();
-  }
+  rc = k_rs_table[ln - HENTT_LOG_N_MIN](a, s, (uint64_t *)tl, st);
   pool_put(tl);
-  if (rc) return rc;
-  if (e != hipSuccess) return hip_fail(e);
-  return HENTT_OK;
+  return rc;
 }
 
 int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uint64_t *out, uint32_t batch,
@@ -216,34 +271,23 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
   }
   if (rc) return rc;
   uint64_t *d = (uint64_t *)buf, *acc = d + batch * P, *e = acc + (size_t)batch * 2 * L1 * N, *part = e + e_bytes / 8;
-  // digits: c2 in the coefficient domain, modulo its own primes
-  const hentt_tables lv{s, l};
-  rc = run_inverse_from(&lv, c + 2 * P, 3 * P, d, batch, st);
-  hipError_t he = hipSuccess;
-  if (!rc) {
-    KsArgs a{};
-    a.d = d;
-    a.ksk = ksk;
-    a.e = two_pass ? e : nullptr;
-    a.acc = acc;
-    a.c = c;
-    a.kc = kc;
-    a.part = splits > 1 ? part : nullptr;
-    a.splits = splits;
-    a.batch = batch;
-    a.l = l;
-    k_ks_table[ln - HENTT_LOG_N_MIN](a, s, st);
-    he = hipGetLastError();
-    // divide by P with rounding, over q_0 .. q_{l-1}: [batch][2][l+1] -> [batch][2][l];
-    // the accumulators already hold P c_s, so this yields (c0, c1) + round(P^-1 c2 evk)
-    if (he == hipSuccess) rc = run_rescale(t, acc, out, batch * 2, true, st);
-  }
+  KsArgs a{};
+  a.ksk = ksk;
+  a.e = two_pass ? e : nullptr;
+  a.acc = acc;
+  a.c = c;
+  a.kc = kc;
+  a.part = splits > 1 ? part : nullptr;
+  a.splits = splits;
+  a.batch = batch;
+  a.l = l;
+  rc = k_ks_table[ln - HENTT_LOG_N_MIN](a, s, d, st);
+  // divide by P with rounding, over q_0 .. q_{l-1}: [batch][2][l+1] -> [batch][2][l];
+  // the accumulators already hold P c_s, so this yields (c0, c1) + round(P^-1 c2 evk)
+  if (!rc) rc = run_rescale(t, acc, out, batch * 2, true, st);
   pool_put(buf);
-  if (rc) return rc;
-  if (he != hipSuccess) return hip_fail(he);
-  return HENTT_OK;
+  return rc;
 }
-
 
 // ------------------------------------------------------------ matMul
 int run_matmul(const hentt_tables *t, const uint64_t *A, const uint64_t *B, uint64_t *C, uint32_t m, uint32_t n,
