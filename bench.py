@@ -599,7 +599,7 @@ def bench_matmul(args):
         ms = a.elapsed_time(b) / reps
         terms = m * n * k * L * n_
         work = R.Work(8.0 * L * n_ * (2 * m * k + 2 * k * n + 6 * m * n), R.MUL_TENSOR * terms,
-                      (R.VALU_MAC if k >= 3 else R.VALU_MAC_B) * terms)
+                      R.VALU_MAC * terms)
         rl = R.roof(work, ms / 1e3)
         rl.update({"kernel": "k_ct_matmul<13>", "launch_ms": round(ms, 4), "traffic": R.stored_traffic("k_ct_matmul<13>")})
         rows.append({"shape": "%dx%dx%d" % (m, n, k), "ms": round(ms, 4),
@@ -624,7 +624,7 @@ def ks_work(batch, l, logn, ec):
     from paper_2109_14704_amd import roofline as R
     n = 1 << logn
     L1 = l + 1
-    w = R.transform_work(n, batch * L1 * l, logn - ec)
+    w = R.transform_work(n, batch * l * l, logn - ec)  # a digit at its own prime is not transformed
     muls = batch * L1 * l * R.MUL_KS_MAC * n + batch * 2 * n * (l * 2 * R.MUL_SHOUP + R.MUL_SHOUP)
     valu = batch * L1 * l * 2 * R.VALU_KS_MAC * n + batch * 2 * n * (l * R.VALU_KS_FIN_C + R.VALU_KS_FIN)
     nbytes = 8.0 * n * (batch * l * L1 + l * 2 * L1 + batch * 2 * l + batch * 2 * L1)

@@ -214,11 +214,11 @@ __global__ __launch_bounds__(cols_lanes<EC>(), EC < 8 ? 4 : 1) void k_ks_cols(Ks
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
-// rounds of every digit, accumulated with the key in registers.  VALU-bound (a
-// fifth of its HBM time at the copy rate).  N = 2^15, 8 primes, 32 entries, the
+// rounds of every digit, accumulated with the key in registers.  VALU-bound: 320 us,
+// its bytes take 120 at the copy rate.  At N = 2^15, 8 primes, 32 entries, the
 // whole relinearization: 720 us with Montgomery products of 64-bit words, 690 with
 // mont30_mul at the 134 VGPRs it takes (three waves per SIMD), 678 held to 128
-// (four waves, six words spilled).  The key in root-power form, a third fewer
+// (four waves), 600 with the column passes fused.  The key in root-power form, a third fewer
 // instructions than the 64-bit products for twice its bytes, gave 716.  A small batch
 // has fewer blocks than the chip has places for waves; their digits are then
 // spread over `splits` workgroups, whose partial sums k_ks_sum adds up.

@@ -15,7 +15,7 @@ namespace {
 // ---------------------------------------------------------------- rescale
 // Constants of RS from a level of `level` limbs to level - 1 (section II-A):
 // per remaining limb i, floor(2^64 / q_i), q_i - (h mod q_i) with
-// h = (qL - 1) / 2, and qL^-1 mod q_i with its Shoup quotient.  Made once per
+// h = (qL - 1) / 2, and qL^-1 mod q_i as a root power.  Made once per
 // (tables, level) with a synchronous upload, like the tables themselves.
 int rs_constants(Storage *s, uint32_t level, const RsLimb **out) {
   std::lock_guard<std::mutex> lk(s->rs_mu);
@@ -47,8 +47,8 @@ int rs_constants(Storage *s, uint32_t level, const RsLimb **out) {
 }
 
 // Stage split of the rescale's forward transforms: whole up to 2^13, the two-pass
-// split above (2^16, 64 polynomials of 24 limbs: 753 us with seven column stages,
-// 771 with six, 762 with five in registers).
+// split above (2^16, 64 polynomials of 24 limbs, when measured: 753 us with seven column
+// stages, 771 with six, 762 with five in registers; 734 since).
 template <int LOGN> struct RsPlan {
   static constexpr bool WHOLE = LOGN <= 13;
   static constexpr int EC = two_pass_cols(LOGN), E = 3, ST = LOGN - EC, B = block_words(ST, E);
@@ -155,8 +155,8 @@ int ks_consts(Storage *s, uint32_t L1, const KsLimb **out) {
 
 // Key-switch split: the digit loop holds two accumulator arrays, so whole
 // transforms only up to 2^12 (256 lanes); above, the two-pass split (2^15, 32
-// ciphertexts, 8 primes: 546 us with six column stages, 549 with seven, 595 with
-// five in registers).
+// ciphertexts, 8 primes, the key switch alone when measured: 546 us with six column
+// stages, 549 with seven, 595 with five in registers; 455 since).
 template <int LOGN> struct KsPlan {
   static constexpr bool WHOLE = LOGN <= 12;
   static constexpr int EC = two_pass_cols(LOGN);

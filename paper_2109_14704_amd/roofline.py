@@ -41,15 +41,14 @@ MUL_KS_MAC = 22     # key switch, per digit word: products with both key compone
 MUL_RS_PRO = 7      # rescale prologue: floor-estimate of s / q_i (4) and its product by q_i (3)
 
 # VALU lane-operations of this implementation per unit (counted in its AMD asm).
-VALU_BFLY = 21      # 9 multiplies + 64-bit adds, one compare, two selects
-VALU_PROD = 19      # Montgomery product a b R^-1 mod q
-VALU_TENSOR = 68    # c0d0, c1d1 (2 x 19) + c0d1 + c1d0 with one Montgomery reduction (30)
-VALU_RS_EPI = 17    # rescale epilogue: Shoup product by qL^-1 and a reduction from [0, 4q)
-VALU_MAC = 83       # one matMul product term, k >= 3: the tensor's Montgomery products (68), three lazy additions
-VALU_MAC_B = 121    # one matMul product term, k <= 2: the tensor's three outputs accumulated with Barrett mad_mod
-VALU_KS_MAC = 24    # key switch, per digit word and key component: Montgomery product (19), lazy addition (5)
-VALU_KS_FIN = 20    # key switch, per output word: Shoup product by R mod q (12), reduction from [0, 4q) (8)
-VALU_KS_FIN_C = 38  # the same plus P c_s: a second Shoup product, an addition, a reduction from [0, 8q)
+VALU_BFLY = 11      # forward butterfly: 8 multiplies or multiply-adds, 3 additions (the inverse takes 12)
+VALU_PROD = 15      # product of two variables, two 30-bit Montgomery steps (12) and a split (3)
+VALU_TENSOR = 48    # c0d0, c1d1 (2 x 12) + c0d1 + c1d0 summed ahead of each reduction (16) + the shared splits
+VALU_RS_EPI = 19    # rescale epilogue: c + off - t (2), product by qL^-1 (8), canonical reduction (9)
+VALU_MAC = 36       # one matMul product term: four products by A's words in root-power form (8 each), reductions
+VALU_KS_MAC = 15    # key switch, per digit word and key component: product (12), half the word's cut and split (3)
+VALU_KS_FIN = 17    # key switch, per output word: product by 2^60 (8), canonical reduction (9)
+VALU_KS_FIN_C = 29  # the same plus P c_s: a second product (8), a cut (4)
 
 
 def paper_density(kind, n):
