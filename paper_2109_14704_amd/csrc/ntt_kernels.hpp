@@ -127,9 +127,10 @@ template <typename F> __device__ __forceinline__ void by_class(const NttConst &c
 // Moduli of up to 56 bits need no corrections: a transform adds at most 12q
 // per stage to inputs of a few q.  Larger ones (FIX) enter with any 64-bit
 // words and bring X below 3q before every stage (3 + 12 < 16).
-template <int B, int E, int LO, int R, bool FIX>
+template <int B, int E, int LO, int R, bool FIX, bool PRE = false>
 __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
-                                          uint32_t lanePart, const TwM* __restrict__ tw, const NttConst &c) {
+                                          uint32_t lanePart, const TwM* __restrict__ tw, const NttConst &c,
+                                          const TwM *pf = nullptr) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t four = opaque4();
   static_for<0, R>([&](auto U) __attribute__((always_inline)) {
@@ -147,7 +148,8 @@ __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, 
 #pragma unroll
       for (int k = 0; k < (1 << R); ++k) {
         if (k & h) continue;
-        ct_bfly_m(x[(g << R) + k], x[(g << R) + k + h], ld_tw(tw, base + (k >> (R - u))), c, four);
+        const TwM w = PRE ? pf[(1 << u) - 1 + (k >> (R - u))] : ld_tw(tw, base + (k >> (R - u)));
+        ct_bfly_m(x[(g << R) + k], x[(g << R) + k + h], w, c, four);
       }
     }
   });
@@ -177,9 +179,10 @@ template <int R, int LBIN, int LBOUT> constexpr bool inv_over(int k) {
   const int bound = h < 0 ? 1 << (LBIN + R) : 12 << (R - 1 - h);
   return bound > (1 << LBOUT);
 }
-template <int B, int E, int LO, int R, int LBIN, int LBOUT, bool FIX>
+template <int B, int E, int LO, int R, int LBIN, int LBOUT, bool FIX, bool PRE = false>
 __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
-                                           uint32_t lanePart, const TwM* __restrict__ itw, const NttConst& c) {
+                                           uint32_t lanePart, const TwM* __restrict__ itw, const NttConst& c,
+                                           const TwM* pf = nullptr) {
   using M = RoundMap<B, E, LO, R>;
   static_assert(LBIN + R <= 9, "words stay below 512q inside a round");
   const uint32_t four = opaque4();
@@ -204,7 +207,8 @@ __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, 
 #pragma unroll
         for (int k = 0; k < (1 << R); ++k) {
           if (k & d) continue;
-          gs_bfly_m(x[(g << R) + k], x[(g << R) + k + d], ld_tw(itw, base + (k >> (u + 1))), off, c, four);
+          const TwM w = PRE ? pf[(1 << (R - 1 - u)) - 1 + (k >> (u + 1))] : ld_tw(itw, base + (k >> (u + 1)));
+          gs_bfly_m(x[(g << R) + k], x[(g << R) + k + d], w, off, c, four);
         }
       }
       if constexpr (FIX) {
@@ -370,21 +374,40 @@ template <int E, bool FIX> __device__ __forceinline__ void reduce_out(uint64_t (
 // [LO, LO+R)), starting from registers already loaded with the first round's
 // map.  Ends with the lane holding the last round (LO = 0) map in registers,
 // i.e. 2^E consecutive elements, lazy values (see fwd_round).
-template <int B, int E, int LO, int R, bool FIX>
+//
+// PRE: a round's twiddles (2^R - 1 root powers per lane) are loaded ahead of the
+// LDS exchange in front of it, so that their latency runs beside the barrier and
+// not after it, and once per round instead of in two groups as registers allow.
+// HAVE: this round's are in pf.  Used where the registers it takes (84 -> 112 for
+// the whole 2^12, 95 for blocks) cost no occupancy that counts, the polymul of 2^10
+// and more: 2^12, one product, 12.7 -> 12.2 us; 512 x 8 limbs 196 -> 192; 2^10, 2048
+// x 8 limbs 171 -> 161; blocks at 2^15, 128 x 16 limbs, 582 -> 567.  The tensor's
+// and the key switch's blocks stand at 128 registers without it.
+template <int B, int E, int LO, int R, bool FIX, bool PRE = false, bool HAVE = false>
 __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
-                                                 uint32_t blockStart, const TwM* __restrict__ tw, const NttConst &c) {
+                                                 uint32_t blockStart, const TwM* __restrict__ tw, const NttConst &c,
+                                                 const TwM *pf = nullptr) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  fwd_round<B, E, LO, R, FIX>(x, logn, blockStart, lp, tw, c);
+  fwd_round<B, E, LO, R, FIX, HAVE>(x, logn, blockStart, lp, tw, c, pf);
   if constexpr (LO > 0) {
     constexpr int R2 = E;
     constexpr int LO2 = LO - R2;
     static_assert(LO2 >= 0, "rounds must tile the block");
+    using M2 = RoundMap<B, E, LO2, R2>;
+    TwM w[PRE ? (1 << R2) - 1 : 1];
+    if constexpr (PRE) {
+#pragma unroll
+      for (int u = 0; u < R2; ++u) {
+        const uint32_t base = ((1u << (logn - B)) << (B - LO2 - R2 + u)) + ((blockStart | M2::lane_part(tid)) >> (LO2 + R2 - u));
+#pragma unroll
+        for (int i = 0; i < (1 << u); ++i) w[(1 << u) - 1 + i] = ld_tw(tw, base + i);
+      }
+    }
     store_lds<B, E, LO, R>(x, lds, lp);
     __syncthreads();
-    using M2 = RoundMap<B, E, LO2, R2>;
     load_lds<B, E, LO2, R2>(x, lds, M2::lane_part(tid));
-    fwd_block_rounds<B, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, tw, c);
+    fwd_block_rounds<B, E, LO2, R2, FIX, PRE, PRE>(x, logn, lds, tid, blockStart, tw, c, w);
   }
 }
 
@@ -393,21 +416,31 @@ __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t
 // 2^ST words side by side.  Ends with the lane holding the last round's map
 // (covering [ST - Rlast, ST)); words enter below 16q and leave below 16q, or
 // are the transform's lazy outputs.
-template <int B, int ST, int E, int LO, int R, bool FIX>
+template <int B, int ST, int E, int LO, int R, bool FIX, bool PRE = false, bool HAVE = false>
 __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
                                                  uint32_t blockStart, const TwM* __restrict__ itw,
-                                                 const NttConst& c) {
+                                                 const NttConst& c, const TwM* pf = nullptr) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  inv_round<B, E, LO, R, 5, (LO + R < ST ? 5 : 4), FIX>(x, logn, blockStart, lp, itw, c);
+  inv_round<B, E, LO, R, 5, (LO + R < ST ? 5 : 4), FIX, HAVE>(x, logn, blockStart, lp, itw, c, pf);
   if constexpr (LO + R < ST) {
     constexpr int LO2 = LO + R;
     constexpr int R2 = (ST - LO2) < E ? (ST - LO2) : E;
+    using M2 = RoundMap<B, E, LO2, R2>;
+    constexpr bool AHEAD = PRE && R2 == E && !M2::LANE_LOW;
+    TwM w[AHEAD ? (1 << R2) - 1 : 1];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int u = 0; u < R2; ++u) {
+        const uint32_t base = ((1u << logn) >> (LO2 + u + 1)) + ((blockStart | M2::lane_part(tid)) >> (LO2 + u + 1));
+#pragma unroll
+        for (int i = 0; i < (1 << (R2 - 1 - u)); ++i) w[(1 << (R2 - 1 - u)) - 1 + i] = ld_tw(itw, base + i);
+      }
+    }
     store_lds<B, E, LO, R>(x, lds, lp);
     __syncthreads();
-    using M2 = RoundMap<B, E, LO2, R2>;
     load_lds<B, E, LO2, R2>(x, lds, M2::lane_part(tid));
-    inv_block_rounds<B, ST, E, LO2, R2, FIX>(x, logn, lds, tid, blockStart, itw, c);
+    inv_block_rounds<B, ST, E, LO2, R2, FIX, PRE, AHEAD>(x, logn, lds, tid, blockStart, itw, c, w);
   }
 }
 
@@ -874,6 +907,7 @@ template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV, bo
 __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, uint64_t out_off, uint32_t blockStart,
                                           const TwM *t, const NttConst &c, const MontLimb *mont, uint64_t *lds) {
   constexpr int NIN = ProdShape<MODE>::NIN, NOUT = ProdShape<MODE>::NOUT;
+  constexpr bool PRE = MODE == PROD_MUL && LOGN > 9;  // see fwd_block_rounds
   const TwM *it = t + (1u << LOGN);
   const uint32_t tid = threadIdx.x;
   using F = FwdFirst<ST, E>;
@@ -892,7 +926,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
       // from cache instead of being hoisted out of the loop into VGPRs
       const TwM *tp = opaque(t);
       load_global<B, E, F::LO, F::R, true>(v, pick_ptr(a.in, p) + in_off, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
-      fwd_block_rounds<B, E, F::LO, F::R, FIX>(v, LOGN, lds, tid, blockStart, tp, c);
+      fwd_block_rounds<B, E, F::LO, F::R, FIX, PRE>(v, LOGN, lds, tid, blockStart, tp, c);
       if constexpr (DO_INV) reduce_for_mont<E, FIX>(v, c);
       else reduce_out<E, FIX>(v, c);
     } else {
@@ -923,7 +957,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, uint64_t in_off, ui
     });
     if constexpr (DO_INV) {
       __syncthreads();  // earlier LDS reads of this workgroup are done
-      inv_block_rounds<B, ST, E, 0, E, FIX>(v, LOGN, lds, tid, blockStart, opaque(it), c);
+      inv_block_rounds<B, ST, E, 0, E, FIX, PRE>(v, LOGN, lds, tid, blockStart, opaque(it), c);
       if constexpr (ST == LOGN) reduce_out<E, FIX>(v, c);
       store_global<B, E, L::LO, L::R>(v, pick_ptr(a.out, o) + out_off, RoundMap<B, E, L::LO, L::R>::lane_part(tid));
     } else {
