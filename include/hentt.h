@@ -21,7 +21,8 @@
  *     lazy butterflies need).
  *
  * Memory and streams.  Every data pointer is a DEVICE pointer owned by the
- * caller, who keeps it alive until the work queued on `stream` completes.
+ * caller, who keeps it alive until the work queued on `stream` completes; the
+ * alignment of a word (8 bytes) is enough.
  * `stream` is a hipStream_t passed as void* (NULL = default stream).  Compute
  * calls only enqueue work: they never synchronise the host.  Tables are
  * owned by the library, immutable after creation, and may be shared across

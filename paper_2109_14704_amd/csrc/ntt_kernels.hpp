@@ -328,6 +328,12 @@ __device__ __forceinline__ void load_global_m0(uint64_t (&x)[1 << E], const uint
 // the block sits at LDS pair 8t + (k ^ (t mod 8)) (the map is its own
 // inverse), which puts the eight pairs one 8-lane group reads in eight
 // different 16-byte bank groups.  Ends with a barrier, like load_global_m0.
+//
+// Data need only be 8-byte aligned.  The 16-byte form moves 16-byte units, so
+// where src is not one (uniform per workgroup) four 4-byte loads (at four
+// times the instructions) fill the same layout dword by dword.  Taking
+// load_global_m0 there instead cost registers on the aligned path: 69 for 56
+// in the whole 2^11 and 2^12 inverse, 24 spilled in the persistent batch's.
 #ifndef HENTT_DMA_LOAD
 #define HENTT_DMA_LOAD 1
 #endif
@@ -340,11 +346,21 @@ __device__ __forceinline__ void load_global_m0_fresh(uint64_t (&x)[1 << E], cons
     constexpr uint32_t WAVE_WORDS = 64u << E;   // the words one wave moves
     const uint32_t wave = tid >> 6, lane = tid & 63;
     typedef __attribute__((address_space(3))) void lds_void;
+    if ((__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)src) & 15) == 0) {
 #pragma unroll
-    for (uint32_t i = 0; i < WAVE_WORDS / 128; ++i) {
-      const uint32_t win = wave * WAVE_WORDS + 128 * i;   // first word of this instruction's window
-      const uint32_t pair = win / 2 + lane;                  // LDS pair this lane fills
-      __builtin_amdgcn_global_load_lds(src + 2 * dma_swz(pair), (lds_void*)(lds + win), 16, 0, 0);
+      for (uint32_t i = 0; i < WAVE_WORDS / 128; ++i) {
+        const uint32_t win = wave * WAVE_WORDS + 128 * i;   // first word of this instruction's window
+        const uint32_t pair = win / 2 + lane;                  // LDS pair this lane fills
+        __builtin_amdgcn_global_load_lds(src + 2 * dma_swz(pair), (lds_void*)(lds + win), 16, 0, 0);
+      }
+    } else {
+#pragma unroll 1
+      for (uint32_t i = 0; i < WAVE_WORDS / 32; ++i) {
+        const uint32_t win = wave * WAVE_WORDS + 32 * i;    // 64 dwords: 16 pairs
+        const uint32_t pair = win / 2 + (lane >> 2);           // LDS pair this lane fills a quarter of
+        __builtin_amdgcn_global_load_lds((const uint32_t*)src + 4 * dma_swz(pair) + (lane & 3), (lds_void*)(lds + win), 4,
+                                         0, 0);
+      }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

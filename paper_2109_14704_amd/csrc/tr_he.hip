@@ -56,23 +56,16 @@ template <int LOGN> struct RsPlan {
 
 // Block pass of the inverse transform of `limbs` limbs from limb `first` on, read
 // where they lie (limb l of entry b at src + b src_sb + l N) into dst; the column
-// passes of the rescale and the key switch take the rest.  16-byte loads: words of
-// a source that is only 8-byte aligned are copied first (dst is the library's own
-// buffer).
+// passes of the rescale and the key switch take the rest.
 template <int LOGN>
-int inv_blocks_from(const Storage *s, uint32_t first, uint32_t limbs, const uint64_t *src, uint64_t src_sb,
+void inv_blocks_from(const Storage *s, uint32_t first, uint32_t limbs, const uint64_t *src, uint64_t src_sb,
                     uint64_t *dst, uint32_t batch, hipStream_t st) {
   constexpr int E = 3, ST = LOGN - two_pass_cols(LOGN), B = block_words(ST, E);
   const uint64_t sb = (uint64_t)limbs << LOGN;
-  InvIO io{src, dst, src_sb, sb};
-  if ((uintptr_t)src & 15) {
-    HIPCHK(hipMemcpy2DAsync(dst, sb * 8, src, src_sb * 8, sb * 8, batch, hipMemcpyDeviceToDevice, st));
-    io = InvIO{dst, dst, sb, sb};
-  }
+  const InvIO io{src, dst, src_sb, sb};
   LaunchTimer lt_("k_inv_blocks", LOGN, st);
   hipLaunchKernelGGL((k_inv_blocks<LOGN, ST, B, E>), dim3((batch * limbs) << (LOGN - B)), dim3(1 << (B - E)), 0, st, io,
                      s->d_twm + (size_t)first * 2 * (1u << LOGN), s->d_nc + first, batch, limbs);
-  return HENTT_OK;
 }
 
 // The last limb of every batch entry goes through `last`, [batch][N] words of the
@@ -103,8 +96,7 @@ template <int LOGN> int launch_rescale_ntt(RsArgs a, Storage *s, uint64_t *last,
     constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, P::EC>(), lanes = cols_lanes<P::EC>();
     const dim3 g(units * tiles), blk(lanes);
     if ((uint64_t)units * tiles * (lanes / 64) <= kRsWaves) {
-      const int rc = inv_blocks_from<LOGN>(s, a.L, 1, cl, sb, last, a.batch, st);
-      if (rc) return rc;
+      inv_blocks_from<LOGN>(s, a.L, 1, cl, sb, last, a.batch, st);
       LaunchTimer lt_("k_rs_cols", LOGN, st);
       hipLaunchKernelGGL((k_rs_cols<LOGN, P::EC, true>), g, blk, 0, st, a, s->d_twm, s->d_nc);
     } else {
@@ -192,8 +184,7 @@ template <int LOGN> int launch_keyswitch(KsArgs a, Storage *s, uint64_t *d, hipS
     LaunchTimer lt_("k_ks_whole", LOGN, st);
     hipLaunchKernelGGL((k_ks_whole<LOGN, whole_e(LOGN)>), dim3(a.batch * L1), dim3(1 << (LOGN - whole_e(LOGN))), 0, st, a, s->d_twm, s->d_nc);
   } else {
-    const int rc = inv_blocks_from<LOGN>(s, 0, a.l, a.c + 2 * P2, 3 * P2, d, a.batch, st);
-    if (rc) return rc;
+    inv_blocks_from<LOGN>(s, 0, a.l, a.c + 2 * P2, 3 * P2, d, a.batch, st);
     constexpr uint32_t tiles = cols_blocks_per_unit<LOGN, P::EC>();
     a.col_splits = col_splits<P::EC>((uint64_t)a.batch * a.l * tiles, L1);
     {

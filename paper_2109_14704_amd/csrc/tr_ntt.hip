@@ -125,12 +125,6 @@ int run_transform(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_
 int run_inverse_from(const hentt_tables *t, const uint64_t *src, uint64_t src_sb, uint64_t *dst, uint32_t batch,
                      hipStream_t st) {
   const uint64_t sb = (uint64_t)t->limbs << t->s->log_n;
-  // the inverse kernels load 16 bytes per lane: words of a source that is only
-  // 8-byte aligned are copied first (dst is the library's own buffer)
-  if ((uintptr_t)src & 15) {
-    HIPCHK(hipMemcpy2DAsync(dst, sb * 8, src, src_sb * 8, sb * 8, batch, hipMemcpyDeviceToDevice, st));
-    return run(t, InvIO{dst, dst, sb, sb}, batch, st, true);
-  }
   return run(t, InvIO{src, dst, src_sb, sb}, batch, st, true);
 }
 
