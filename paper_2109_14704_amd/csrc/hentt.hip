@@ -144,7 +144,7 @@ int pool_get(size_t bytes, hipStream_t stream, void **out) {
   void *p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
   if (e != hipSuccess) {
-    g_last_hip = (int)e;
+    hip_note(e);
     return HENTT_ENOMEM;
   }
   g_pool.push_back({p, bytes, dev, stream, true});
@@ -507,7 +507,7 @@ int plan_build(const hentt_job *jobs, uint32_t njobs, int dir, hentt_batch_plan 
   }
   if (e != hipSuccess) {
     plan_free(p);
-    g_last_hip = (int)e;
+    hip_note(e);
     return e == hipErrorOutOfMemory ? HENTT_ENOMEM : HENTT_EHIP;
   }
   if (p->nunits) {
@@ -692,7 +692,7 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     release(s);
-    g_last_hip = (int)e;
+    hip_note(e);
     return e == hipErrorOutOfMemory ? HENTT_ENOMEM : HENTT_EHIP;
   }
   hentt_tables *h = new (std::nothrow) hentt_tables{s, limbs};

@@ -24,8 +24,16 @@ using namespace hentt;
 
 extern thread_local int g_last_hip;
 
-inline int hip_fail(hipError_t e) {
+// Notes a failed HIP call for hentt_last_hip_error and takes it out of the
+// runtime's own last-error slot: it is reported by the status here, and left
+// there it would be taken for a failure of the next launch (the checks after
+// launches read that slot), of a retry in the same call or of the caller's own.
+inline void hip_note(hipError_t e) {
   g_last_hip = (int)e;
+  (void)hipGetLastError();
+}
+inline int hip_fail(hipError_t e) {
+  hip_note(e);
   return HENTT_EHIP;
 }
 #define HIPCHK(x)                              \
