@@ -149,6 +149,10 @@ inline ColArgs col_args(uint64_t *x, uint64_t sb) {
   return a;
 }
 
+// Work-items of one launch: HIP refuses 2^32 and more; half of that is far more than
+// fills the chip, so calls beyond it run as several launches.
+constexpr uint64_t kMaxItems = 1ull << 31;
+
 #define HENTT_SIZES(M) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16) M(17)
 
 // ------------------------------------------------------------ dispatch

@@ -284,12 +284,18 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
 int run_matmul(const hentt_tables *t, const uint64_t *A, const uint64_t *B, uint64_t *C, uint32_t m, uint32_t n,
                uint32_t k, hipStream_t st) {
   const uint32_t ln = t->s->log_n, L = t->limbs;
+  const uint64_t P = (uint64_t)L << ln;
+  if ((uint64_t)m * n * L * (((1ull << ln) + 2047) >> 11) > 0x7fffffffu) return HENTT_EINVAL;  // as the header states
   const uint32_t tiles = ln > 8 ? 1u << (ln - 8) : 1u, runs = (n + CT_J - 1) / CT_J;
-  const uint64_t groups = (uint64_t)L * runs * tiles, grid = (groups + 7) / 8 * 8 * m;
-  if ((uint64_t)m * n * L * ((1ull << ln) + 2047 >> 11) > 0x7fffffffu || grid > 0x7fffffffu) return HENTT_EINVAL;
-  const MatmulArgs p{A, B, C, m, n, k, L, ln, tiles, runs, (uint32_t)groups};
-  LaunchTimer lt_("k_ct_matmul", (int)ln, st);
-  hipLaunchKernelGGL(k_ct_matmul, dim3((uint32_t)grid), dim3(256), 0, st, p, t->s->d_nc, t->s->d_mat);
+  const uint64_t groups = (uint64_t)L * runs * tiles, per_row = (groups + 7) / 8 * 8;
+  if (per_row > kMaxItems / 256) return HENTT_EINVAL;
+  const uint32_t rows = (uint32_t)std::min<uint64_t>(m, kMaxItems / 256 / per_row);
+  for (uint64_t i = 0; i < m; i += rows) {
+    const uint32_t mi = (uint32_t)std::min<uint64_t>(rows, m - i);
+    const MatmulArgs p{A + i * k * 2 * P, B, C + i * n * 3 * P, mi, n, k, L, ln, tiles, runs, (uint32_t)groups};
+    LaunchTimer lt_("k_ct_matmul", (int)ln, st);
+    hipLaunchKernelGGL(k_ct_matmul, dim3((uint32_t)(per_row * mi)), dim3(256), 0, st, p, t->s->d_nc, t->s->d_mat);
+  }
   HIPCHK(hipGetLastError());
   return HENTT_OK;
 }
