@@ -152,6 +152,14 @@ inline ColArgs col_args(uint64_t *x, uint64_t sb) {
 // Work-items of one launch: HIP refuses 2^32 and more; half of that is far more than
 // fills the chip, so calls beyond it run as several launches.
 constexpr uint64_t kMaxItems = 1ull << 31;
+// Batch entries (of `limbs` limbs of N = 2^log_n) that one launch sequence of the
+// transforms, the products and the rescale takes: 2^32 words of an operand.  Their
+// kernels hold at least 4 words per lane, and no array of 2^32 words fills less than
+// the chip by far.
+inline uint32_t batch_piece(uint32_t log_n, uint32_t limbs, uint32_t batch) {
+  const uint64_t piece = (1ull << 32) / ((uint64_t)limbs << log_n);
+  return piece < batch ? (uint32_t)piece : batch;
+}
 
 #define HENTT_SIZES(M) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16) M(17)
 

@@ -233,10 +233,16 @@ int run_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint32_
     HIPCHK(hipGetLastError());
     return HENTT_OK;
   }
+  const uint32_t piece = batch_piece(ln, L, batch);
   void *tl = nullptr;
-  rc = pool_get((size_t)batch * N * 8, st, &tl);
+  rc = pool_get((size_t)piece * N * 8, st, &tl);
   if (rc) return rc;
-  rc = k_rs_table[ln - HENTT_LOG_N_MIN](a, s, (uint64_t *)tl, st);
+  for (uint64_t b = 0; b < batch && !rc; b += piece) {
+    a.c = c + (b * level << ln);
+    a.out = out + (b * L << ln);
+    a.batch = (uint32_t)std::min<uint64_t>(piece, batch - b);
+    rc = k_rs_table[ln - HENTT_LOG_N_MIN](a, s, (uint64_t *)tl, st);
+  }
   pool_put(tl);
   return rc;
 }

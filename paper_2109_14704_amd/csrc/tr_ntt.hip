@@ -7,6 +7,8 @@
 // the default; the autotuner may select another per (operation, N, shape
 // class), where the shape class groups the number of (batch entry, limb)
 // units of a call.
+#include <algorithm>
+
 #include "runtime.hpp"
 
 namespace hentt_rt {
@@ -112,7 +114,10 @@ static int run(const hentt_tables *t, const InvIO &io, uint32_t batch, hipStream
   const TrList &l = k_tr[ln - HENTT_LOG_N_MIN];
   uint32_t c = tune_choice(inv ? HENTT_OP_INV : HENTT_OP_FWD, ln, (uint64_t)batch * t->limbs);
   if (c >= l.n) c = 0;
-  l.c[c].fn(t, io, batch, inv, st);
+  const uint32_t piece = batch_piece(ln, t->limbs, batch);
+  for (uint64_t b = 0; b < batch; b += piece)
+    l.c[c].fn(t, InvIO{io.src + b * io.src_sb, io.dst + b * io.dst_sb, io.src_sb, io.dst_sb},
+              (uint32_t)std::min<uint64_t>(piece, batch - b), inv, st);
   HIPCHK(hipGetLastError());
   return HENTT_OK;
 }

@@ -1,6 +1,8 @@
 // Compiled instances of the dyadic product and the fused negacyclic polymul at
 // every N (candidate 0 is the default and serves every domain combination),
 // and the common entry of both product kinds.
+#include <algorithm>
+
 #include "prod_launch.hpp"
 
 namespace hentt_rt {
@@ -44,12 +46,18 @@ int run_prod(const hentt_tables *t, int mode, const ProdArgs &pa, uint32_t batch
   const int nin = mode == PROD_MUL ? 2 : 4;
   const uint64_t NL = (uint64_t)t->limbs << ln;
   const ProdCand &c = prod_select(mode, ln, (uint64_t)batch * t->limbs, in_coeff && out_coeff);
+  const uint32_t piece = batch_piece(ln, t->limbs, batch);
   void *ws = nullptr;
   if (in_coeff && c.pec > 0) {
-    int rc = pool_get((size_t)nin * batch * NL * 8ull, st, &ws);
+    int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws);
     if (rc) return rc;
   }
-  c.fn(t, pa, batch, in_coeff, out_coeff, (uint64_t *)ws, st);
+  for (uint64_t b = 0; b < batch; b += piece) {
+    ProdArgs pb = pa;
+    for (int p = 0; p < nin; ++p) pb.in[p] += b * pa.in_sb;
+    for (int o = 0; o < (mode == PROD_MUL ? 1 : 3); ++o) pb.out[o] += b * pa.out_sb;
+    c.fn(t, pb, (uint32_t)std::min<uint64_t>(piece, batch - b), in_coeff, out_coeff, (uint64_t *)ws, st);
+  }
   hipError_t e = hipGetLastError();
   if (ws) pool_put(ws);
   if (e != hipSuccess) return hip_fail(e);

@@ -34,6 +34,46 @@ def zero_elsewhere(t, at):
     return all(int(torch.count_nonzero(flat[i:i + (1 << 30)])) == 0 for i in range(0, flat.numel(), 1 << 30))
 
 
+def test_transforms_of_2_34_words(gpu, room):
+    import paper_2109_14704_amd as H
+    log_n, batch = 10, 1 << 24           # 128 GiB, 4 words per lane
+    print("case transforms of 2^34 words", flush=True)
+    room(128)
+    mods = primes(55, log_n)
+    at = [0, (1 << 22) - 1, 1 << 22, 3 << 22, batch - 1]
+    x = words(np.random.default_rng(1), (len(at), 1, 1 << log_n), mods)
+    d = torch.zeros((batch, 1, 1 << log_n), dtype=torch.int64, device=gpu)
+    put(d, at, x, gpu)
+    t = H.Tables(log_n, mods)
+    H.ntt_fwd(t, d)
+    assert np.array_equal(host(d[at]), oracle.batch_ntt(x, mods, +1))
+    H.ntt_inv(t, d)
+    assert np.array_equal(host(d[at]), x)
+    assert zero_elsewhere(d, at)
+
+
+def test_polymul_and_rescale_in_pieces(gpu, room):
+    import paper_2109_14704_amd as H
+    log_n, batch = 9, (1 << 22) + 5       # two limbs: more than 2^32 words an operand
+    print("case polymul and rescale of more than 2^32 words", flush=True)
+    room(100)
+    mods = primes(55, log_n) + primes(58, log_n)
+    rng = np.random.default_rng(2)
+    at = [0, (1 << 22) - 1, 1 << 22, batch - 1]
+    x, y = (words(rng, (len(at), 2, 1 << log_n), mods) for _ in range(2))
+    a, b = (torch.zeros((batch, 2, 1 << log_n), dtype=torch.int64, device=gpu) for _ in range(2))
+    put(a, at, x, gpu)
+    put(b, at, y, gpu)
+    t = H.Tables(log_n, mods)
+    out = H.polymul(t, a, b)
+    assert np.array_equal(host(out[at]), oracle.batch_polymul(x, y, mods))
+    assert zero_elsewhere(out, at)
+    del b, out
+    out = H.rescale(t, a, ntt=True)
+    assert np.array_equal(host(out[at]), oracle.batch_rescale_ntt(x, mods))
+    assert zero_elsewhere(out, at)
+
+
 def test_matmul_of_2_32_coefficients(gpu, room):
     import paper_2109_14704_amd as H
     log_n, m = 13, 1 << 19                # A 64 GiB, C 96 GiB
