@@ -205,7 +205,9 @@ int hentt_dyadic_mul(const hentt_tables *t, const uint64_t *a, const uint64_t *b
  * a, b over [batch][limbs][N] (section II-B), fused so that the NTT-domain
  * values never leave the chip.  out must not overlap a or b (HENTT_EINVAL).
  * For N > 2^12 the forward column pass writes a workspace of 2 batch limbs N
- * words taken from the library's pool (allocated on first need, reused). */
+ * words (of at most 2^32-word pieces of the batch) taken from the library's pool
+ * (allocated on first need, reused); N = 2^13 runs without one, slower, under
+ * stream capture while the pool has none and where it cannot be allocated. */
 int hentt_polymul(const hentt_tables *t, const uint64_t *a, const uint64_t *b, uint64_t *out, uint32_t batch,
                   void *stream);
 

@@ -120,7 +120,7 @@ ApiRange::~ApiRange() {
   if (on) roctx().pop();
 }
 
-int pool_get(size_t bytes, hipStream_t stream, void **out) {
+int pool_get(size_t bytes, hipStream_t stream, void **out, bool grow) {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(g_pool_mu);
@@ -136,6 +136,7 @@ int pool_get(size_t bytes, hipStream_t stream, void **out) {
     *out = g_pool[best].ptr;
     return HENTT_OK;
   }
+  if (!grow) return HENTT_ENOMEM;
   if (const uint64_t cap = pool_cap()) {
     uint64_t held = 0;
     for (auto &pe : g_pool) held += pe.bytes;

@@ -69,8 +69,9 @@ void release(Storage *s);
 // Device buffers reused by capacity (the memory cache of section III-C-1); see
 // hentt.hip.  pool_put returns a buffer right after the launches that use it
 // are enqueued on `stream`: later users of the same entry enqueue on the same
-// stream, so stream order keeps reuse after completion.
-int pool_get(size_t bytes, hipStream_t stream, void **out);
+// stream, so stream order keeps reuse after completion.  Without `grow` only a
+// buffer that the pool holds already is given (HENTT_ENOMEM if there is none).
+int pool_get(size_t bytes, hipStream_t stream, void **out, bool grow = true);
 void pool_put(void *p);
 
 // ------------------------------------------------------------ launch timing

@@ -40,23 +40,40 @@ const ProdCand &prod_select(int mode, uint32_t log_n, uint64_t units, bool fused
   return c[i < n ? i : 0];
 }
 
+// The instance that needs no workspace, for the fused product of the sizes that
+// have one beside a two-pass default (2^13), else null.
+static const ProdCand *whole_instance(int mode, uint32_t log_n) {
+  uint32_t n = 0;
+  const ProdCand *c = prod_candidates(mode, log_n, &n);
+  for (uint32_t i = 0; i < n; ++i)
+    if (c[i].pec == 0) return c + i;
+  return nullptr;
+}
+
 int run_prod(const hentt_tables *t, int mode, const ProdArgs &pa, uint32_t batch, bool in_coeff, bool out_coeff,
              hipStream_t st) {
   const uint32_t ln = t->s->log_n;
   const int nin = mode == PROD_MUL ? 2 : 4;
   const uint64_t NL = (uint64_t)t->limbs << ln;
-  const ProdCand &c = prod_select(mode, ln, (uint64_t)batch * t->limbs, in_coeff && out_coeff);
+  const ProdCand *c = &prod_select(mode, ln, (uint64_t)batch * t->limbs, in_coeff && out_coeff);
   const uint32_t piece = batch_piece(ln, t->limbs, batch);
   void *ws = nullptr;
-  if (in_coeff && c.pec > 0) {
-    int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws);
-    if (rc) return rc;
+  if (in_coeff && c->pec > 0) {
+    // Where a whole instance exists, the workspace only makes the call faster: it is
+    // not allocated into a capture (which an allocation would end), and done without
+    // when it cannot be had.
+    const ProdCand *whole = out_coeff ? whole_instance(mode, ln) : nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (whole && hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws, cap == hipStreamCaptureStatusNone);
+    if (rc == HENTT_ENOMEM && whole) c = whole;
+    else if (rc) return rc;
   }
   for (uint64_t b = 0; b < batch; b += piece) {
     ProdArgs pb = pa;
     for (int p = 0; p < nin; ++p) pb.in[p] += b * pa.in_sb;
     for (int o = 0; o < (mode == PROD_MUL ? 1 : 3); ++o) pb.out[o] += b * pa.out_sb;
-    c.fn(t, pb, (uint32_t)std::min<uint64_t>(piece, batch - b), in_coeff, out_coeff, (uint64_t *)ws, st);
+    c->fn(t, pb, (uint32_t)std::min<uint64_t>(piece, batch - b), in_coeff, out_coeff, (uint64_t *)ws, st);
   }
   hipError_t e = hipGetLastError();
   if (ws) pool_put(ws);
