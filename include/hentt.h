@@ -66,7 +66,9 @@ typedef struct hentt_tables hentt_tables;
  * root powers W and root power quotients W' = floor(W 2^64 / q)).
  * log_n in [HENTT_LOG_N_MIN, HENTT_LOG_N_MAX]; moduli_host: `limbs` host
  * words.  Builds on the host, uploads on `stream`, and waits for the upload.
- * Device footprint: 32 N bytes per limb plus 64 bytes per limb.
+ * Device footprint: 32 N + 352 bytes per limb; as much as the first term again
+ * once the (W, W') pairs have been asked for (hentt_tables_device_ptrs, the kernel-design
+ * ladder), and the per-level constants of the rescale and the key switch.
  * *out receives a handle the caller releases with hentt_tables_destroy. */
 int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_host, void *stream,
                         hentt_tables **out);
@@ -88,7 +90,10 @@ int hentt_tables_info(const hentt_tables *t, uint32_t *log_n, uint32_t *limbs);
  * points at limb 0's forward table (W = psi^brv(k)) and inv at limb 0's
  * inverse table (W = psi^-brv(k)); limb l's tables start 4 N l words later.
  * moduli points at [limbs] records of 12 uint64 words whose first word is q
- * (the rest are the library's reduction constants). */
+ * (the rest are the library's reduction constants).  The library's own transforms
+ * read another form of the root powers: the pairs are made on the first call that
+ * asks for fwd or inv (a synchronous upload on a stream of its own) and stay until
+ * the storage is released.  A null argument is not written. */
 int hentt_tables_device_ptrs(const hentt_tables *t, const uint64_t **fwd, const uint64_t **inv,
                              const uint64_t **moduli);
 

@@ -45,6 +45,50 @@ void release(Storage *s) {
   }
 }
 
+// The Shoup pairs are read by the design ladder and by callers of the ABI's table
+// query alone, so they are made for the first of those and not with the tables.
+// Nothing of it runs on the caller's stream: a stream of its own, and allocation
+// that another stream's capture does not refuse.
+int shoup_pairs(Storage *s, const Tw **out) try {
+  std::lock_guard<std::mutex> lk(s->rs_mu);
+  if (!s->d_tw) {
+    const uint32_t N = 1u << s->log_n;
+    std::vector<Tw> tw((size_t)s->limbs * 2 * N);
+    std::vector<uint64_t> pw(N), ipw(N);
+    for (uint32_t l = 0; l < s->limbs; ++l) {
+      Tw *f = &tw[(size_t)l * 2 * N];
+      LimbConst lc, lcm;
+      MontLimb mont;
+      if (!host::make_limb(s->moduli[l], (int)s->log_n, f, f + N, lc, lcm, mont, pw.data(), ipw.data()))
+        return HENTT_EMODULUS;
+    }
+    int cur = 0;
+    (void)hipGetDevice(&cur);
+    (void)hipSetDevice(s->device);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipStream_t st = nullptr;
+    Tw *d = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipMalloc(&d, tw.size() * sizeof(Tw));
+    if (e == hipSuccess) e = hipMemcpyAsync(d, tw.data(), tw.size() * sizeof(Tw), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (st) (void)hipStreamDestroy(st);
+    if (e != hipSuccess && d) (void)hipFree(d);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipSetDevice(cur);
+    if (e != hipSuccess) {
+      hip_note(e);
+      return e == hipErrorOutOfMemory ? HENTT_ENOMEM : HENTT_EHIP;
+    }
+    s->d_tw = d;
+  }
+  *out = s->d_tw;
+  return HENTT_OK;
+} catch (const std::bad_alloc &) {  // the host copy
+  return HENTT_ENOMEM;
+}
+
 // ------------------------------------------------------------ workspace pool
 // Device buffers reused by capacity: a request takes the smallest free buffer
 // of its device and stream that is large enough, else allocates (the memory
@@ -186,18 +230,18 @@ void prof_record(const char *name, int log_n, hipEvent_t a, hipEvent_t b) {
 
 namespace {
 
-// The transforms' tables from the Shoup pairs: W to (W 2^30 mod q, W 2^62 mod q),
-// split at bit 30.  One lane per entry, a workgroup within one limb (2N >= 128
-// entries per limb).
-__global__ __launch_bounds__(64) void k_tables_m(const Tw *__restrict__ tw, TwM *__restrict__ out,
-                                                 const NttConst *__restrict__ nc, uint32_t log_n) {
+// The transforms' tables from the Shoup pairs, in place: (W, W') to (W 2^30 mod q,
+// W 2^62 mod q), split at bit 30.  One lane per entry, a workgroup within one limb
+// (2N >= 128 entries per limb).
+__global__ __launch_bounds__(64) void k_tables_m(TwM *__restrict__ t, const NttConst *__restrict__ nc, uint32_t log_n) {
   const uint32_t i = blockIdx.x * 64 + threadIdx.x;
   const NttConst c = nc[(blockIdx.x * 64) >> (log_n + 1)];
-  const uint64_t w = tw[i].w, lo = (1ull << 30) - 1;
+  const uint64_t w = (uint64_t)t[i].a1 << 32 | t[i].a0, lo = (1ull << 30) - 1;
   const uint64_t a = mulmod(w, (1ull << 30) % c.q, c.q, c.mu, c.k);
   const uint64_t b = mulmod(w, (1ull << 62) % c.q, c.q, c.mu, c.k);
-  out[i] = TwM{(uint32_t)(a & lo), (uint32_t)(a >> 30), (uint32_t)(b & lo), (uint32_t)(b >> 30)};
+  t[i] = TwM{(uint32_t)(a & lo), (uint32_t)(a >> 30), (uint32_t)(b & lo), (uint32_t)(b >> 30)};
 }
+static_assert(sizeof(TwM) == sizeof(Tw), "k_tables_m converts in place");
 
 }  // namespace
 
@@ -668,10 +712,9 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   s->moduli.assign(moduli_host, moduli_host + limbs);
   (void)hipGetDevice(&s->device);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = hipMalloc(&s->d_tw, tw.size() * sizeof(Tw));
+  hipError_t e = hipMalloc(&s->d_twm, tw.size() * sizeof(TwM));
   if (e == hipSuccess) e = hipMalloc(&s->d_lc, lc.size() * sizeof(LimbConst));
-  if (e == hipSuccess) e = hipMemcpyAsync(s->d_tw, tw.data(), tw.size() * sizeof(Tw), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMalloc(&s->d_twm, tw.size() * sizeof(TwM));
+  if (e == hipSuccess) e = hipMemcpyAsync(s->d_twm, tw.data(), tw.size() * sizeof(Tw), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMalloc(&s->d_nc, limbs * sizeof(NttConst));
   if (e == hipSuccess) e = hipMalloc(&s->d_ncm, limbs * sizeof(NttConst));
   if (e == hipSuccess) e = hipMalloc(&s->d_mont, mont.size() * sizeof(MontLimb));
@@ -687,7 +730,7 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   if (e == hipSuccess)
     e = hipMemcpyAsync(s->d_mont, mont.data(), mont.size() * sizeof(MontLimb), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_tables_m, dim3(limbs * 2 * N / 64), dim3(64), 0, st, s->d_tw, s->d_twm, s->d_nc, log_n);
+    hipLaunchKernelGGL(k_tables_m, dim3(limbs * 2 * N / 64), dim3(64), 0, st, s->d_twm, s->d_nc, log_n);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -733,9 +776,14 @@ int hentt_tables_device_ptrs(const hentt_tables *t, const uint64_t **fwd, const 
                              const uint64_t **moduli) {
   if (!t) return HENTT_EINVAL;
   const size_t N = 1u << t->s->log_n;
-  // per limb: fwd pairs then inv pairs; callers index limb l at l * 2N pairs
-  if (fwd) *fwd = (const uint64_t *)t->s->d_tw;
-  if (inv) *inv = (const uint64_t *)(t->s->d_tw + N);
+  if (fwd || inv) {
+    // per limb: fwd pairs then inv pairs; callers index limb l at l * 2N pairs
+    const Tw *tw = nullptr;
+    const int rc = shoup_pairs(t->s, &tw);
+    if (rc) return rc;
+    if (fwd) *fwd = (const uint64_t *)tw;
+    if (inv) *inv = (const uint64_t *)(tw + N);
+  }
   if (moduli) *moduli = (const uint64_t *)t->s->d_lc;
   return HENTT_OK;
 }

@@ -49,7 +49,7 @@ inline int hip_fail(hipError_t e) {
 struct Storage {
   std::atomic<int> refs{1};
   uint32_t log_n = 0, limbs = 0;
-  Tw *d_tw = nullptr;          // [limbs][2][N] Shoup pairs (the ABI's table views, the design ladder)
+  Tw *d_tw = nullptr;          // [limbs][2][N] Shoup pairs, once something asked for them (shoup_pairs)
   LimbConst *d_lc = nullptr;   // [limbs]
   TwM *d_twm = nullptr;        // [limbs][2][N] the transforms' tables
   NttConst *d_nc = nullptr;    // [limbs]
@@ -58,12 +58,15 @@ struct Storage {
   MatLimb *d_mat = nullptr;    // [limbs] constants of the matrix product
   std::vector<uint64_t> moduli;
   int device = 0;
-  std::mutex rs_mu;                  // rescale and key-switch constants per level, made on first use
+  std::mutex rs_mu;                  // what is made on first use: d_tw, and the constants per level of
+                                     // the rescale and the key switch
   std::map<uint32_t, RsLimb *> rs;   // per level (limb count)
   std::map<uint32_t, KsLimb *> ks;   // per level (limb count, the last one the special prime)
 };
 void retain(Storage *s);
 void release(Storage *s);
+// The (W, W') pairs of a storage, made on the first call (synchronous).
+int shoup_pairs(Storage *s, const Tw **out);
 
 // ------------------------------------------------------------ workspace pool
 // Device buffers reused by capacity (the memory cache of section III-C-1); see

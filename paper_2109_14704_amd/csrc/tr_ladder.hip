@@ -198,13 +198,13 @@ namespace {
 // of 2048 words with radix-2 rounds, one stage per LDS exchange); and staged
 // transforms whose LDS rounds are radix-4, -8 or -16 on blocks of 4096 words
 // (the paper's work-group tile) after one radix-8 column pass.
-void launch_naive_stages(const hentt_tables *t, uint64_t *x, uint64_t units, uint32_t s0, uint32_t s1,
+void launch_naive_stages(const hentt_tables *t, const Tw *tw, uint64_t *x, uint64_t units, uint32_t s0, uint32_t s1,
                          hipStream_t st) {
   const uint32_t ln = t->s->log_n;
   const uint64_t grid = ((units << (ln - 1)) + 255) / 256;
   for (uint32_t s = s0; s < s1; ++s) {
     LaunchTimer lt_("k_naive_stage", (int)ln, st);
-    hipLaunchKernelGGL(k_naive_stage, dim3((uint32_t)grid), dim3(256), 0, st, x, t->s->d_tw, t->s->d_lc,
+    hipLaunchKernelGGL(k_naive_stage, dim3((uint32_t)grid), dim3(256), 0, st, x, tw, t->s->d_lc,
                        (uint32_t)units, t->limbs, ln, s);
   }
 }
@@ -216,12 +216,12 @@ template <int E> void launch_staged15(const hentt_tables *t, uint64_t *x, uint32
   { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_twm, t->s->d_nc, batch, L); }
 }
 
-template <int S> void launch_simd15(const hentt_tables *t, uint64_t *x, uint64_t units, uint32_t batch,
+template <int S> void launch_simd15(const hentt_tables *t, const Tw *tw, uint64_t *x, uint64_t units, uint32_t batch,
                                    hipStream_t st) {
-  launch_naive_stages(t, x, units, 0, 4, st);
+  launch_naive_stages(t, tw, x, units, 0, 4, st);
   LaunchTimer lt_(S == 1 ? "k_fwd_simd1" : S == 2 ? "k_fwd_simd2" : "k_fwd_simd4", 15, st);
   hipLaunchKernelGGL((k_fwd_simd<15, S>), dim3((uint32_t)(units << 4)), dim3(SimdPlan<S>::LANES), 0, st, x,
-                     t->s->d_tw, t->s->d_lc, batch, t->limbs);
+                     tw, t->s->d_lc, batch, t->limbs);
 }
 
 }  // namespace
@@ -229,13 +229,16 @@ template <int S> void launch_simd15(const hentt_tables *t, uint64_t *x, uint64_t
 int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int variant, hipStream_t st) {
   const uint32_t ln = t->s->log_n, L = t->limbs;
   const uint64_t units = (uint64_t)batch * L;
+  if (variant == HENTT_VARIANT_LIBRARY) return run_transform(t, x, batch, st, false);
+  if (variant < 0 || variant > HENTT_VARIANT_SIMD4 || (variant != HENTT_VARIANT_NAIVE && ln != 15)) return HENTT_EINVAL;
+  const Tw *tw = nullptr;
+  const int rc = shoup_pairs(t->s, &tw);
+  if (rc) return rc;
   switch (variant) {
-    case HENTT_VARIANT_LIBRARY:
-      return run_transform(t, x, batch, st, false);
     case HENTT_VARIANT_NAIVE: {
       const uint64_t grid = ((units << (ln - 1)) + 255) / 256, words = units << ln;
       if (grid > 0x7fffffffu || (words + 255) / 256 > 0x7fffffffu || units > 0xffffffffu) return HENTT_EINVAL;
-      launch_naive_stages(t, x, units, 0, ln, st);
+      launch_naive_stages(t, tw, x, units, 0, ln, st);
       {
         LaunchTimer lt_("k_reduce8q", (int)ln, st);
         hipLaunchKernelGGL(k_reduce8q, dim3((uint32_t)((words + 255) / 256)), dim3(256), 0, st, x, t->s->d_lc, words, L,
@@ -245,7 +248,7 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
     }
     case HENTT_VARIANT_STAGED_R2:
       if (ln != 15 || ((units << 14) + 255) / 256 > 0x7fffffffu) return HENTT_EINVAL;
-      launch_naive_stages(t, x, units, 0, 4, st);
+      launch_naive_stages(t, tw, x, units, 0, 4, st);
       {
         LaunchTimer lt_("k_fwd_blocks_r2", 15, st);
         hipLaunchKernelGGL((k_fwd_blocks<15, 11, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x,
@@ -256,9 +259,9 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
     case HENTT_VARIANT_SIMD2:
     case HENTT_VARIANT_SIMD4:
       if (ln != 15 || ((units << 14) + 255) / 256 > 0x7fffffffu) return HENTT_EINVAL;
-      if (variant == HENTT_VARIANT_SIMD1) launch_simd15<1>(t, x, units, batch, st);
-      else if (variant == HENTT_VARIANT_SIMD2) launch_simd15<2>(t, x, units, batch, st);
-      else launch_simd15<4>(t, x, units, batch, st);
+      if (variant == HENTT_VARIANT_SIMD1) launch_simd15<1>(t, tw, x, units, batch, st);
+      else if (variant == HENTT_VARIANT_SIMD2) launch_simd15<2>(t, tw, x, units, batch, st);
+      else launch_simd15<4>(t, tw, x, units, batch, st);
       break;
     case HENTT_VARIANT_STAGED_R4:
     case HENTT_VARIANT_STAGED_R8:
