@@ -500,8 +500,8 @@ def bench_ladder(args):
         x[:, l].copy_(torch.randint(0, q, (polys, n), generator=gen, device="cuda:0", dtype=torch.int64))
     coeffs = polys * L * n
     from paper_2109_14704_amd import roofline as R
-    tw = R.transform_work(n, polys * L)
-    one = R.Work(16.0 * coeffs) + tw
+    one = R.Work(16.0 * coeffs) + R.transform_work(n, polys * L)
+    rung = R.Work(16.0 * coeffs) + R.transform_work(n, polys * L, valu=R.VALU_BFLY_SHOUP)  # every design but the library
     designs = [(H.VARIANT_NAIVE, "naive radix-2, one global-memory launch per stage"),
                (H.VARIANT_STAGED_R2, "4 naive global stages + LDS blocks of 2048, radix-2 rounds"),
                (H.VARIANT_SIMD1, "SIMD(64,64): radix-2 LDS stages to gap 128, wave shuffles for gaps 64..1, 1 slot"),
@@ -531,7 +531,7 @@ def bench_ladder(args):
         b.record()
         torch.cuda.synchronize()
         ms = a.elapsed_time(b) / k
-        rl = R.roof(one, ms / 1e3)
+        rl = R.roof(one if v == H.VARIANT_LIBRARY else rung, ms / 1e3)
         rows.append({"variant": v, "design": desc, "ms": round(ms, 4), "gcoeff_s": round(coeffs / ms / 1e6, 3),
                      "frac": rl["frac"], "bound": rl["bound"], "valu_frac": rl["valu"]["frac"]})
     base = rows[0]["ms"]

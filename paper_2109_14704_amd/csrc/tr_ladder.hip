@@ -41,6 +41,99 @@ __global__ __launch_bounds__(256) void k_reduce8q(uint64_t *__restrict__ x, cons
 }
 
 
+// ------------------------------------------------------ register rounds --
+// The staged radix-2 to radix-16 rungs: the round structure of the library's
+// forward kernels with Shoup butterflies, as in the other rungs, so that a step of
+// the ladder changes the memory structure alone.  A pass corrects X at its
+// even-numbered stages (ct_bfly16); P is the parity of a round's first one.
+__device__ __forceinline__ Tw ld_pair(const Tw *t, uint32_t i) {
+  const __attribute__((address_space(4))) uint64_t *p = (const __attribute__((address_space(4))) uint64_t *)(t + i);
+  return Tw{p[0], p[1]};
+}
+template <int B, int E, int LO, int R, int P>
+__device__ __forceinline__ void shoup_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
+                                            uint32_t lanePart, const Tw *__restrict__ tw, const ModQ &m) {
+  using M = RoundMap<B, E, LO, R>;
+#pragma unroll
+  for (int g = 0; g < (1 << (E - R)); ++g) {
+    const uint32_t J0 = M::LANE_LOW ? (blockStart | M::g_part(g)) : (blockStart | lanePart | M::g_part(g));
+    static_for<0, R>([&](auto U) __attribute__((always_inline)) {
+      constexpr int u = decltype(U)::value, h = 1 << (R - 1 - u);
+      const uint32_t base = ((1u << (logn - B)) << (B - LO - R + u)) + (J0 >> (LO + R - u));
+#pragma unroll
+      for (int k = 0; k < (1 << R); ++k) {
+        if (k & h) continue;
+        const Tw w = ld_pair(tw, base + (k >> (R - u)));
+        ct_bfly16<((P + u) & 1) == 0>(x[(g << R) + k], x[(g << R) + k + h], w.w, w.ws, m);
+      }
+    });
+  }
+}
+template <int B, int E, int LO, int R, int P = 0>
+__device__ __forceinline__ void shoup_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t *lds, uint32_t tid,
+                                                   uint32_t blockStart, const Tw *__restrict__ tw, const ModQ &m) {
+  const uint32_t lp = RoundMap<B, E, LO, R>::lane_part(tid);
+  shoup_round<B, E, LO, R, P>(x, logn, blockStart, lp, tw, m);
+  if constexpr (LO > 0) {
+    static_assert(LO >= E, "rounds must tile the block");
+    store_lds<B, E, LO, R>(x, lds, lp);
+    __syncthreads();
+    load_lds<B, E, LO - E, E>(x, lds, RoundMap<B, E, LO - E, E>::lane_part(tid));
+    shoup_block_rounds<B, E, LO - E, E, (P + R) & 1>(x, logn, lds, tid, blockStart, tw, m);
+  }
+}
+
+// The first three stages, two neighbouring columns per lane.
+template <int LOGN>
+__global__ __launch_bounds__(256) void k_ladder_cols(uint64_t *__restrict__ x, const Tw *__restrict__ tw,
+                                                     const LimbConst *__restrict__ lc, uint32_t batch, uint32_t limbs) {
+  constexpr int E = 3, LO = LOGN - E;
+  const Unit un = unit_of(blockIdx.x, (1u << LO) / 512, batch, limbs);
+  const ModQ m = lc[un.limb].m;
+  const Tw *t = tw + (size_t)un.limb * 2 * (1u << LOGN);
+  uint64_t *p = x + (size_t)un.poly * (1u << LOGN);
+  const uint32_t col = un.tile * 512 + 2 * threadIdx.x;
+  uint64_t v0[1 << E], v1[1 << E];
+#pragma unroll
+  for (int s = 0; s < (1 << E); ++s) {
+    const u64x2 w = __builtin_nontemporal_load((const HENTT_GLOBAL u64x2 *)(p + col + ((uint32_t)s << LO)));
+    v0[s] = w.x;
+    v1[s] = w.y;
+  }
+  shoup_round<LOGN, E, LO, E, 0>(v0, LOGN, 0, col, t, m);
+  shoup_round<LOGN, E, LO, E, 0>(v1, LOGN, 0, col, t, m);
+#pragma unroll
+  for (int s = 0; s < (1 << E); ++s) {
+    const u64x2 w = {v0[s], v1[s]};
+    __builtin_nontemporal_store(w, (HENTT_GLOBAL u64x2 *)(p + col + ((uint32_t)s << LO)));
+  }
+}
+
+// The remaining stages on blocks of 2^B words, radix-2^E rounds; canonical output.
+template <int LOGN, int B, int E>
+__global__ __launch_bounds__(1 << (B - E)) void k_ladder_blocks(uint64_t *__restrict__ x, const Tw *__restrict__ tw,
+                                                                const LimbConst *__restrict__ lc, uint32_t batch,
+                                                                uint32_t limbs) {
+  __shared__ uint64_t lds[LdsSize<B>::value];
+  const Unit un = unit_of(blockIdx.x, 1u << (LOGN - B), batch, limbs);
+  const LimbConst c = lc[un.limb];
+  const uint32_t blockStart = un.tile << B, tid = threadIdx.x;
+  uint64_t *p = x + (size_t)un.poly * (1u << LOGN) + blockStart;
+  using F = FwdFirst<B, E>;
+  uint64_t v[1 << E];
+  load_global<B, E, F::LO, F::R>(v, p, RoundMap<B, E, F::LO, F::R>::lane_part(tid));
+  shoup_block_rounds<B, E, F::LO, F::R>(v, LOGN, lds, tid, blockStart, tw + (size_t)un.limb * 2 * (1u << LOGN), c.m);
+  if (c.k >= 34) {
+    const uint32_t ce = est_c(c.mu, c.k), sh = c.k - 33;
+#pragma unroll
+    for (int s = 0; s < (1 << E); ++s) v[s] = csubn(reduce_est(v[s], c.m.nq, ce, sh), c.m.nq);
+  } else {
+#pragma unroll
+    for (int s = 0; s < (1 << E); ++s) v[s] = reduce_16q(v[s], c.m);
+  }
+  store_global_m0<B, E>(v, p, lds, tid);
+}
+
 // ----------------------------------------------------- wave-shuffle stages --
 // The staged radix-2 transform with the smallest gaps exchanged between the
 // lanes of a wavefront instead of through LDS (the SIMD shuffling of section
@@ -81,11 +174,6 @@ template <int J> __device__ __forceinline__ uint32_t lane_xor32(uint32_t v, uint
 }
 template <int J> __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, uint32_t lane) {
   return ((uint64_t)lane_xor32<J>(hi32(v), lane) << 32) | lane_xor32<J>(lo32(v), lane);
-}
-
-__device__ __forceinline__ Tw ld_pair(const Tw *t, uint32_t i) {
-  const __attribute__((address_space(4))) uint64_t *p = (const __attribute__((address_space(4))) uint64_t *)(t + i);
-  return Tw{p[0], p[1]};
 }
 
 // One stage over block bit LO with the classic butterfly (every stage corrects,
@@ -209,11 +297,17 @@ void launch_naive_stages(const hentt_tables *t, const Tw *tw, uint64_t *x, uint6
   }
 }
 
-template <int E> void launch_staged15(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st) {
+template <int E> void launch_staged15(const hentt_tables *t, const Tw *tw, uint64_t *x, uint32_t batch, hipStream_t st) {
   const uint32_t L = t->limbs, units = batch * L;
   const char *name = E == 2 ? "k_fwd_blocks_r4" : E == 3 ? "k_fwd_blocks_r8" : "k_fwd_blocks_r16";
-  { LaunchTimer lt_("k_cols_fwd_r8", 15, st); hipLaunchKernelGGL((k_cols<15, 3, false>), dim3(units * ((1u << 12) / (256 * ColCpl<3>::value))), dim3(256), 0, st, col_args(x, (uint64_t)L << 15), t->s->d_twm, t->s->d_nc, batch, L); }
-  { LaunchTimer lt_(name, 15, st); hipLaunchKernelGGL((k_fwd_blocks<15, 12, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, t->s->d_twm, t->s->d_nc, batch, L); }
+  {
+    LaunchTimer lt_("k_cols_fwd_r8", 15, st);
+    hipLaunchKernelGGL((k_ladder_cols<15>), dim3(units * ((1u << 12) / 512)), dim3(256), 0, st, x, tw, t->s->d_lc, batch,
+                       L);
+  }
+  LaunchTimer lt_(name, 15, st);
+  hipLaunchKernelGGL((k_ladder_blocks<15, 12, E>), dim3(units << 3), dim3(1 << (12 - E)), 0, st, x, tw, t->s->d_lc, batch,
+                     L);
 }
 
 template <int S> void launch_simd15(const hentt_tables *t, const Tw *tw, uint64_t *x, uint64_t units, uint32_t batch,
@@ -251,8 +345,8 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
       launch_naive_stages(t, tw, x, units, 0, 4, st);
       {
         LaunchTimer lt_("k_fwd_blocks_r2", 15, st);
-        hipLaunchKernelGGL((k_fwd_blocks<15, 11, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x,
-                           t->s->d_twm, t->s->d_nc, batch, L);
+        hipLaunchKernelGGL((k_ladder_blocks<15, 11, 1>), dim3((uint32_t)(units << 4)), dim3(1 << 10), 0, st, x, tw,
+                           t->s->d_lc, batch, L);
       }
       break;
     case HENTT_VARIANT_SIMD1:
@@ -267,9 +361,9 @@ int run_fwd_variant(const hentt_tables *t, uint64_t *x, uint32_t batch, int vari
     case HENTT_VARIANT_STAGED_R8:
     case HENTT_VARIANT_STAGED_R16:
       if (ln != 15) return HENTT_EINVAL;
-      if (variant == HENTT_VARIANT_STAGED_R4) launch_staged15<2>(t, x, batch, st);
-      else if (variant == HENTT_VARIANT_STAGED_R8) launch_staged15<3>(t, x, batch, st);
-      else launch_staged15<4>(t, x, batch, st);
+      if (variant == HENTT_VARIANT_STAGED_R4) launch_staged15<2>(t, tw, x, batch, st);
+      else if (variant == HENTT_VARIANT_STAGED_R8) launch_staged15<3>(t, tw, x, batch, st);
+      else launch_staged15<4>(t, tw, x, batch, st);
       break;
     default:
       return HENTT_EINVAL;

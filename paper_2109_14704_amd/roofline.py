@@ -42,6 +42,7 @@ MUL_RS_PRO = 7      # rescale prologue: floor-estimate of s / q_i (4) and its pr
 
 # VALU lane-operations of this implementation per unit (counted in its AMD asm).
 VALU_BFLY = 11      # forward butterfly: 8 multiplies or multiply-adds, 3 additions (the inverse takes 12)
+VALU_BFLY_SHOUP = 21  # Shoup butterfly of the design ladder: 9 multiplies, 64-bit adds, one compare, two selects
 VALU_PROD = 15      # product of two variables, two 30-bit Montgomery steps (12) and a split (3)
 VALU_TENSOR = 48    # c0d0, c1d1 (2 x 12) + c0d1 + c1d0 summed ahead of each reduction (16) + the shared splits
 VALU_RS_EPI = 19    # rescale epilogue: c + off - t (2), product by qL^-1 (8), canonical reduction (9)
@@ -83,10 +84,10 @@ class Work:
         return {"bytes": self.nbytes, "multiplies": self.muls, "valu_ops": self.valu}
 
 
-def transform_work(n, polys, stages=None):
+def transform_work(n, polys, stages=None, valu=VALU_BFLY):
     """Butterfly arithmetic of `stages` stages of `polys` (polynomial, limb) transforms (no bytes)."""
     b = butterflies(n, polys, stages)
-    return Work(0, MUL_BFLY * b, VALU_BFLY * b)
+    return Work(0, MUL_BFLY * b, valu * b)
 
 
 def roof(work, seconds, measured=None):
