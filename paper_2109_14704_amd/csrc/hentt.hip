@@ -710,7 +710,9 @@ int hentt_tables_create(uint32_t log_n, uint32_t limbs, const uint64_t *moduli_h
   s->log_n = log_n;
   s->limbs = limbs;
   s->moduli.assign(moduli_host, moduli_host + limbs);
-  (void)hipGetDevice(&s->device);
+  if (hipGetDevice(&s->device) == hipSuccess &&
+      hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess)
+    s->cus = 256;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipMalloc(&s->d_twm, tw.size() * sizeof(TwM));
   if (e == hipSuccess) e = hipMalloc(&s->d_lc, lc.size() * sizeof(LimbConst));

@@ -57,7 +57,7 @@ struct Storage {
   MontLimb *d_mont = nullptr;  // [limbs] Montgomery constants
   MatLimb *d_mat = nullptr;    // [limbs] constants of the matrix product
   std::vector<uint64_t> moduli;
-  int device = 0;
+  int device = 0, cus = 256;   // the device and its compute units
   std::mutex rs_mu;                  // what is made on first use: d_tw, and the constants per level of
                                      // the rescale and the key switch
   std::map<uint32_t, RsLimb *> rs;   // per level (limb count)

@@ -292,7 +292,14 @@ int run_matmul(const hentt_tables *t, const uint64_t *A, const uint64_t *B, uint
   const uint32_t ln = t->s->log_n, L = t->limbs;
   const uint64_t P = (uint64_t)L << ln;
   if ((uint64_t)m * n * L * (((1ull << ln) + 2047) >> 11) > 0x7fffffffu) return HENTT_EINVAL;  // as the header states
-  const uint32_t tiles = ln > 8 ? 1u << (ln - 8) : 1u, runs = (n + CT_J - 1) / CT_J;
+  const uint32_t tiles = ln > 8 ? 1u << (ln - 8) : 1u;
+  // Runs of up to CT_J columns; shorter ones where that leaves the chip short of two
+  // workgroups per CU, since a workgroup's time is its chain of k steps over its run
+  // (4 limbs, 10 x 9 x 8: N = 2^8 11.1 us with runs of 5 columns, 8.4 with single ones,
+  // 2^10 16.4 and 14.6, no difference from 2^11 on).
+  const uint64_t per_run = (uint64_t)L * tiles * m, want = 2ull * t->s->cus;
+  const uint32_t runs =
+      (uint32_t)std::min<uint64_t>(n, std::max<uint64_t>((n + CT_J - 1) / CT_J, (want + per_run - 1) / per_run));
   const uint64_t groups = (uint64_t)L * runs * tiles, per_row = (groups + 7) / 8 * 8;
   if (per_row > kMaxItems / 256) return HENTT_EINVAL;
   const uint32_t rows = (uint32_t)std::min<uint64_t>(m, kMaxItems / 256 / per_row);
