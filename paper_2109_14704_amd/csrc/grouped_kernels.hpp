@@ -60,7 +60,7 @@ __global__ __launch_bounds__(cols_lanes<E>()) void k_cols_g(GroupTable g) {
 }
 
 template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
-__global__ __launch_bounds__(1 << (B - E)) void k_prod_g(GroupTable g) {
+__global__ __launch_bounds__(1 << (B - E), prod_waves(E, MODE, DO_FWD, DO_INV)) void k_prod_g(GroupTable g) {
   constexpr uint32_t per = 1u << (LOGN - B);
   const GroupJob &J = g.j[group_job(g, blockIdx.x / per)];
   prod_block<LOGN, ST, B, E, MODE, DO_FWD, DO_INV>(J.pa, J.tw, J.lc, J.mont, J.batch, J.limbs,

@@ -1004,8 +1004,16 @@ __device__ __forceinline__ void prod_block(const ProdArgs &a, const TwM *__restr
   });
 }
 
+// Waves per SIMD asked of the compiler.  The tensor of NTT-domain inputs with
+// coefficient-domain outputs takes 130 to 133 VGPRs at 2^11 and 2^12 by itself, which
+// at 2^12 leaves one workgroup of 8 waves per CU; held to 128, two (2^12, 4096 units:
+// 379 -> 297 us, 463 -> 339 with 60-bit moduli; 2^11 167 -> 152 with those).
+constexpr int prod_waves(int e, int mode, bool do_fwd, bool do_inv) {
+  return mode == PROD_TENSOR && !do_fwd && do_inv && e == 3 ? 4 : 1;
+}
+
 template <int LOGN, int ST, int B, int E, int MODE, bool DO_FWD, bool DO_INV>
-__global__ __launch_bounds__(1 << (B - E)) void k_prod(ProdArgs a, const TwM *__restrict__ tw,
+__global__ __launch_bounds__(1 << (B - E), prod_waves(E, MODE, DO_FWD, DO_INV)) void k_prod(ProdArgs a, const TwM *__restrict__ tw,
                                                         const NttConst *__restrict__ lc,
                                                         const MontLimb *__restrict__ mont, uint32_t batch,
                                                         uint32_t limbs) {
