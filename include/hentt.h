@@ -211,8 +211,9 @@ int hentt_dyadic_mul(const hentt_tables *t, const uint64_t *a, const uint64_t *b
  * values never leave the chip.  out must not overlap a or b (HENTT_EINVAL).
  * For N > 2^12 the forward column pass writes a workspace of 2 batch limbs N
  * words (of at most 2^32-word pieces of the batch) taken from the library's pool
- * (allocated on first need, reused); N = 2^13 runs without one, slower, under
- * stream capture while the pool has none and where it cannot be allocated. */
+ * (allocated on first need, reused); N = 2^13 runs without one where that is
+ * faster by the number of units, under stream capture while the pool has none, and
+ * where it cannot be allocated. */
 int hentt_polymul(const hentt_tables *t, const uint64_t *a, const uint64_t *b, uint64_t *out, uint32_t batch,
                   void *stream);
 
@@ -383,7 +384,9 @@ int hentt_stage_split(uint32_t log_n, uint32_t *transform_cols, uint32_t *produc
  * class 0 below 64, class 1 below 1024, class 2 above.  Every instance gives
  * the same results (bit-exact); only its speed differs.  Products select
  * among their instances only in the fused coefficient-to-coefficient form
- * (the other forms run instance 0).  Host-only, no device work:
+ * (the other forms run instance 0); at N = 2^13 a product left at instance 0 takes
+ * the one without column stages by the number of units (hentt_polymul).
+ * Host-only, no device work:
  *   count: number of instances of op at N = 2^log_n;
  *   describe: text of instance `choice` (copied into buf) and, if
  *     column_stages is not null, the stages of its column pass (0: the whole

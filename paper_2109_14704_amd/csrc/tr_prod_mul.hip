@@ -50,19 +50,33 @@ static const ProdCand *whole_instance(int mode, uint32_t log_n) {
   return nullptr;
 }
 
+// Whether the fused product at 2^13 runs whole where no instance was chosen.  A whole
+// one fills a CU, so calls take 32 us (38 with 60-bit moduli) per generation of as
+// many units as the chip has CUs; the two-pass default takes time in proportion, 0.13
+// us a unit.  Measured on 256 CUs, two-pass and whole, 55 bits (60 bits): 128 units 26.2
+// and 26.5 (29.5, 32.0), 256 45.4 and 32.1 (50.4, 38.6), 264 49.7 and 55.4 (56.5, 67.2),
+// 512 78 and 65 (88, 76), 640 87 and 82 (96, 98), 704 97 and 83 (106, 99), 1120 138 and 134
+// (152, 161), 4096 464 and 423 (518, 511): whole where the last generation is full or
+// more than half full.
+static bool whole_fits(uint64_t units, uint32_t cus) {
+  const uint64_t last = units % cus;
+  return last == 0 || 2 * last > cus;
+}
+
 int run_prod(const hentt_tables *t, int mode, const ProdArgs &pa, uint32_t batch, bool in_coeff, bool out_coeff,
              hipStream_t st) {
   const uint32_t ln = t->s->log_n;
   const int nin = mode == PROD_MUL ? 2 : 4;
-  const uint64_t NL = (uint64_t)t->limbs << ln;
-  const ProdCand *c = &prod_select(mode, ln, (uint64_t)batch * t->limbs, in_coeff && out_coeff);
+  const uint64_t NL = (uint64_t)t->limbs << ln, units = (uint64_t)batch * t->limbs;
+  const ProdCand *c = &prod_select(mode, ln, units, in_coeff && out_coeff);
+  const ProdCand *whole = in_coeff && out_coeff && c->pec > 0 ? whole_instance(mode, ln) : nullptr;
+  if (whole && whole_fits(units, t->s->cus)) c = whole;
   const uint32_t piece = batch_piece(ln, t->limbs, batch);
   void *ws = nullptr;
   if (in_coeff && c->pec > 0) {
     // Where a whole instance exists, the workspace only makes the call faster: it is
     // not allocated into a capture (which an allocation would end), and done without
     // when it cannot be had.
-    const ProdCand *whole = out_coeff ? whole_instance(mode, ln) : nullptr;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (whole && hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
     int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws, cap == hipStreamCaptureStatusNone);

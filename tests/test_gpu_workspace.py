@@ -38,7 +38,7 @@ def test_polymul_captured_without_a_warm_pool(gpu):
 def test_polymul_without_room_for_the_workspace(gpu):
     import paper_2109_14704_amd as H
     print("case polymul 2^13, no room", flush=True)
-    batch = 1 << 16                       # 4 GiB an operand, 8 GiB of workspace
+    batch = (1 << 16) + 8                 # 4 GiB an operand, 8 GiB of workspace; no whole generations of units
     mods = primes(55, LOG_N)
     t = H.Tables(LOG_N, mods)
     at = [0, 777, batch - 1]
