@@ -490,13 +490,15 @@ __device__ __forceinline__ Unit unit_of(uint32_t bid, uint32_t tiles, uint32_t b
 // lanes with fewer words win at every batch size, by latency at few units (the
 // product of one pair of 2^12: 13.0 us with 8 words, 16.2 with 16) and by
 // occupancy at many (2^12 forward, 4096 units: 68.6 against 72.9 us; 2^10
-// product, 512 units: 9.8 us with 4 words, 12.4 with 8, 14.9 with 16).
+// product, 512 units: 9.8 us with 4 words, 12.4 with 8, 14.9 with 16).  At 2^13, where a
+// workgroup of 8 words per lane fills a CU, the forward transform keeps 16 for calls of
+// more than two generations (launch_whole).
 constexpr int whole_e(int log_n) { return log_n <= 10 ? 2 : log_n <= 13 ? 3 : 4; }
 
 // ------------------------------------------------------------- kernels ----
 // Whole transform of one polynomial per workgroup (N = 2^LOGN fits in LDS).
 template <int LOGN, int E>
-__global__ __launch_bounds__(1 << (LOGN - E)) void k_fwd_whole(uint64_t* __restrict__ x, const TwM* __restrict__ tw,
+__global__ __launch_bounds__(1 << (LOGN - E), LOGN == 13 && E == 4 ? 4 : 1) void k_fwd_whole(uint64_t* __restrict__ x, const TwM* __restrict__ tw,
                                                                 const NttConst* __restrict__ lc, uint32_t batch,
                                                                 uint32_t limbs) {
   __shared__ __attribute__((aligned(16))) uint64_t lds[LdsSize<LOGN>::value];

@@ -15,19 +15,34 @@ namespace hentt_rt {
 namespace {
 
 // Whole transform of one (batch entry, limb) per workgroup.
+template <int LOGN, int E>
+void launch_fwd_whole(const hentt_tables *t, uint64_t *x, uint32_t batch, hipStream_t st) {
+  LaunchTimer lt_("k_fwd_whole", LOGN, st);
+  hipLaunchKernelGGL((k_fwd_whole<LOGN, E>), dim3(batch * t->limbs), dim3(1 << (LOGN - E)), 0, st, x, t->s->d_twm,
+                     t->s->d_nc, batch, t->limbs);
+}
 template <int LOGN>
 void launch_whole(const hentt_tables *t, const InvIO &io, uint32_t batch, bool inv, hipStream_t st) {
   constexpr int E = whole_e(LOGN);
   const uint32_t L = t->limbs, units = batch * L;
-  if (!inv) {
-    LaunchTimer lt_("k_fwd_whole", LOGN, st);
-    hipLaunchKernelGGL((k_fwd_whole<LOGN, E>), dim3(units), dim3(1 << (LOGN - E)), 0, st, io.dst, t->s->d_twm, t->s->d_nc,
-                       batch, L);
-  } else {
+  if (inv) {
     LaunchTimer lt_("k_inv_whole", LOGN, st);
     hipLaunchKernelGGL((k_inv_whole<LOGN, E>), dim3(units), dim3(1 << (LOGN - E)), 0, st, io, t->s->d_twm, t->s->d_nc,
                        batch, L);
+    return;
   }
+  if constexpr (LOGN == 13) {
+    // The 16 waves of a forward 2^13 with 8 words per lane (78 VGPRs) have a CU to
+    // themselves and stand at its barriers together.  With 16 words and 128 VGPRs two
+    // workgroups share the CU: slower while there are no two (256 units 13.9 and 14.8
+    // us), even at 512, faster from there on (1024 units 50.1 and 46.4, 4096 187 and 176;
+    // with 60-bit moduli 54.6 and 50.9, 197 and 188).
+    if (units > 2u * t->s->cus) {
+      launch_fwd_whole<LOGN, 4>(t, io.dst, batch, st);
+      return;
+    }
+  }
+  launch_fwd_whole<LOGN, E>(t, io.dst, batch, st);
 }
 
 // Column pass of EC stages and block pass on 2^(LOGN - EC) words, 2^E per lane.
