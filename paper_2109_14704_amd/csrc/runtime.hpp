@@ -144,6 +144,10 @@ const ProdCand *tensor_candidates(uint32_t log_n, uint32_t *count);
 // coefficient form, the default otherwise
 const ProdCand &prod_select(int mode, uint32_t log_n, uint64_t units, bool fused);
 uint32_t product_default_cols(uint32_t log_n);
+// Tensors of 2^9 with 8 words per lane, one wave each: by occupancy where there are many
+// (4096 units 55 -> 43 us, 63 -> 53 with 60-bit moduli; 1024 units 20.1 -> 17.2, 22.9 -> 21.0),
+// not where latency counts (256 units 11.9 -> 13.2, 13.7 -> 16.9).
+constexpr bool tensor9_one_wave(uint64_t units) { return units >= 1024; }
 
 inline ColArgs col_args(uint64_t *x, uint64_t sb) {
   ColArgs a{};

@@ -34,9 +34,9 @@ uint64_t ws_words(const HostJob &h) { return 4ull * h.batch * ((uint64_t)h.t->li
 
 // One launch sequence over jobs[0, n), n <= kGroupJobs, all at N = 2^LOGN.
 // ws: workspace of sum(ws_words) words when the forward column pass runs.
-template <int LOGN>
+template <int LOGN, int PE = grouped_pe(LOGN)>
 int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff, uint64_t *ws, hipStream_t st) {
-  constexpr int PEC = grouped_pec(LOGN), PE = grouped_pe(LOGN);
+  constexpr int PEC = grouped_pec(LOGN);
   constexpr int ST = LOGN - PEC, B = PEC ? block_words(ST, PE) : LOGN;
   GroupTable g{};
   g.n = n;
@@ -56,6 +56,9 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
   // units < 2^24 per chunk and at most 64 workgroups per unit in any kernel
   // here: every grid stays below 2^30
   const uint32_t u = (uint32_t)units;
+  if constexpr (LOGN == 9 && PE == 2) {
+    if (tensor9_one_wave(units)) return launch_group<9, 3>(jobs, n, in_coeff, out_coeff, ws, st);
+  }
   auto nl = [&](uint32_t i) { return (uint64_t)g.j[i].limbs << LOGN; };
 
   if (!in_coeff && !out_coeff) {

@@ -35,8 +35,9 @@ uint32_t product_default_cols(uint32_t log_n) { return k_mul[log_n - HENTT_LOG_N
 const ProdCand &prod_select(int mode, uint32_t log_n, uint64_t units, bool fused) {
   uint32_t n = 0;
   const ProdCand *c = prod_candidates(mode, log_n, &n);
-  if (!fused) return c[0];  // the NTT-domain forms run the default instance
-  uint32_t i = tune_choice(mode == PROD_MUL ? HENTT_OP_POLYMUL : HENTT_OP_TENSOR, log_n, units);
+  // the NTT-domain forms run the default instance
+  uint32_t i = fused ? tune_choice(mode == PROD_MUL ? HENTT_OP_POLYMUL : HENTT_OP_TENSOR, log_n, units) : 0;
+  if (i == 0 && mode == PROD_TENSOR && log_n == 9 && tensor9_one_wave(units)) i = 1;
   return c[i < n ? i : 0];
 }
 

@@ -6,7 +6,7 @@ namespace hentt_rt {
 namespace {
 #define D(n, pec, e) {launch_prod_cfg<n, PROD_TENSOR, pec, e, true>, pec, "column stages " #pec ", block words per lane 2^" #e}
 #define C(n, pec, e) {launch_prod_cfg<n, PROD_TENSOR, pec, e, false>, pec, "column stages " #pec ", block words per lane 2^" #e}
-const ProdCand t6[] = {D(6, 0, 2)}, t7[] = {D(7, 0, 2)}, t8[] = {D(8, 0, 2)}, t9[] = {D(9, 0, 2)},
+const ProdCand t6[] = {D(6, 0, 2)}, t7[] = {D(7, 0, 2)}, t8[] = {D(8, 0, 2)}, t9[] = {D(9, 0, 2), D(9, 0, 3)},
                t10[] = {D(10, 0, 2)}, t11[] = {D(11, 0, 3)}, t12[] = {D(12, 0, 3)};
 const ProdCand t13[] = {D(13, 7, 2), C(13, 6, 3)};
 const ProdCand t14[] = {D(14, 6, 3), C(14, 7, 2)};
