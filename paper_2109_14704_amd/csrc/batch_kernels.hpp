@@ -89,7 +89,7 @@ __device__ __forceinline__ void batch_cols(uint64_t *p, uint32_t tile, uint32_t 
     if constexpr (!INV) {
       fwd_round<LOGN, EC, LO, EC, FIX>(v, LOGN, 0, col, t, c);
     } else {
-      inv_round<LOGN, EC, LO, EC, 4, 4, FIX>(v, LOGN, 0, col, t, c);
+      inv_round<LOGN, EC, LO, EC, LB_PASS, LB_PASS, FIX>(v, LOGN, 0, col, t, c);
       reduce_out<EC, FIX>(v, c);
     }
     const uint64_t *ps = opaque_s(p);

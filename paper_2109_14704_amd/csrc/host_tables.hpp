@@ -184,5 +184,10 @@ inline NttConst ntt_const_after_products(const LimbConst &c) {
   return n;
 }
 
+// A multiple of q above every lazy forward output that c + off - t (below 2^64) takes
+// it from, in the rescale: of 60-bit words uncorrected up to 55 bits (below 2^60 + 2^62.7),
+// below 15q above; moduli of 33 or fewer bits come nowhere near.
+inline uint64_t rs_off(uint64_t q) { return q >> 55 ? 15 * q : (1ull << 63) / q * q; }
+
 }  // namespace host
 }  // namespace hentt

@@ -213,10 +213,7 @@ __device__ __forceinline__ uint64_t reduce_word(uint64_t x, const NttConst &c) {
 
 // Forward (Cooley-Tukey) butterfly: X' = X + W Y, Y' = X - W Y + 12q (mod q);
 // both below X + 12q.  Eleven instructions.  X must leave room for 12q below
-// 2^64; Y is any 64-bit word.  Up to 56 bits a whole transform of 17 stages
-// stays below 256q without a correction; above, the rounds bring X below 3q
-// (est3) before every second stage (57 to 59 bits: 3 + 24 < 32) or before
-// every stage (60 bits: 3 + 12 < 16).
+// 2^64; Y is any 64-bit word.  Which stages correct X first: schedule.hpp.
 __device__ __forceinline__ void ct_bfly_m(uint64_t &X, uint64_t &Y, TwM w, const NttConst &c, uint32_t four) {
   const uint64_t s = mul_tw_add(w, Y, X, c, four);
   Y = ((X << 1) + c.off) - s;

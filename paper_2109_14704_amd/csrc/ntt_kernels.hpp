@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "modarith.hpp"
+#include "schedule.hpp"
 
 namespace hentt {
 
@@ -102,15 +103,15 @@ template <int I0, int I1, typename F> __device__ __forceinline__ void static_for
   }
 }
 
-// Moduli of 34 to 55 bits run without corrections inside the rounds; the
-// others (FIX) take theirs unconditionally.  A kernel holds both forms of its
+// Moduli of 34 to 55 bits run without corrections inside the rounds (schedule.hpp);
+// the others (FIX) take theirs unconditionally.  A kernel holds both forms of its
 // body and branches once, on its workgroup's limb.  Tests at every stage
 // instead cut the body into blocks that the scheduler could not overlap and
 // roughly doubled its registers (k_cols of five stages 260 VGPRs against 103);
 // the markers keep the compiler from merging the two forms' heads and tails,
 // which did the same.
 template <typename F> __device__ __forceinline__ void by_class(const NttConst &c, F &&f) {
-  if (c.k - 34u <= 21u) {
+  if (uncorrected(c.k)) {
     asm volatile("; class 0");
     f(std::false_type{});
     asm volatile("; end 0");
@@ -124,9 +125,7 @@ template <typename F> __device__ __forceinline__ void by_class(const NttConst &c
 // ---------------------------------------------------------------- rounds --
 // Forward stages with global index s = LOGN - LO - R + u, u < R.  Stage s
 // pairs j with j + N/2^(s+1) and uses psi_rev[2^s + (j >> (LOGN - s))].
-// Moduli of up to 56 bits need no corrections: a transform adds at most 12q
-// per stage to inputs of a few q.  Larger ones (FIX) enter with any 64-bit
-// words and bring X below 3q before every stage (3 + 12 < 16).
+// Bounds and corrections: schedule.hpp.
 template <int B, int E, int LO, int R, bool FIX, bool PRE = false>
 __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
                                           uint32_t lanePart, const TwM* __restrict__ tw, const NttConst &c,
@@ -156,29 +155,7 @@ __device__ __forceinline__ void fwd_round(uint64_t (&x)[1 << E], uint32_t logn, 
 }
 // Inverse stages v = LO + u.  Stage v pairs j with j + 2^v and uses
 // psi_rev^-1[N/2^(v+1) + (j >> (v+1))].  The last stage (v = LOGN-1) also
-// multiplies both outputs by N^-1.
-//
-// X' = X + Y doubles the bound of the words that stay on the X side, while
-// every product is below 12q.  Corrections (est3, to below 3q) by modulus
-// size, k uniform per workgroup:
-//   34..55 bits  (not FIX) none inside a round of up to five stages: words enter below
-//                2^LBIN q (16q, or 32q for rounds of at most four stages) and
-//                stay below 512q; at its end the words that could exceed
-//                2^LBOUT q are corrected (the few with a long run of X sides
-//                behind them);
-//   56..60 bits  words below 4q on entry: the product corrected after every
-//                stage, X' after every second one and after the round's last
-//                (4 + 4 <= 8, 8 + 8 <= 16);
-//   33 or fewer  none in the whole transform: at stage v words are below
-//                16q 2^v < 2^54 (est3 leaves them as they are).
-// `off`, the multiple of q that keeps X - Y positive, follows the same bounds.
-template <int R, int LBIN, int LBOUT> constexpr bool inv_over(int k) {
-  int h = -1;
-  for (int b = 0; b < R; ++b)
-    if ((k >> b) & 1) h = b;
-  const int bound = h < 0 ? 1 << (LBIN + R) : 12 << (R - 1 - h);
-  return bound > (1 << LBOUT);
-}
+// multiplies both outputs by N^-1.  Bounds and corrections: schedule.hpp.
 template <int B, int E, int LO, int R, int LBIN, int LBOUT, bool FIX, bool PRE = false>
 __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, uint32_t blockStart,
                                            uint32_t lanePart, const TwM* __restrict__ itw, const NttConst& c,
@@ -188,7 +165,7 @@ __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, 
   const uint32_t four = opaque4();
   static_for<0, R>([&](auto U) __attribute__((always_inline)) {
     constexpr int u = decltype(U)::value, v = LO + u, d = 1 << u;
-    const uint64_t off = c.q << (!FIX ? (uint32_t)(LBIN + u) : c.k < 34 ? 4u + v : 3u);
+    const uint64_t off = c.q << inv_off_log(c.k, FIX, LBIN, u, v);
     // only the block's top stage can be the transform's last one
     if (LO + u == B - 1 && (uint32_t)v == logn - 1) {
       // last stage: one group, twiddle psi^-brv(1) folded with N^-1
@@ -214,7 +191,7 @@ __device__ __forceinline__ void inv_round(uint64_t (&x)[1 << E], uint32_t logn, 
       if constexpr (FIX) {
 #pragma unroll
         for (int i = 0; i < (1 << E); ++i)
-          if ((i & d) || (u & 1) || u == R - 1) x[i] = est3(x[i], c);
+          if (inv_fix(R, u, i & d)) x[i] = est3(x[i], c);
       } else if (u == R - 1) {
 #pragma unroll
         for (int i = 0; i < (1 << E); ++i)
@@ -438,7 +415,7 @@ __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t
                                                  const NttConst& c, const TwM* pf = nullptr) {
   using M = RoundMap<B, E, LO, R>;
   const uint32_t lp = M::lane_part(tid);
-  inv_round<B, E, LO, R, 5, (LO + R < ST ? 5 : 4), FIX, HAVE>(x, logn, blockStart, lp, itw, c, pf);
+  inv_round<B, E, LO, R, LB_ROUND, (LO + R < ST ? LB_ROUND : LB_PASS), FIX, HAVE>(x, logn, blockStart, lp, itw, c, pf);
   if constexpr (LO + R < ST) {
     constexpr int LO2 = LO + R;
     constexpr int R2 = (ST - LO2) < E ? (ST - LO2) : E;
@@ -460,16 +437,6 @@ __device__ __forceinline__ void inv_block_rounds(uint64_t (&x)[1 << E], uint32_t
   }
 }
 
-// Round geometry helpers, for the block pass's stage count.
-template <int B, int E> struct FwdFirst {   // forward: first round is the short one
-  static constexpr int R = (B % E) ? (B % E) : E;
-  static constexpr int LO = B - R;
-};
-template <int B, int E> struct InvLast {    // inverse: last round is the short one
-  static constexpr int R = (B % E) ? (B % E) : E;
-  static constexpr int LO = B - R;
-};
-
 // Map blockIdx -> (polynomial, tile): limb-major, batch next, tile fastest, so
 // that concurrently running workgroups share one limb's twiddle table in L2.
 struct Unit {
@@ -484,16 +451,6 @@ __device__ __forceinline__ Unit unit_of(uint32_t bid, uint32_t tiles, uint32_t b
   u.poly = u.b * limbs + u.limb;
   return u;
 }
-
-// Words per lane (log2) of the kernels that hold a whole transform, product, or
-// rescale in one workgroup.  Measured over 2, 3 and 4 at 1 to 4096 units: more
-// lanes with fewer words win at every batch size, by latency at few units (the
-// product of one pair of 2^12: 13.0 us with 8 words, 16.2 with 16) and by
-// occupancy at many (2^12 forward, 4096 units: 68.6 against 72.9 us; 2^10
-// product, 512 units: 9.8 us with 4 words, 12.4 with 8, 14.9 with 16).  At 2^13, where a
-// workgroup of 8 words per lane fills a CU, the forward transform keeps 16 for calls of
-// more than two generations (launch_whole).
-constexpr int whole_e(int log_n) { return log_n <= 10 ? 2 : log_n <= 13 ? 3 : 4; }
 
 // ------------------------------------------------------------- kernels ----
 // Whole transform of one polynomial per workgroup (N = 2^LOGN fits in LDS).
@@ -571,7 +528,7 @@ __device__ __forceinline__ void col_pass(const uint64_t *src, uint64_t *dst, uin
   if constexpr (!INV) {
     fwd_round<LOGN, E, LO, E, FIX>(v, LOGN, 0, col, t, c);
   } else {
-    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v, LOGN, 0, col, t, c);
+    inv_round<LOGN, E, LO, E, LB_PASS, LB_PASS, FIX>(v, LOGN, 0, col, t, c);
     reduce_out<E, FIX>(v, c);
   }
   store_global<LOGN, E, LO, E, true>(v, dst, col);
@@ -599,8 +556,8 @@ __device__ __forceinline__ void col_pass2(const uint64_t *src, uint64_t *dst, ui
     fwd_round<LOGN, E, LO, E, FIX>(v0, LOGN, 0, col, t, c);
     fwd_round<LOGN, E, LO, E, FIX>(v1, LOGN, 0, col, t, c);
   } else {
-    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v0, LOGN, 0, col, t, c);
-    inv_round<LOGN, E, LO, E, 4, 4, FIX>(v1, LOGN, 0, col, t, c);
+    inv_round<LOGN, E, LO, E, LB_PASS, LB_PASS, FIX>(v0, LOGN, 0, col, t, c);
+    inv_round<LOGN, E, LO, E, LB_PASS, LB_PASS, FIX>(v1, LOGN, 0, col, t, c);
     reduce_out<E, FIX>(v0, c);
     reduce_out<E, FIX>(v1, c);
   }
@@ -679,14 +636,14 @@ __device__ __forceinline__ void lcol_inv(uint64_t (&v)[16], LD ld, const TwM *t,
 #pragma unroll
   for (uint32_t g = 0; g < G; ++g) {
     const uint32_t hi = w * G + g;
-    inv_round<LOGN, R2, LOGN - EC, R2, 4, 5, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
+    inv_round<LOGN, R2, LOGN - EC, R2, LB_PASS, LB_ROUND, FIX>(a[g], LOGN, hi << (LOGN - R1), 0, t, c);
 #pragma unroll
     for (uint32_t k = 0; k < (1u << R2); ++k) l[((hi << R2) + k) * LC<EC>] = a[g][k];
   }
   __syncthreads();
 #pragma unroll
   for (uint32_t r = 0; r < 16; ++r) v[r] = l[((r << R2) + w) * LC<EC>];
-  inv_round<LOGN, R1, LOGN - R1, R1, 5, 4, FIX>(v, LOGN, 0, 0, t, c);
+  inv_round<LOGN, R1, LOGN - R1, R1, LB_ROUND, LB_PASS, FIX>(v, LOGN, 0, 0, t, c);
   reduce_out<R1, FIX>(v, c);
 }
 template <int LOGN, int EC, bool INV, bool FIX, typename LD, typename STO>
@@ -753,16 +710,6 @@ __global__ __launch_bounds__(cols_lanes<E>()) void k_cols(ColArgs a, const TwM *
                                                           uint32_t limbs) {
   cols_block<LOGN, E, INV>(a, tw, lc, batch, limbs, blockIdx.x);
 }
-
-// Column stages of a two-pass transform or product at N = 2^log_n (measured over
-// 6 to 8 stages and, through registers alone, 1 to 5): the blocks behind it are
-// of 2^7 to 2^9 words, so that one wave holds a block (three radix-8 rounds and
-// no barrier).
-constexpr int two_pass_cols(int log_n) { return log_n <= 15 ? 6 : log_n - 9; }
-
-// Words of a workgroup of a two-pass transform's block pass of ST stages, 2^E
-// words per lane: at least one wave.
-constexpr int block_words(int st, int e) { return st > e + 6 ? st : e + 6; }
 
 // Block pass of the forward transform: the last ST stages, on 2^(B - ST)
 // contiguous blocks of 2^ST elements per workgroup; canonical output.

@@ -32,7 +32,7 @@ int rs_constants(Storage *s, uint32_t level, const RsLimb **out) {
     host[i].mu = (uint64_t)(((host::u128)1 << 64) / q);
     host[i].nh = q - h % q;
     host[i].w = host::tw_m(host::pow(qL % q, q - 2, q), q);
-    host[i].off = q >> 55 ? 15 * q : (1ull << 63) / q * q;
+    host[i].off = host::rs_off(q);
   }
   RsLimb *d = nullptr;
   hipError_t e = hipMalloc(&d, L * sizeof(RsLimb));
