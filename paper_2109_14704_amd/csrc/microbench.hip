@@ -6,9 +6,9 @@
 //     arithmetic is built from (v_mad_u64_u32, v_mul_hi_u32, v_mul_lo_u32),
 //     of the other instructions its butterflies issue (the 64-bit add
 //     v_lshl_add_u64, the 64-bit compare, the three-input add, register
-//     moves), of a plain v_add_u32 for comparison, and of the library's own
-//     lazy forward butterfly (multiplies, additions, compares and selects as
-//     the kernels issue them).
+//     moves), of a plain v_add_u32 for comparison, and of whole butterflies
+//     on registers: the library's forward and inverse ones, and the design
+//     ladder's Shoup one.
 // Every issue kernel keeps 8 independent dependency chains per lane and
 // writes every chain's final value, so no operation can be removed or
 // hoisted; the single-instruction kernels spell the instruction in inline
@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "host_tables.hpp"
 #include "modarith.hpp"
 
 namespace hentt_mb {
@@ -52,18 +53,25 @@ __global__ __launch_bounds__(256) void mb_read_k(const u64x2 *__restrict__ src, 
   out[(uint64_t)blockIdx.x * 256 + threadIdx.x] = acc;
 }
 
-enum { MB_MAD64 = 0, MB_MULHI = 1, MB_MULLO = 2, MB_ADD = 3, MB_BFLY = 4, MB_ADD64 = 5, MB_CMP64 = 6, MB_ADD3 = 7,
-       MB_MOV = 8 };
+enum { MB_MAD64 = 0, MB_MULHI = 1, MB_MULLO = 2, MB_ADD = 3, MB_SHOUP = 4, MB_ADD64 = 5, MB_CMP64 = 6, MB_ADD3 = 7,
+       MB_MOV = 8, MB_BFLY = 9, MB_BFLY_INV = 10 };
+
+struct Consts {
+  hentt::ModQ m;
+  hentt::NttConst c;
+  hentt::TwM t;  // w in the library's form
+};
 
 // The butterfly's constants arrive as kernel arguments, as the library's
 // kernels load theirs from memory, so that the compiler cannot specialise
 // the arithmetic to known values.
 template <int KIND>
 __global__ __launch_bounds__(256) void mb_issue_k(uint64_t *out, uint32_t iters, uint32_t a, uint64_t w, uint64_t ws,
-                                                  hentt::ModQ m) {
+                                                  Consts k) {
   const uint64_t gid = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if constexpr (KIND == MB_BFLY) {
-    const uint64_t q = m.q;
+  if constexpr (KIND == MB_SHOUP || KIND == MB_BFLY || KIND == MB_BFLY_INV) {
+    const uint64_t q = k.m.q;
+    const uint32_t four = hentt::opaque4();
     uint64_t x[8], y[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -73,7 +81,13 @@ __global__ __launch_bounds__(256) void mb_issue_k(uint64_t *out, uint32_t iters,
 #pragma unroll 2
     for (uint32_t it = 0; it < iters; ++it) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) hentt::ct_bfly(x[j], y[j], w, ws, m);
+      for (int j = 0; j < 8; ++j) {
+        // the library's butterflies uncorrected, as for moduli of 34 to 55 bits: the
+        // words run past 64 bits here, which the time does not depend on
+        if constexpr (KIND == MB_SHOUP) hentt::ct_bfly(x[j], y[j], w, ws, k.m);
+        else if constexpr (KIND == MB_BFLY) hentt::ct_bfly_m(x[j], y[j], k.t, k.c, four);
+        else hentt::gs_bfly_m(x[j], y[j], k.t, k.c.off, k.c, four);
+      }
     }
     uint64_t r = 0;
 #pragma unroll
@@ -162,20 +176,27 @@ int mb_read(const void *src, uint64_t bytes, uint64_t *out, uint32_t grid, void 
 }
 
 // Issue-rate kernel `kind` (0 v_mad_u64_u32, 1 v_mul_hi_u32, 2 v_mul_lo_u32,
-// 3 v_add_u32, 4 forward butterfly, 5 v_lshl_add_u64, 6 v_cmp_lt_u64,
-// 7 v_add3_u32, 8 v_mov_b32): grid workgroups of 256 lanes, each lane
-// running 8 chains of `iters` operations; out receives grid * 256 words.
-// For kind 4, w, ws, q are a twiddle, its Shoup quotient and the modulus.
+// 3 v_add_u32, 4 Shoup forward butterfly, 5 v_lshl_add_u64, 6 v_cmp_lt_u64,
+// 7 v_add3_u32, 8 v_mov_b32, 9 and 10 the library's forward and inverse
+// butterflies): grid workgroups of 256 lanes, each lane running 8 chains of
+// `iters` operations; out receives grid * 256 words.  For the butterflies, w,
+// ws, q are a twiddle, its Shoup quotient and an odd modulus of 34 to 55 bits.
 int mb_issue(int kind, uint64_t *out, uint32_t iters, uint32_t grid, uint32_t a, uint64_t w, uint64_t ws, uint64_t q,
              void *stream) {
   if (!out || grid == 0) return -1;
   hipStream_t st = (hipStream_t)stream;
-  const hentt::ModQ m{q, 0 - q, 2 * q, 0 - 2 * q, 4 * q, 0 - 4 * q};
+  if (q < (1ull << 33) || q >> 55 || !(q & 1)) return -1;
+  hentt::LimbConst lc{};
+  lc.m = hentt::ModQ{q, 0 - q, 2 * q, 0 - 2 * q, 4 * q, 0 - 4 * q};
+  lc.k = 64 - (uint32_t)__builtin_clzll(q);
+  const Consts m{lc.m, hentt::host::ntt_const(lc), hentt::host::tw_m(w % q, q)};
   switch (kind) {
     case MB_MAD64: hipLaunchKernelGGL(mb_issue_k<MB_MAD64>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_MULHI: hipLaunchKernelGGL(mb_issue_k<MB_MULHI>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_MULLO: hipLaunchKernelGGL(mb_issue_k<MB_MULLO>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_ADD: hipLaunchKernelGGL(mb_issue_k<MB_ADD>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
+    case MB_SHOUP: hipLaunchKernelGGL(mb_issue_k<MB_SHOUP>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
+    case MB_BFLY_INV: hipLaunchKernelGGL(mb_issue_k<MB_BFLY_INV>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_BFLY: hipLaunchKernelGGL(mb_issue_k<MB_BFLY>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_ADD64: hipLaunchKernelGGL(mb_issue_k<MB_ADD64>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;
     case MB_CMP64: hipLaunchKernelGGL(mb_issue_k<MB_CMP64>, dim3(grid), dim3(256), 0, st, out, iters, a, w, ws, m); break;

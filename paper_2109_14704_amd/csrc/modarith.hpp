@@ -151,9 +151,9 @@ __device__ __forceinline__ uint32_t est_c(uint64_t mu, uint32_t k) { return (uin
 // 30 bits is what keeps p0 inside one 64-bit accumulator: no carry between the
 // halves, so all of it is seven multiply-adds and one low product, and X + T
 // costs nothing more (X starts p1).  A Shoup product takes nine multiplies
-// and about four additions more.  Measured in registers at full occupancy
-// (wave cycles per butterfly at 2.1 GHz): forward 64.6 with Shoup products,
-// 39.7 with these; inverse 71.6 and 43.6.
+// and about four additions more.  In registers at full occupancy (the issue-rate
+// microbenchmarks): 3250 G forward and 3120 G inverse butterflies a second, 1917 G
+// with Shoup products.
 //
 // The last multiply-add's factor is an opaque 4: spelled as a shift it would
 // cost two register moves and an add.

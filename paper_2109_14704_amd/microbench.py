@@ -11,11 +11,12 @@ known work:
     v_mad_u64_u32, v_mul_hi_u32, v_mul_lo_u32, v_add_u32;
   * add64 / cmp64 / add3 / mov: the same for the other instructions the
     butterflies issue (v_lshl_add_u64, v_cmp_lt_u64, v_add3_u32, v_mov_b32);
-  * mul_mix: the rate of the Shoup butterfly's own multiply mix (3
-    v_mad_u64_u32, 2 v_mul_hi_u32, 4 v_mul_lo_u32 per butterfly), i.e. nine
-    multiplies in the time the three measured rates give them;
-  * bfly: Shoup forward butterflies per second, the library's own lazy
-    butterfly on registers with no memory traffic.
+  * mul_mix: the rate of the butterfly's own multiply mix (7 v_mad_u64_u32
+    and 1 v_mul_lo_u32 per butterfly), i.e. eight multiplies in the time the
+    measured rates give them;
+  * bfly, bfly_inv, bfly_shoup: butterflies per second on registers with no
+    memory traffic: the library's forward and inverse ones, uncorrected, and the
+    design ladder's Shoup one.
 """
 import ctypes
 import os
@@ -26,7 +27,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhentt_mb.so")
 _lib = None
 
-MB_MAD64, MB_MULHI, MB_MULLO, MB_ADD, MB_BFLY, MB_ADD64, MB_CMP64, MB_ADD3, MB_MOV = range(9)
+MB_MAD64, MB_MULHI, MB_MULLO, MB_ADD, MB_SHOUP, MB_ADD64, MB_CMP64, MB_ADD3, MB_MOV, MB_BFLY, MB_BFLY_INV = range(11)
 
 
 def lib():
@@ -103,12 +104,12 @@ def hbm_read_gbs(nbytes=4 << 30, reps=5):
 
 
 def issue_rate(kind, iters=None, reps=3):
-    """Lane-operations (or butterflies, for MB_BFLY) per second."""
+    """Lane-operations (or butterflies) per second."""
     grid = _cus() * 8
     out = torch.empty(grid * 256, dtype=torch.int64, device="cuda")
-    iters = iters or (4000 if kind == MB_BFLY else 60000)
+    iters = iters or (4000 if kind in (MB_SHOUP, MB_BFLY, MB_BFLY_INV) else 60000)
     L = lib()
-    q = (1 << 55) - (1 << 22) + 1        # odd 55-bit modulus: the butterfly's timing does not depend on primality
+    q = (1 << 55) - (1 << 22) + 1        # odd 55-bit modulus: the butterflies' timing does not depend on primality
     w = 12345678901234 % q
     ws = (w << 64) // q
 
@@ -132,10 +133,11 @@ def measure_all(detail=None):
         "add3_tops": issue_rate(MB_ADD3) / 1e12,
         "mov_tops": issue_rate(MB_MOV) / 1e12,
         "bfly_gbfly_s": issue_rate(MB_BFLY) / 1e9,
+        "bfly_inv_gbfly_s": issue_rate(MB_BFLY_INV) / 1e9,
+        "bfly_shoup_gbfly_s": issue_rate(MB_SHOUP) / 1e9,
     }
-    # the butterfly's nine multiplies at the measured rates of their kinds
-    t9 = 3 / r["mad64_tops"] + 2 / r["mulhi_tops"] + 4 / r["mullo_tops"]
-    r["mul_mix_tops"] = 9 / t9
+    # the butterfly's eight multiplies at the measured rates of their kinds
+    r["mul_mix_tops"] = 8 / (7 / r["mad64_tops"] + 1 / r["mullo_tops"])
     return {k: round(v, 3) for k, v in r.items()}
 
 

@@ -33,8 +33,9 @@ VALU_PEAK_TOPS = CUS * SIMDS_PER_CU * LANES * CLOCK_GHZ / 1000.0   # 39.32 T lan
 MUL_PEAK_TOPS = VALU_PEAK_TOPS        # one 32-bit multiply per lane per clock
 
 # Algorithmic 32-bit multiplies per unit of work.
-MUL_BFLY = 10       # Shoup butterfly: quotient estimate (3), W Y mod 2^64 (3), Q q mod 2^64 (3), ~1 more
-MUL_SHOUP = 10      # a Shoup product by a constant (the butterfly's multiply)
+MUL_BFLY = 10       # the unit of the accounting, a Shoup butterfly's: quotient estimate (3), W Y mod 2^64 (3), Q q mod
+                    # 2^64 (3), ~1 more; the library's own butterfly issues 8
+MUL_SHOUP = 10      # a product by a constant (the butterfly's multiply)
 MUL_PROD = 11       # a b mod q for two variables: 128-bit product (4) + Montgomery/Barrett reduction (7)
 MUL_TENSOR = 37     # c0 d0, c1 d1 (11 each) + c0 d1 + c1 d0 summed before one reduction (4 + 4 + 7)
 MUL_KS_MAC = 22     # key switch, per digit word: products with both key components
@@ -46,7 +47,8 @@ VALU_BFLY_SHOUP = 21  # Shoup butterfly of the design ladder: 9 multiplies, 64-b
 VALU_PROD = 15      # product of two variables, two 30-bit Montgomery steps (12) and a split (3)
 VALU_TENSOR = 48    # c0d0, c1d1 (2 x 12) + c0d1 + c1d0 summed ahead of each reduction (16) + the shared splits
 VALU_RS_EPI = 19    # rescale epilogue: c + off - t (2), product by qL^-1 (8), canonical reduction (9)
-VALU_MAC = 36       # one matMul product term: four products by A's words in root-power form (8 each), reductions
+VALU_MAC = 44       # one matMul product term: four products by A's words in root-power form (8 each), and A's two
+                    # words brought to that form (30 each) over a run of 5 columns
 VALU_KS_MAC = 15    # key switch, per digit word and key component: product (12), half the word's cut and split (3)
 VALU_KS_FIN = 17    # key switch, per output word: product by 2^60 (8), canonical reduction (9)
 VALU_KS_FIN_C = 29  # the same plus P c_s: a second product (8), a cut (4)
