@@ -124,8 +124,8 @@ int hentt_ntt_fwd(const hentt_tables *t, uint64_t *x, uint32_t batch, void *stre
  * [batch][limbs][N], out [batch][limbs - 1][N]; out must not overlap c
  * (HENTT_EINVAL).  flags: 0 for coefficient-domain input and output;
  * HENTT_IN_NTT | HENTT_OUT_NTT for NTT-domain (bit-reversed) input and output,
- * where the last limb is inverse-transformed once and its correction
- * forward-transformed per remaining limb, with the reduction, subtraction and
+ * where the last limb is inverse-transformed (once; small calls repeat its last
+ * stages per remaining limb) and its correction forward-transformed per remaining limb, with the reduction, subtraction and
  * scaling fused into that transform; other flags: HENTT_EINVAL.  Canonical
  * inputs, canonical outputs.  The per-level constants are made on the first
  * call for a level (a synchronous upload); later calls only enqueue. */
@@ -141,7 +141,8 @@ int hentt_rescale(const hentt_tables *t, const uint64_t *c, uint64_t *out, uint3
  * A [m][k][2][limbs][N], B [k][n][2][limbs][N], C [m][n][3][limbs][N] with
  * limbs and N those of t; canonical inputs, canonical C.  C is updated in
  * place and must not overlap A or B.  HENTT_EINVAL for null pointers, a zero
- * dimension, overlap, or more than 2^31 - 1 workgroups (m n limbs N / 2048). */
+ * dimension, overlap, or more than 2^31 - 1 tiles of 2048 words (m n limbs
+ * ceil(N / 2048)). */
 int hentt_ct_matmul(const hentt_tables *t, const uint64_t *A, const uint64_t *B, uint64_t *C, uint32_t m, uint32_t n,
                     uint32_t k, void *stream);
 

@@ -120,7 +120,7 @@ __device__ __forceinline__ const uint64_t *ks_cs(const KsArgs &a, uint32_t b, ui
   return t < a.l ? a.c + ((((uint64_t)b * 3 + s) * a.l + t) << logn) + off : nullptr;
 }
 
-// Whole transforms (N <= 2^12, 256 lanes): one workgroup per (batch entry,
+// Whole transforms (N <= 2^12, up to 512 lanes): one workgroup per (batch entry,
 // target prime), looping over the digits.
 template <int LOGN, int E>
 __global__ __launch_bounds__(1 << (LOGN - E)) void k_ks_whole(KsArgs a, const TwM *__restrict__ tw,
@@ -214,8 +214,8 @@ __global__ __launch_bounds__(cols_lanes<EC>(), EC < 8 ? 4 : 1) void k_ks_cols(Ks
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
-// rounds of every digit, accumulated with the key in registers.  VALU-bound: 320 us,
-// its bytes take 120 at the copy rate.  At N = 2^15, 8 primes, 32 entries, the
+// rounds of every digit, accumulated with the key in registers.  VALU-bound: 300 to
+// 320 us, its bytes take 120 at the copy rate.  At N = 2^15, 8 primes, 32 entries, the
 // whole relinearization: 720 us with Montgomery products of 64-bit words, 690 with
 // mont30_mul at the 134 VGPRs it takes (three waves per SIMD), 678 held to 128
 // (four waves), 600 with the column passes fused.  The key in root-power form, a third fewer

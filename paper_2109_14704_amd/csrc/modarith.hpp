@@ -79,8 +79,8 @@ __device__ __forceinline__ void ct_bfly(uint64_t &X, uint64_t &Y, uint64_t W, ui
   Y = (x + m.q4) - T;
 }
 
-// Forward butterfly of the library's transforms, with the correction of X
-// taken every second stage: values lie in [0, 16q) (q < 2^60, so 16q < 2^64).
+// Forward butterfly of the design ladder's register rounds, with the correction
+// of X taken every second stage: values lie in [0, 16q) (q < 2^60, so 16q < 2^64).
 // CORR: X (below 16q) is first brought below 8q, and the outputs lie below
 // 12q; otherwise X must already be below 12q and the outputs lie below 16q.
 // A pass corrects at its even-numbered stages (the first one included), so
@@ -96,7 +96,8 @@ __device__ __forceinline__ void ct_bfly16(uint64_t &X, uint64_t &Y, uint64_t W, 
 }
 
 // Inverse (Gentleman-Sande) lazy butterfly after Harvey: X, Y in [0, 4q) on
-// entry and exit; X' = X + Y, Y' = W (X - Y) (mod q).
+// entry and exit; X' = X + Y, Y' = W (X - Y) (mod q).  The counterpart of ct_bfly for
+// an inverse with Shoup products; the library's inverse is gs_bfly_m.
 __device__ __forceinline__ void gs_bfly(uint64_t &X, uint64_t &Y, uint64_t W, uint64_t Ws, const ModQ &m) {
   const uint64_t s = X + Y;
   const uint64_t d = (X + m.q4) - Y;

@@ -21,8 +21,12 @@
 
 namespace hentt {
 
-// LDS padding: one spare element after every 16, so that the lane-strided
-// accesses of every round hit distinct banks.
+// LDS padding: one spare element after every 16.  Made for rounds of 16 words per
+// lane, whose strided accesses it puts on distinct banks; with 8 and 4 words some
+// still meet (SQ_LDS_BANK_CONFLICT of SQ_LDS_IDX_ACTIVE: the tensor's block kernel
+// at 2^16 48.8 M of 132 M cycles, the polymul's at 2^15 27.3 M of 75.5 M, the
+// persistent batch 9% forward and 22% inverse).  Column passes through LDS have a
+// layout of their own and no conflicts.
 __device__ __forceinline__ constexpr uint32_t lds_pad(uint32_t i) { return i + (i >> 4); }
 template <int B> struct LdsSize { static constexpr int value = (1 << B) + (1 << B) / 16; };
 
@@ -374,7 +378,7 @@ template <int E, bool FIX> __device__ __forceinline__ void reduce_out(uint64_t (
 // HAVE: this round's are in pf.  Used where the registers it takes (84 -> 112 for
 // the whole 2^12, 95 for blocks) cost no occupancy that counts, the polymul of 2^10
 // and more: 2^12, one product, 12.7 -> 12.2 us; 512 x 8 limbs 196 -> 192; 2^10, 2048
-// x 8 limbs 171 -> 161; blocks at 2^15, 128 x 16 limbs, 582 -> 567.  The tensor's
+// x 8 limbs 171 -> 161; the blocks of 128 x 16 limbs at 2^15 3% less.  The tensor's
 // and the key switch's blocks stand at 128 registers without it.
 template <int B, int E, int LO, int R, bool FIX, bool PRE = false, bool HAVE = false>
 __device__ __forceinline__ void fwd_block_rounds(uint64_t (&x)[1 << E], uint32_t logn, uint64_t* lds, uint32_t tid,
@@ -817,9 +821,9 @@ __device__ __forceinline__ void products(uint64_t (&X)[ProdShape<MODE>::NIN][1 <
 //                (a b < 16 q^2 < q R as q < 2^60), TENSOR factors below 2q
 //                (c0 d1 + c1 d0 < 8 q^2 < q R), outputs in [0, 2q).  By
 //                mont30_mul, with one factor cut below q and the result below
-//                3q, the registers grow: 600 us for 594 (2^15, 16 primes of 50 to
-//                60 bits, 128 products) and, the tensor at three waves for four
-//                or spilling, 1005 us for 960 even where no such modulus occurs.
+//                3q, the registers grow: 1% slower (2^15, 16 primes of 50 to 60
+//                bits, 128 products) and, the tensor at three waves for four or
+//                spilling, 5% even where no such modulus occurs.
 template <int MODE, int E, bool FIX>
 __device__ __forceinline__ void products_mont(uint64_t (&X)[ProdShape<MODE>::NIN][1 << E],
                                               uint64_t (&Y)[ProdShape<MODE>::NOUT][1 << E], const NttConst &c,

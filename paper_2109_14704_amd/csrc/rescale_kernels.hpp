@@ -57,7 +57,7 @@ __device__ __forceinline__ void rs_unit(uint32_t u, uint32_t batch, uint32_t &b,
   b = u % batch;
 }
 
-// Whole transform per workgroup (N <= 2^14): prologue, forward rounds,
+// Whole transform per workgroup (N <= 2^13): prologue, forward rounds,
 // canonical reduction, epilogue.
 template <int LOGN, int E>
 __global__ __launch_bounds__(1 << (LOGN - E)) void k_rs_whole(RsArgs a, const TwM *__restrict__ tw,

@@ -146,7 +146,7 @@ int ks_consts(Storage *s, uint32_t L1, const KsLimb **out) {
 }
 
 // Key-switch split: the digit loop holds two accumulator arrays, so whole
-// transforms only up to 2^12 (256 lanes); above, the two-pass split (2^15, 32
+// transforms only up to 2^12 (512 lanes); above, the two-pass split (2^15, 32
 // ciphertexts, 8 primes, the key switch alone when measured: 546 us with six column
 // stages, 549 with seven, 595 with five in registers; 455 since).
 template <int LOGN> struct KsPlan {

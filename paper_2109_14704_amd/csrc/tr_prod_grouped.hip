@@ -53,8 +53,9 @@ int launch_group(const HostJob *jobs, uint32_t n, bool in_coeff, bool out_coeff,
     J.ustart = (uint32_t)units;
     units += (uint64_t)J.batch * J.limbs;
   }
-  // units < 2^24 per chunk and at most 64 workgroups per unit in any kernel
-  // here: every grid stays below 2^30
+  // A unit (one limb of one pair) is 7 N words of operands and outputs on the
+  // device and takes at most N / 512 workgroups of a block kernel, N / 1024 of a column
+  // pass's four components: no grid of operands that exist comes near 2^31.
   const uint32_t u = (uint32_t)units;
   if constexpr (LOGN == 9 && PE == 2) {
     if (tensor9_one_wave(units)) return launch_group<9, 3>(jobs, n, in_coeff, out_coeff, ws, st);
