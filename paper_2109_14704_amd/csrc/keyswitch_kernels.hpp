@@ -214,8 +214,8 @@ __global__ __launch_bounds__(cols_lanes<EC>(), EC < 8 ? 4 : 1) void k_ks_cols(Ks
 }
 
 // Two-pass sizes, pass 2: per (batch entry, target prime, block), the block
-// rounds of every digit, accumulated with the key in registers.  VALU-bound: 300 to
-// 320 us, its bytes take 120 at the copy rate.  At N = 2^15, 8 primes, 32 entries, the
+// rounds of every digit, accumulated with the key in registers.  300 to 320 us, VALU
+// busy 60% of a counter run; its 0.93 GB take 190 at the copy rate.  At N = 2^15, 8 primes, 32 entries, the
 // whole relinearization: 720 us with Montgomery products of 64-bit words, 690 with
 // mont30_mul at the 134 VGPRs it takes (three waves per SIMD), 678 held to 128
 // (four waves), 600 with the column passes fused.  The key in root-power form, a third fewer
