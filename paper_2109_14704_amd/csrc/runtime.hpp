@@ -76,6 +76,12 @@ int shoup_pairs(Storage *s, const Tw **out);
 // buffer that the pool holds already is given (HENTT_ENOMEM if there is none).
 int pool_get(size_t bytes, hipStream_t stream, void **out, bool grow = true);
 void pool_put(void *p);
+// Whether work enqueued on `stream` goes into a capture.
+inline bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+  return cap != hipStreamCaptureStatusNone;
+}
 
 // ------------------------------------------------------------ launch timing
 // While enabled (hentt_prof_enable), every launch is bracketed by HIP events

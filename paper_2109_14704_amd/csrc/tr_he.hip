@@ -260,9 +260,12 @@ int run_relin(const hentt_tables *t, const uint64_t *c, const uint64_t *ksk, uin
   const size_t e_bytes = two_pass ? (size_t)batch * l * L1 * N * 8 : 0;
   const uint64_t waves = (uint64_t)batch * L1 * N >> 9;
   uint32_t splits = two_pass ? (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(l / 2, kKsWaves / waves)) : 1;
+  // The partial sums only make the call faster: where the pool cannot grow for them
+  // (memory, or a capture, which an allocation would end), it does without.
   void *buf = nullptr;
-  rc = pool_get(d_bytes + acc_bytes + e_bytes + (splits > 1 ? splits * acc_bytes : 0), st, &buf);
-  if (rc == HENTT_ENOMEM && splits > 1) {  // only faster: do without the partial sums
+  rc = pool_get(d_bytes + acc_bytes + e_bytes + (splits > 1 ? splits * acc_bytes : 0), st, &buf,
+                splits == 1 || !capturing(st));
+  if (rc == HENTT_ENOMEM && splits > 1) {
     splits = 1;
     rc = pool_get(d_bytes + acc_bytes + e_bytes, st, &buf);
   }

@@ -78,9 +78,7 @@ int run_prod(const hentt_tables *t, int mode, const ProdArgs &pa, uint32_t batch
     // Where a whole instance exists, the workspace only makes the call faster: it is
     // not allocated into a capture (which an allocation would end), and done without
     // when it cannot be had.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (whole && hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
-    int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws, cap == hipStreamCaptureStatusNone);
+    int rc = pool_get((size_t)nin * piece * NL * 8ull, st, &ws, !whole || !capturing(st));
     if (rc == HENTT_ENOMEM && whole) c = whole;
     else if (rc) return rc;
   }

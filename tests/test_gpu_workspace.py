@@ -1,5 +1,7 @@
-"""The product at N = 2^13 runs with or without a workspace: captured with no
-buffer in the pool, and where the device has no room for one."""
+"""Calls that only take more workspace to be faster run without it: the product at N =
+2^13, captured with no buffer in the pool and where the device has no room for one;
+the key switch of a small batch, captured with a buffer that holds all but its
+partial sums."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +59,38 @@ def test_polymul_without_room_for_the_workspace(gpu):
     finally:
         del filler, a, b, out
         torch.cuda.empty_cache()
+
+
+def test_relin_captured_with_room_for_all_but_the_partial_sums(gpu):
+    import paper_2109_14704_amd as H
+    print("case relin 2^13 captured, pool short of the partial sums", flush=True)
+    l = 8
+    mods = primes(55, LOG_N, l + 1)
+    rng = np.random.default_rng(15)
+    t = H.Tables(LOG_N, mods)
+    c, ksk = words(rng, (1, 3, l, N), mods[:l]), words(rng, (l, 2, l + 1, N), mods)
+    cd, kd = dev(c, gpu), dev(ksk, gpu)
+    out = H.relin(t, cd, kd)              # the level's constants
+    big = H.Tables(14, primes(55, 14))
+    a = torch.zeros((30, 1, 2 * N), dtype=torch.int64, device=gpu)
+    o = torch.empty_like(a)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    H.pool_trim()
+    # the pool's buffers for this stream: 2 N words for the rescale inside, 120 N for the key
+    # switch, which needs 98 N and 72 N more for partial sums of 4
+    H.rescale(t.view(2), torch.zeros((2, 2, N), dtype=torch.int64, device=gpu), ntt=True, stream=s)
+    H.polymul(big, a, a, out=o, stream=s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        H.relin(t, cd, kd, out=out)
+    for _ in range(3):
+        c = words(rng, (1, 3, l, N), mods[:l])
+        cd.copy_(dev(c, gpu))
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        want = oracle.relin(c, ksk, mods)
+        assert np.array_equal(host(out), want)
+        assert np.array_equal(host(H.relin(t, cd, kd)), want)
